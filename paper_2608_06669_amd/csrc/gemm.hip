@@ -1,5 +1,8 @@
 // Matrix-core GEMM for gfx950 (CDNA4), FP64 / FP32 / BF16 compute.
 //
+// FP64 products run in gemm_f64_pipe (gemm_f64.hpp), BF16 ones of packed
+// operands in gemm_bf16_pipe; the others in gemm_kernel:
+//
 // One workgroup = 4 wavefronts of 64 lanes computes a BM x BN tile of C.
 // The waves form a WGM x WGN grid; each wave owns (BM/WGM) x (BN/WGN)
 // outputs as a grid of matrix-core instruction tiles held in registers for
@@ -15,8 +18,9 @@
 //   f64  4x4x4 (4 blocks), used as one 4 x 16 x 4 product:
 //        A[i][k] at i = l%4, k = l/16 (the same for the 4 blocks);
 //        B[k][j] at j = l%16, k = l/16;  D[i][j] at i = l/16, j = l%16.
-//        On gfx950 this instruction runs at the full FP64 matrix rate,
-//        while the 16x16x4 f64 instruction reaches about two thirds of it.
+//        On gfx950 this instruction runs at the full FP64 matrix rate (75 to
+//        77 TFLOP/s with operands in registers), while the 16x16x4 f64
+//        instruction reaches 36 to 48.
 //   f32  16x16x4:  A[i][k] at i = l%16, k = l/16;  B[k][j] at j = l%16;
 //        D[i][j] at j = l%16, i = 4*(l/16) + r, r = 0..3
 //   bf16 16x16x32: A[i][k..k+7] at i = l%16, k = 8*(l/16); B likewise;
@@ -33,6 +37,7 @@
 // never depend on timing.
 
 #include "gemm.hpp"
+#include "gemm_f64.hpp"
 #include "mfma_tiles.hpp"
 
 #include <algorithm>
@@ -61,21 +66,6 @@ struct KArgs {
   double alpha, beta;
 };
 
-// LDS row padding of an FP64 panel stored [k][rows + pad]. The 4x4x4 f64
-// reads take, per k, 4 consecutive values of A or 16 of B; half a wave (two
-// k rows) is served per LDS cycle, so the two rows must fall on disjoint
-// banks (64 banks of 4 bytes): a row stride of 9 modulo 32 doubles offsets
-// them by 18 banks, 16 modulo 32 by 32 banks (the 16-value B reads need
-// that). A panel loaded along k (KC) is written one value per lane at a
-// stride of two rows, which a 16-modulo-32 stride turns into an 8-way
-// conflict, so those panels take 9. Other compute types keep kPad.
-template <class Mma, int ROWS, bool KC, bool IS_B>
-constexpr int lds_pad() {
-  if constexpr (sizeof(typename Mma::L) != 8) return kPad;
-  const int want = (IS_B && !KC) ? 16 : 9;
-  return ((want - ROWS) % 32 + 32) % 32;
-}
-
 template <class Mma, typename TA, typename TB, typename TC, int BM, int BN, int BK, int WGM, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(256) void gemm_kernel(KArgs p) {
   using L = typename Mma::L;
@@ -85,8 +75,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(KArgs p) {
   constexpr int TMI = WTM / Mma::TM, TNI = WTN / Mma::TN;
   static_assert(WTM % Mma::TM == 0 && WTN % Mma::TN == 0, "wave tile must split into instruction tiles");
   static_assert(BK % Mma::KSTEP == 0, "BK must be a multiple of the MFMA depth");
-  constexpr int PA = lds_pad<Mma, BM, A_KC, false>();
-  constexpr int PB = lds_pad<Mma, BN, B_KC, true>();
+  constexpr int PA = kPad, PB = kPad;
   constexpr int ALDS = lds_elems<Mma, BM, BK, PA>();
   constexpr int BLDS = lds_elems<Mma, BN, BK, PB>();
   __shared__ __attribute__((aligned(16))) L As[2][ALDS];
@@ -493,167 +482,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_pipe(KArgs p) {
   }
 }
 
-// FP64 product, A k-contiguous, B k-contiguous (B_KC) or n-contiguous, the
-// contraction a multiple of 16: 64 x 64 tiles, 16-deep panels loaded
-// straight into LDS (16 bytes = two doubles per lane) in a ring of three
-// stages, as in gemm_bf16_pipe. A k-contiguous operand is stored [row][16]
-// with the eight 16-byte chunks of a row at slot chunk ^ (row % 8); B
-// n-contiguous is stored [k][64] with its 32 chunks at slot chunk ^ (8 (k %
-// 4)): the 4 x 4 x 4 operand reads (4 rows x 4 k of A, 16 columns x 4 k of
-// B per instruction) then fall on distinct banks. A second product (A2,
-// B2) continues the same k loop into the same accumulators.
-template <bool B_KC>
-__global__ __launch_bounds__(256, 2) void gemm_f64_pipe(KArgs p) {
-  constexpr int BM = 64, BN = 64, BK = 16, STAGES = 3, AE = BM * BK, SE = AE + BN * BK;
-  __shared__ __attribute__((aligned(1024))) double st0[SE], st1[SE], st2[SE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-
-  const int ntiles = p.tiles_m * p.tiles_n;
-  int bid = blockIdx.x;
-  {
-    const int q = ntiles >> 3, r = ntiles & 7, x = bid & 7;
-    bid = x * q + min(x, r) + (bid >> 3);
-  }
-  constexpr int kGroupM = 8;
-  const int gsize = kGroupM * p.tiles_n;
-  const int grp = bid / gsize;
-  const int first_m = grp * kGroupM;
-  const int gm = min(p.tiles_m - first_m, kGroupM);
-  const int rem = bid - grp * gsize;
-  const int m0 = (first_m + rem % gm) * BM;
-  const int n0 = (rem / gm) * BN;
-
-  const int split = blockIdx.z % p.splits;
-  const int zb = blockIdx.z / p.splits;
-  const int b0 = blockIdx.y % p.nb0;
-  const int b1 = blockIdx.y / p.nb0 + zb * (gridDim.y / p.nb0);
-  const int kbeg = split * p.kchunk;
-  const int nk1 = (min(p.K, kbeg + p.kchunk) - kbeg) / BK;  // >= 1
-  const bool dual = p.A2 != nullptr;
-  const int nk = dual ? 2 * nk1 : nk1;
-  const int64_t lda = p.a_m, ldb = B_KC ? p.b_n : p.b_k;
-  const int64_t aoff = b0 * p.a_b0 + b1 * p.a_b1 + kbeg;
-  const int64_t boff = b0 * p.b_b0 + b1 * p.b_b1 + (B_KC ? kbeg : (int64_t)kbeg * ldb);
-  double* __restrict__ Cg = (double*)p.C + b0 * p.c_b0 + b1 * p.c_b1;
-
-  // this thread's chunks c = j 256 + tid, j = 0, 1, of A and of B (offsets
-  // within an operand; rows and columns past the matrix read its last ones,
-  // whose outputs are not written)
-  int64_t oa[2], ob[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int c = j * 256 + tid;
-    {
-      const int r = c >> 3, g = (c & 7) ^ (r & 7);
-      oa[j] = (int64_t)min(m0 + r, p.M - 1) * lda + 2 * g;
-    }
-    if constexpr (B_KC) {
-      const int r = c >> 3, g = (c & 7) ^ (r & 7);
-      ob[j] = (int64_t)min(n0 + r, p.N - 1) * ldb + 2 * g;
-    } else {
-      const int k = c >> 5, g = (c & 31) ^ (8 * (k & 3));
-      ob[j] = (int64_t)k * ldb + min(n0 + 2 * g, p.N - 2);
-    }
-  }
-  const double* A1 = (const double*)p.A + aoff;
-  const double* B1 = (const double*)p.B + boff;
-  const double* A2 = dual ? (const double*)p.A2 + aoff : A1;
-  const double* B2 = dual ? (const double*)p.B2 + boff : B1;
-  // panel t into stage st (past the last panel: the last one again, never read)
-  auto issue = [&](double* st, int t) {
-    t = min(t, nk - 1);
-    const bool second = t >= nk1;
-    const int k0 = (second ? t - nk1 : t) * BK;
-    const double* Ab = (second ? A2 : A1) + k0;
-    const double* Bb = (second ? B2 : B1) + (B_KC ? (int64_t)k0 : (int64_t)k0 * ldb);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_global_load_lds(Ab + oa[j], (__attribute__((address_space(3))) void*)(st + (j * 256 + wave * 64) * 2),
-                                       16, 0, 0);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_global_load_lds(Bb + ob[j],
-                                       (__attribute__((address_space(3))) void*)(st + AE + (j * 256 + wave * 64) * 2),
-                                       16, 0, 0);
-  };
-  double acc[8][2];
-#pragma unroll
-  for (int a = 0; a < 8; ++a) acc[a][0] = acc[a][1] = 0.0;
-  auto compute = [&](const double* st) {
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 4) {
-      const int k = ks + (lane >> 4);
-      double af[8], bf[2];
-#pragma unroll
-      for (int a = 0; a < 8; ++a) {
-        const int m = wm * 32 + a * 4 + (lane & 3);
-        af[a] = st[m * BK + 2 * ((k >> 1) ^ (m & 7)) + (k & 1)];
-      }
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int n = wn * 32 + b * 16 + (lane & 15);
-        if constexpr (B_KC) bf[b] = st[AE + n * BK + 2 * ((k >> 1) ^ (n & 7)) + (k & 1)];
-        else bf[b] = st[AE + k * BN + 2 * ((n >> 1) ^ (8 * (k & 3))) + (n & 1)];
-      }
-#pragma unroll
-      for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_4x4x4f64(af[a], bf[b], acc[a][b], 0, 0, 0);
-    }
-  };
-  issue(st0, 0);
-  issue(st1, 1);
-  // step t: panel t's 4 loads per thread landed (the next panel's 4 may be
-  // in flight) and this wave's earlier LDS reads done, then a plain barrier,
-  // the refill of the stage read at step t - 1, and panel t
-  auto step = [&](int t, const double* cur, double* nxt) {
-    wait_vm_lgkm0<4 * (STAGES - 2)>();
-    __builtin_amdgcn_s_barrier();
-    issue(nxt, t + STAGES - 1);
-    compute(cur);
-  };
-  int t = 0;
-  for (; t + 3 <= nk; t += 3) {
-    step(t, st0, st2);
-    step(t + 1, st1, st0);
-    step(t + 2, st2, st1);
-  }
-  if (t < nk) step(t, st0, st2);
-  if (t + 1 < nk) step(t + 1, st1, st0);
-  wait_vm_lgkm0<0>();
-
-  const double alpha = p.alpha, beta = p.beta;
-  auto row_of = [&](int a) { return m0 + wm * 32 + a * 4 + (lane >> 4); };
-  auto col_of = [&](int b) { return n0 + wn * 32 + b * 16 + (lane & 15); };
-  if (p.splits > 1) {
-    double* __restrict__ W = p.ws + ((int64_t)split * p.nbtot + (int64_t)b1 * p.nb0 + b0) * p.M * p.N;
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-        if (row_of(a) < p.M && col_of(b) < p.N) W[(int64_t)row_of(a) * p.N + col_of(b)] = acc[a][b];
-  } else if (beta == 0.0) {
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-        if (row_of(a) < p.M && col_of(b) < p.N) Cg[row_of(a) * p.c_m + col_of(b) * p.c_n] = alpha * acc[a][b];
-  } else {
-    double cv[8][2];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) cv[a][b] = Cg[min(row_of(a), p.M - 1) * p.c_m + min(col_of(b), p.N - 1) * p.c_n];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-        if (row_of(a) < p.M && col_of(b) < p.N)
-          Cg[row_of(a) * p.c_m + col_of(b) * p.c_n] = alpha * acc[a][b] + beta * cv[a][b];
-  }
-}
-
 // Products with a short contraction (K <= kSmallK) and a short output side
 // (<= kSmallSide): a matrix-core tile would be mostly padding and the cost
 // is one pass over the long operand. Each lane owns one index of the long
@@ -768,18 +596,16 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
   const bool bkc = d.b_k == 1 && d.b_n != 1;
   p.a_vec = vec_ok<TA>(A, d.a_m, d.a_k, d.a_b0, d.a_b1, akc) && (!A2 || vec_ok<TA>(A2, d.a_m, d.a_k, d.a_b0, d.a_b1, akc));
   p.b_vec = vec_ok<TB>(B, d.b_n, d.b_k, d.b_b0, d.b_b1, bkc) && (!A2 || vec_ok<TB>(B2, d.b_n, d.b_k, d.b_b0, d.b_b1, bkc));
+  constexpr bool f64 = sizeof(typename Mma::L) == 8;
+  if (f64) p.a_vec = p.b_vec = 0;  // operands contiguous along neither index
   // split-K when the output tiles cannot fill the GPU
   int splits = 1;
   const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n * nb;
   // (short contractions are not split: the extra pass over the partial sums
   // would cost more than the product). About 900 workgroups in all (3.5 per
-  // CU): for the o v x o v products of the rotated 10/90 workload that is 4
-  // chunks, 10 % faster than 3 (a sweep over 3..12); thin products with a
-  // long contraction stay near 512 (8 chunks for the ladder, its best).
-  // Long contractions with fewer than 512 tiles (one or two workgroups per
-  // CU, each walking thousands of k steps) are split too: the T1 part of
-  // the ladder at o=20/v=180 (400 x 3600 x 32400, 399 tiles) ran at 22
-  // TFLOP/s unsplit.
+  // CU); thin products with a long contraction stay near 512. Long
+  // contractions with fewer than 512 tiles (one or two workgroups per CU,
+  // each walking thousands of k steps) are split too.
   // gridDim.y * gridDim.z covers the batch; y is a multiple of nb0, and z
   // also carries the chunks
   int64_t gy = d.nb0, gz = d.nb1;
@@ -787,32 +613,7 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
   const bool thin = d.M <= 64 && d.K >= 1024;
   const int64_t ws_fit =
       d.ws ? std::min<int64_t>(d.ws_elems / std::max<int64_t>(1, nb * d.M * d.N), 65535 / gz) : 0;
-  constexpr bool f64 = sizeof(typename Mma::L) == 8;
-  if (f64 && d.ws && ((d.K >= 8192 && tiles < 2048) || (d.K >= 2048 && tiles >= 256 && tiles < 1024))) {
-    // Long FP64 contractions: split so that the work items (tiles x
-    // chunks) reach about 2048 of 64 x 64 tiles' worth (8 per CU, enough
-    // resident workgroups to hide latency) and fill the 256 CUs in whole
-    // rounds; up to 8 chunks for a few hundred tiles or more, up to 1024 for
-    // a handful (thin products streaming a long operand). Contractions of
-    // 2048 or more with a few hundred tiles (2 or 3 per CU, unevenly) are
-    // split the same way (the 600 x 3600 x 3600 DF product at o = 20, v =
-    // 180: 570 tiles). At o = 20, v = 180
-    // this took the antisymmetric ladder (756 tiles) from 3.0 to 2.5 ms with
-    // 3 chunks and the symmetric one (384 tiles of 72 x 128) to 2.7 ms with
-    // 4 (3 chunks, 4.5 rounds: 3.15).
-    const double target = 2048.0 * 4096.0 / (BM * BN);
-    const int64_t cap = tiles >= 256 ? 8 : 1024;
-    double best = -1.0;
-    for (int64_t sp = 1; sp <= cap && sp <= d.K / (2 * BK) && sp <= ws_fit; ++sp) {
-      const int64_t items = tiles * sp;
-      const double fill = std::min(1.0, (double)items / target);
-      const double rounds = (double)items / (double)(ceil_div(items, 256) * 256);
-      if (fill * rounds > best + 1e-9) {
-        best = fill * rounds;
-        splits = (int)sp;
-      }
-    }
-  } else if (d.ws && d.K >= 256 && (tiles < 256 || (tiles < 512 && d.K >= 8192))) {
+  if (d.ws && d.K >= 256 && (tiles < 256 || (tiles < 512 && d.K >= 8192))) {
     int64_t want = ceil_div(thin ? 512 : 900, tiles);
     want = std::min<int64_t>(want, d.K / (2 * BK));
     want = std::min<int64_t>(want, ws_fit);
@@ -830,12 +631,6 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
   constexpr bool pipe_cfg = std::is_same<Mma, MmaBF16>::value && std::is_same<TA, uint16_t>::value &&
                             std::is_same<TB, uint16_t>::value && std::is_same<TC, double>::value && BM == 128 &&
                             BN == 128 && BK == 64;
-  // FP64, A k-contiguous, B k- or n-contiguous (an even number of columns),
-  // whole 16-deep panels, 16-byte rows: the pipelined FP64 kernel
-  constexpr bool f64_cfg = std::is_same<Mma, MmaF64>::value && std::is_same<TA, double>::value &&
-                           std::is_same<TB, double>::value && std::is_same<TC, double>::value && BM == 64 && BN == 64 &&
-                           BK == 16;
-  const bool bnc = d.b_n == 1 && d.b_k != 1;
   auto reduce = [&](const KArgs& q) {
     if (q.splits <= 1) return;
     const int64_t total = nb * d.M * d.N;
@@ -878,10 +673,8 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
   }
   if (pipe_cfg && akc && bkc && !A2 && d.K % 64 == 0 && p.a_vec && p.b_vec) {
     gemm_bf16_pipe<128, 4><<<grid, 256, 0, s>>>(p);
-  } else if (f64_cfg && akc && d.K % 16 == 0 && p.a_vec && p.b_vec && d.M >= 2 && (bkc || (bnc && d.N % 2 == 0))) {
-    if (bkc) gemm_f64_pipe<true><<<grid, 256, 0, s>>>(p);
-    else gemm_f64_pipe<false><<<grid, 256, 0, s>>>(p);
-  } else if (akc && bkc) gemm_kernel<Mma, TA, TB, TC, BM, BN, BK, WGM, true, true><<<grid, 256, 0, s>>>(p);
+  } else if constexpr (f64) gemm_kernel<Mma, TA, TB, TC, BM, BN, BK, WGM, false, false><<<grid, 256, 0, s>>>(p);
+  else if (akc && bkc) gemm_kernel<Mma, TA, TB, TC, BM, BN, BK, WGM, true, true><<<grid, 256, 0, s>>>(p);
   else if (akc) gemm_kernel<Mma, TA, TB, TC, BM, BN, BK, WGM, true, false><<<grid, 256, 0, s>>>(p);
   else if (bkc) gemm_kernel<Mma, TA, TB, TC, BM, BN, BK, WGM, false, true><<<grid, 256, 0, s>>>(p);
   else gemm_kernel<Mma, TA, TB, TC, BM, BN, BK, WGM, false, false><<<grid, 256, 0, s>>>(p);
@@ -890,66 +683,149 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
 }
 
 
-// Tile choice. FP64: 64 x 64 with 16-deep panels (a sweep over 32/64/96/128
-// x 64 tiles and 16/32-deep panels on MI355X put it at or within 3 % of the
-// best for square products from 900 to 3600); row counts that 72-row tiles
-// fit much better take 72 x 128; thin products (at most 64 rows) with a
-// long contraction stream their wide operand from HBM and take 32-deep
-// panels (about 20 % faster there).
-// FP32/BF16: 128 x 128. Small products: 64 x 64 (split-K fills the GPU).
+// ---- FP64: gemm_f64_pipe ----
+
+// An operand's layout for gemm_f64_pipe: contiguous along k (kc) or along its
+// row index, the stride of the other index, and whether 16-byte loads apply.
+struct F64Layout {
+  bool ok, kc, vec;
+  int64_t ld;
+};
+F64Layout f64_layout(const void* x, const void* x2, int rows, int K, int64_t s_r, int64_t s_k, int64_t s_b0, int64_t s_b1) {
+  F64Layout l;
+  l.kc = s_k == 1 || K == 1;
+  l.ok = l.kc || s_r == 1 || rows == 1;
+  const int64_t ld = l.kc ? s_r : s_k;
+  l.ld = (l.kc ? rows : K) == 1 ? 0 : ld;
+  // the kernel keeps a tile's offsets in 32 bits
+  l.ok = l.ok && l.ld >= 0 && l.ld < (int64_t(1) << 22);
+  l.vec = aligned16(x) && (!x2 || aligned16(x2)) && l.ld % 2 == 0 && s_b0 % 2 == 0 && s_b1 % 2 == 0 &&
+          (l.kc ? K : rows) % 2 == 0;
+  return l;
+}
+
+// How many tiles run in one piece (nfull) and into how many chunks along K
+// the others are cut (ts), by the estimated time. In units of one 64 x 64
+// tile's whole contraction at full matrix rate on its CU (512 cycles for each
+// 8-deep panel, about 0.235 us of a CU's time; 0.27 with 4-byte loads; a 64 x
+// 128 tile 0.456), w units of work per CU take w / e with e the share of the
+// matrix rate that the c workgroups resident on a CU reach (measured; a
+// little less where every one ends at once). Chunk sums cost a launch (5 us)
+// and their bytes twice at 4 TB/s. Checked on MI355X against every (nfull,
+// ts) of a sweep over 45 products, 64^3 to 3600^3 and 20 x 20 x 648000 among
+// them: the choice is within 5 % of the best for most and 12 % for the
+// worst. 3600^3 takes 1691 us in whole tiles and 1508 with its last 177 tiles
+// in four chunks; 90 x 90 x 9000 562 us in one piece, 20 us in 63.
+struct F64Plan {
+  int64_t nfull;
+  int ts;
+};
+F64Plan f64_plan(int64_t tiles, int bn, int K, int64_t sum_elems, int64_t ws_elems, bool vec, bool dual) {
+  const double unit = (double)ceil_div(K, 8) * (dual ? 2 : 1) * (bn == 128 ? 0.456 : vec ? 0.235 : 0.27);
+  auto rate = [&](int64_t c, bool together) {
+    static const double e[2][2][4] = {{{0.50, 0.72, 0.85, 0.90}, {0.50, 0.65, 0.78, 0.82}},
+                                      {{0.76, 0.85, 0.90, 0.92}, {0.76, 0.74, 0.85, 0.85}}};
+    return e[bn == 128][together][std::min<int64_t>(c, 4) - 1];
+  };
+  F64Plan best{tiles, 1};
+  const int64_t c0 = ceil_div(tiles, 256);
+  double t_best = c0 <= 4 ? c0 / rate(c0, true) * unit : ((tiles / 256) / 0.9 + (tiles % 256 ? 1.0 / 0.6 : 0.0)) * unit;
+  if (K < 64 || ws_elems <= 0) return best;
+  static const int kCuts[] = {2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
+  const int64_t whole = tiles / 256 * 256;
+  const int64_t fulls[3] = {0, whole, whole - 256};
+  for (int q = 0; q < 3; ++q) {
+    const int64_t nfull = fulls[q], tail = tiles - nfull;
+    if (nfull < 0 || tail == 0 || (q > 0 && nfull == 0)) continue;
+    for (int ts : kCuts) {
+      if ((int64_t)ts * 32 > K || ts * tail * sum_elems > ws_elems) break;
+      const int64_t items = tail * ts;
+      const double w = (double)(nfull / 256) +
+                       (nfull + items > 1024 ? items / 256.0 + 0.3 : (double)ceil_div(items, 256)) / ts +
+                       (nfull == 256 ? 0.35 : nfull == 512 ? 0.1 : 0.0);  // (whole tiles outlast the chunks)
+      const double t = w / rate(ceil_div(nfull + items, 256), false) * unit + 5.0 + (double)items * sum_elems * 16.0 / 4e6;
+      if (t < 0.98 * t_best) {
+        t_best = t;
+        best = F64Plan{nfull, ts};
+      }
+    }
+  }
+  return best;
+}
+
+template <int BN, bool A_KC, bool B_KC>
+void launch_f64_layout(const f64pipe::Args& p, bool vec, unsigned grid, hipStream_t s) {
+  if (vec) f64pipe::gemm_f64_pipe<64, BN, A_KC, B_KC, true><<<grid, 256, 0, s>>>(p);
+  else f64pipe::gemm_f64_pipe<64, BN, A_KC, B_KC, false><<<grid, 256, 0, s>>>(p);
+}
+
+template <int BN>
+void launch_f64_tiles(f64pipe::Args p, const F64Layout& la, const F64Layout& lb, int64_t nb, int64_t ws_elems, hipStream_t s) {
+  const bool vec = la.vec && lb.vec;
+  p.tm = (int)ceil_div(p.M, 64);
+  p.tn = (int)ceil_div(p.N, BN);
+  p.wr = std::min(p.M, 64);
+  p.wc = std::min(p.N, BN);
+  const int64_t tiles = (int64_t)p.tm * p.tn * nb;
+  const F64Plan plan = f64_plan(tiles, BN, p.K, (int64_t)p.wr * p.wc, ws_elems, vec, p.A2 != nullptr);
+  PNK_REQUIRE(tiles * plan.ts < (int64_t(1) << 31), "gemm: batch too large");
+  p.kchunk = plan.ts > 1 ? (int)(ceil_div(ceil_div(p.K, plan.ts), 8) * 8) : p.K;
+  p.ts = (int)ceil_div(p.K, p.kchunk);  // no empty chunk
+  p.nfull = (int)(p.ts > 1 ? plan.nfull : tiles);
+  p.ntail = (int)(tiles - p.nfull);
+  const unsigned grid = (unsigned)(p.nfull + (int64_t)p.ntail * p.ts);
+  if (la.kc && lb.kc) launch_f64_layout<BN, true, true>(p, vec, grid, s);
+  else if (la.kc) launch_f64_layout<BN, true, false>(p, vec, grid, s);
+  else if (lb.kc) launch_f64_layout<BN, false, true>(p, vec, grid, s);
+  else launch_f64_layout<BN, false, false>(p, vec, grid, s);
+  PNK_CHECK_LAUNCH();
+  if (p.ntail) {
+    const int n = p.wr * p.wc;
+    if (p.ts >= 32)
+      f64pipe::gemm_f64_reduce_wide<64, BN><<<dim3((unsigned)p.ntail, (unsigned)ceil_div(n, 16)), 256, 0, s>>>(p);
+    else
+      f64pipe::gemm_f64_reduce<64, BN><<<dim3((unsigned)p.ntail, (unsigned)ceil_div(n, 256)), 256, 0, s>>>(p);
+    PNK_CHECK_LAUNCH();
+  }
+}
+
+// False if an operand is contiguous along neither index.
+bool launch_f64(const GemmDesc& d, const double* A, const double* B, const double* A2, const double* B2, double* C,
+                hipStream_t s) {
+  const F64Layout la = f64_layout(A, A2, d.M, d.K, d.a_m, d.a_k, d.a_b0, d.a_b1);
+  const F64Layout lb = f64_layout(B, B2, d.N, d.K, d.b_n, d.b_k, d.b_b0, d.b_b1);
+  if (!la.ok || !lb.ok) return false;
+  f64pipe::Args p{};
+  p.M = d.M; p.N = d.N; p.K = d.K; p.nb0 = d.nb0;
+  p.A = A; p.B = B; p.A2 = A2; p.B2 = A2 ? B2 : nullptr;
+  p.lda = la.ld; p.a_b0 = d.a_b0; p.a_b1 = d.a_b1;
+  p.ldb = lb.ld; p.b_b0 = d.b_b0; p.b_b1 = d.b_b1;
+  p.C = C; p.c_m = d.c_m; p.c_n = d.c_n; p.c_b0 = d.c_b0; p.c_b1 = d.c_b1;
+  p.alpha = d.alpha; p.beta = d.beta;
+  p.ws = d.ws;
+  const int64_t nb = (int64_t)d.nb0 * d.nb1, ws = d.ws ? d.ws_elems : 0;
+  // The largest products hold the chip at its power limit (the instruction
+  // alone then reaches 72 TFLOP/s), where 64 x 128 tiles, which read LDS and
+  // L2 less for each flop, are 1 to 5 % faster: 3600^3 1441 against 1508 us,
+  // 400 x 3600 x 32400 1692 against 1767. Below about 1e10 multiplications
+  // their coarser rounds cost more than that (600 x 3600 x 3600 306 against
+  // 292 us).
+  const bool wide = d.K >= 2048 && (double)d.M * d.N * d.K * nb >= 1e10;
+  if (wide) launch_f64_tiles<128>(p, la, lb, nb, ws, s);
+  else launch_f64_tiles<64>(p, la, lb, nb, ws, s);
+  return true;
+}
+
+// Tile choice. FP32/BF16: 128 x 128. Small products: 64 x 64 (split-K fills
+// the GPU). FP64: gemm_f64_pipe; an operand contiguous along neither index
+// takes the register-staged 64 x 64 kernel.
 template <class Mma, typename TA, typename TB, typename TC, int BK>
 void launch_sized(const GemmDesc& d, const void* A, const void* B, const void* A2, const void* B2, void* C,
                   hipStream_t s) {
   const int64_t nb = (int64_t)d.nb0 * d.nb1;
   if constexpr (sizeof(typename Mma::L) == 8) {
-    // long contractions of more than 64 rows that the pipelined FP64 kernel
-    // takes (A k-contiguous with 16-byte rows, B k-contiguous or
-    // n-contiguous with an even column count): its 64 x 64 tiles before the
-    // 72/80-row rules below (thin products keep their 32-deep tiles); a
-    // contraction that is not a whole number of 16-deep panels runs its
-    // last K % 16 columns as a second product added into C (the ladders at
-    // o = 20, v = 180: K = 16290 and 16110)
-    const bool akc = d.a_k == 1 && d.a_m != 1, bkc = d.b_k == 1 && d.b_n != 1, bnc = d.b_n == 1 && d.b_k != 1;
-    const bool pipe_ok =
-        akc && d.M > 64 && d.K >= 1024 && (bkc || (bnc && d.N % 2 == 0)) &&
-        vec_ok<double>(A, d.a_m, d.a_k, d.a_b0, d.a_b1, true) &&
-        (!A2 || vec_ok<double>(A2, d.a_m, d.a_k, d.a_b0, d.a_b1, true)) &&
-        vec_ok<double>(B, d.b_n, d.b_k, d.b_b0, d.b_b1, bkc) && (!A2 || vec_ok<double>(B2, d.b_n, d.b_k, d.b_b0, d.b_b1, bkc));
-    if (pipe_ok) {
-      const int r = d.K % 16;
-      GemmDesc dm = d;
-      dm.K = d.K - r;
-      launch_cfg<Mma, TA, TB, TC, 64, 64, 16, 2>(dm, A, B, A2, B2, C, s);
-      if (r) {
-        GemmDesc dt = d;
-        dt.K = r;
-        dt.beta = 1.0;
-        const int64_t ka = (int64_t)(d.K - r) * d.a_k, kb = (int64_t)(d.K - r) * d.b_k;
-        launch_cfg<Mma, TA, TB, TC, 64, 64, 16, 2>(dt, (const double*)A + ka, (const double*)B + kb,
-                                                   A2 ? (const double*)A2 + ka : nullptr,
-                                                   A2 ? (const double*)B2 + kb : nullptr, C, s);
-      }
-      return;
-    }
-    // otherwise, row counts that 72- or 80-row tiles cover with at least 10 %
-    // less padding than 64-row ones (such as the ladder's 210 pair rows, 216
-    // against 256, and the 400 rows of its T1 part, 400 against 448, when
-    // their operands do not suit the pipelined kernel), with a long
-    // contraction: 72 x 128 or 80 x 128 with 8-deep panels (9 % and 16 %
-    // faster than the register-staged 64 x 64 tiles there)
-    const int64_t r64 = ceil_div(d.M, 64) * 64, r72 = ceil_div(d.M, 72) * 72, r80 = ceil_div(d.M, 80) * 80;
-    // (at least 128 such tiles: fewer go to 64 x 64 tiles and many chunks)
-    const int64_t n128 = ceil_div(d.N, 128) * nb;
-    if (d.K >= 1024 && r80 < r72 && 10 * r80 <= 9 * r64 && (r80 / 80) * n128 >= 128)
-      launch_cfg<Mma, TA, TB, TC, 80, 128, 8, 2>(d, A, B, A2, B2, C, s);
-    else if (d.K >= 1024 && 10 * r72 <= 9 * r64 && (r72 / 72) * n128 >= 128)
-      launch_cfg<Mma, TA, TB, TC, 72, 128, 8, 2>(d, A, B, A2, B2, C, s);
-    // a few 64-row tiles with a long contraction (the antisymmetric ladder's
-    // 190 pair rows at o = 20): 64 x 128 with 8-deep panels, 5 % faster
-    else if (d.M > 64 && d.M <= 256 && d.K >= 8192 && (r64 / 64) * n128 >= 128)
-      launch_cfg<Mma, TA, TB, TC, 64, 128, 8, 2>(d, A, B, A2, B2, C, s);
-    else if (d.M <= 64 && d.K >= 1024) launch_cfg<Mma, TA, TB, TC, 64, 64, 32, 2>(d, A, B, A2, B2, C, s);
-    else launch_cfg<Mma, TA, TB, TC, 64, 64, BK, 2>(d, A, B, A2, B2, C, s);
+    if (!launch_f64(d, (const double*)A, (const double*)B, (const double*)A2, (const double*)B2, (double*)C, s))
+      launch_cfg<Mma, TA, TB, TC, 64, 64, BK, 2>(d, A, B, A2, B2, C, s);
   } else {
     const int64_t big = ceil_div(d.M, 128) * ceil_div(d.N, 128) * nb;
     // BF16 128 x 128 tiles take two matrix-core steps per panel (64-deep):
