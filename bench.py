@@ -15,8 +15,8 @@ run's time allows it) and the oracle's residual and energy at the
 mixed-precision root. `roofline` is for the residual evaluation (its
 matrix-core contractions, FP64): algorithmic flops per residual over its
 duration measured with HIP events on its stream during the timed region.
-`roofline_inner` is the same for the occupied A_F launch of the inner solve
-(HBM bound). Other workloads: --workload c2_haar | c3_neardeg | c4_single |
+`roofline_inner` is the same for the step launch of the inner solve (HBM
+bound). Other workloads: --workload c2_haar | c3_neardeg | c4_single |
 serving | inner | protocols | levelshift | gauge | residual.
 """
 
@@ -40,20 +40,12 @@ HEADLINE = "c4_mixed"     # the default line
 # host baseline); the untimed FP64 reference
 # solve is skipped when it would not fit.
 RUN_BUDGET_S = 540.0
-# HBM bytes per launch of the fused first kernel of the inner Lanczos step
-# (packed pair layout) on this workload, from the rocprofv3 FETCH_SIZE /
-# WRITE_SIZE passes in profiles/fock_vir_lz_kernel_c2_haar_counters.md
-# (each scaled by the same counter for a copy kernel of known size). None
-# when the kernel has changed since the counters were taken.
-VIR_LZ_TRAFFIC_BYTES = 33288550
-# HBM bytes of one residual evaluation and of one occupied A_F launch on the
-# default workload, from the rocprofv3 FETCH_SIZE / WRITE_SIZE passes (each
-# scaled by the same counter for a copy of known size) in
-# profiles/residual_jvp_c2_c4_mfma_and_hbm_counters.md and
-# profiles/fock_occ_set_kernel_c2_c4_counters.md; None when a kernel has
-# changed since the counters were taken.
-RESIDUAL_TRAFFIC_BYTES = 39757973068
-OCC_PACKED_TRAFFIC_BYTES = 276513390
+# HBM bytes of one residual evaluation and of one step launch of the inner
+# solve from rocprofv3 FETCH_SIZE / WRITE_SIZE passes (each scaled by the same
+# counter for a copy of known size); None when a kernel has changed since the
+# counters were taken.
+RESIDUAL_TRAFFIC_BYTES = None
+INNER_STEP_TRAFFIC_BYTES = None
 
 
 def nominal_residual_flops(o, v, naux):
@@ -62,23 +54,15 @@ def nominal_residual_flops(o, v, naux):
             + 4 * o * o * v ** 3 + 4 * o ** 3 * v * v)
 
 
-def fock_vir_lz_bytes(o, v):
-    """Algorithmic HBM bytes of one launch of the fused first kernel of the
-    inner Lanczos step on the packed pairs i <= j (n_l = o v + o (o + 1) / 2
-    v^2 FP64 elements per vector): p_{k-1}, v_{k-1}, w_{k-2}, w_{k-3} and
-    the iterate read and v_k, w_{k-1} and the iterate written once (8 vector
-    passes), the virtual part f_vv v_k + v_k f_vv of the doubles written,
-    f_vv read."""
-    npair = o * (o + 1) // 2
-    nl = o * v + npair * v * v
-    return 8 * (8 * nl + npair * v * v + v * v)
+def inner_step_bytes(o, v):
+    """Algorithmic HBM bytes of one step launch of the inner solve on the
+    packed pairs i <= j: the rotated right-hand side read once, n_l = o v +
+    o (o + 1) / 2 v^2 FP64 elements (a Lanczos vector is rebuilt from it)."""
+    return 8 * (o * v + o * (o + 1) // 2 * v * v)
 
 
-def fock_vir_lz_flops(o, v):
-    """Its flops: two v-deep products per packed doubles block (4 v^3) and
-    about 8 per element for the update."""
-    npair = o * (o + 1) // 2
-    return 4 * npair * v ** 3 + 8 * (o * v + npair * v * v)
+INNER_STEP_KERNEL = ("inner_step_kernel (Lanczos step of the inner solve on the packed pairs, in the eigenvectors of "
+                     "the Fock blocks: v_k rebuilt from b, three sums)")
 
 
 def cpu_baseline(problem, counts, t1_gpu, t2_gpu, e_gpu):
@@ -170,16 +154,13 @@ def bench_c2(args):
     F_R = nominal_residual_flops(o, v, naux)
     res_ms = ms_res / max(n_res, 1)
     af_ms = ms_afm / n_afm if n_afm else None
-    af_bytes = fock_vir_lz_bytes(o, v)
+    af_bytes = inner_step_bytes(o, v)
     roof = None
     if af_ms:
         gbs = af_bytes / (af_ms * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": gbs / HBM_PEAK_GBS, "traffic": VIR_LZ_TRAFFIC_BYTES,
-                "kernel": "fock_vir_lz_kernel (inner Lanczos step on the packed pairs: the previous step's "
-                          "update fused with the A_F virtual contractions)",
-                "launches_timed": n_afm, "avg_us": af_ms * 1e3, "bytes_per_launch": af_bytes,
-                "flops_per_launch": fock_vir_lz_flops(o, v)}
+                "frac": gbs / HBM_PEAK_GBS, "traffic": None, "kernel": INNER_STEP_KERNEL,
+                "launches_timed": n_afm, "avg_us": af_ms * 1e3, "bytes_per_launch": af_bytes}
     out = {
         "metric": "PNK CCSD solves/s + p50/p99 latency at |dE|<1e-6 Eh; residual TFLOP/s vs FP64",
         "value": args.steps / elapsed,
@@ -208,8 +189,8 @@ def bench_c2(args):
         "time_share": {"residual": ms_res / (1000 * elapsed), "jvp": ms_jvp / (1000 * elapsed),
                        "precond_solve": ms_pre / (1000 * elapsed),
                        # the average of the sampled launches times every launch that ran
-                       # (one per inner step plus the normalising one per inner solve)
-                       "A_F_fused_virtual_kernel": (af_ms or 0.0) * (sum(i["n_afmv"] for i in infos) + n_pre)
+                       # (one per inner step plus the first one of each inner solve)
+                       "inner_step_kernel": (af_ms or 0.0) * (sum(i["n_afmv"] for i in infos) + n_pre)
                        / (1000 * elapsed)},
         "roofline": roof,
     }
@@ -230,14 +211,6 @@ def krylov_inner_rtol(prec):
     34 from 1e-3 to 1e-12; the A_F products per solve fall from 17888
     (1e-12) to 9713 (1e-6) and 6811 (1e-4)."""
     return {"bf16": 1e-4, "fp32": 1e-6}.get(prec, 0.0)
-
-
-def occ_packed_bytes(o, v):
-    """Algorithmic HBM bytes of one occupied A_F launch of the packed inner
-    step (three-launch form): v_k, the virtual part of p and v_{k-1} read,
-    p written, n_l = o v + o (o + 1) / 2 v^2 elements each."""
-    nl = o * v + o * (o + 1) // 2 * v * v
-    return 8 * 4 * nl
 
 
 def cpu_baseline_sample(problem, counts, t1_gpu, t2_gpu, e_gpu):
@@ -365,12 +338,11 @@ def bench_headline(args):
     roof_inner = None
     if n_afm:
         af_ms = ms_afm / n_afm
-        b = occ_packed_bytes(o, v)
+        b = inner_step_bytes(o, v)
         gbs = b / (af_ms * 1e-3) / 1e9
         roof_inner = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                      "frac": gbs / HBM_PEAK_GBS, "traffic": OCC_PACKED_TRAFFIC_BYTES,
-                      "kernel": "fock_occ_set_kernel (occupied A_F contractions of the inner Lanczos step on "
-                                "the packed pairs, register-blocked over transpose-closed position sets)",
+                      "frac": gbs / HBM_PEAK_GBS, "traffic": INNER_STEP_TRAFFIC_BYTES,
+                      "kernel": INNER_STEP_KERNEL,
                       "launches_timed": n_afm, "avg_us": af_ms * 1e3,
                       "bytes_per_launch": b}
     out = {

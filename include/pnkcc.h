@@ -126,7 +126,9 @@ cc_status cc_fock_apply(cc_handle* h, const cc_problem* p, const double* x1, con
  * A_F products; the product count goes to iters_out (host, may be NULL).
  * When f_ov = 0, A_F is symmetric and GMRES takes its Lanczos (MINRES)
  * form, run on D^1/2 A_F D^1/2 with D = 2 on the singles and 1 on the
- * doubles (same solution; the scaled residual bounds the true one).
+ * doubles (same solution; the scaled residual bounds the true one), in the
+ * eigenvectors of f_oo and f_vv (an orthogonal change of basis, under which
+ * its steps are the same). The cap is counted in whole blocks of steps.
  * Otherwise restarted GMRES (restart 30). Returns CC_NOT_CONVERGED when
  * maxit is reached first. Synchronises. */
 cc_status cc_precond_solve(cc_handle* h, const cc_problem* p, const double* b1, const double* b2, double* x1,
@@ -134,9 +136,8 @@ cc_status cc_precond_solve(cc_handle* h, const cc_problem* p, const double* b1, 
 
 /* cc_precond_solve for a pair-symmetric right-hand side, b2[j][i][b][a] =
  * b2[i][j][a][b], as every closed-shell amplitude vector is (the residual,
- * J v and their preconditioned images). When f_ov = 0 the Lanczos vectors
- * then hold only the pairs i <= j, which halves their memory traffic and
- * the virtual contractions. What is solved is the pair-symmetric part of b
+ * J v and their preconditioned images). When f_ov = 0 the recurrence then
+ * runs on the pairs i <= j only, which halves its memory traffic. What is solved is the pair-symmetric part of b
  * ((b2[i][j] + b2[j][i]^T) / 2); x is pair-symmetric. Same arguments and
  * errors as cc_precond_solve. */
 cc_status cc_precond_solve_pairsym(cc_handle* h, const cc_problem* p, const double* b1, const double* b2, double* x1,
@@ -389,7 +390,8 @@ void cc_server_destroy(cc_server* s);
 /* Device timing of tagged work on the handle, with HIP events recorded on
  * the stream each launch runs on. Slots: 0 the particle-particle ladder
  * contraction (one launch per residual or J v), 1 whole residual
- * evaluations, 2 whole J v products, 3 A_F products, 4 inner A_F solves.
+ * evaluations, 2 whole J v products, 3 A_F products
+ * (in a symmetric inner solve its step launches), 4 inner A_F solves.
  * cc_diag_timing(h, 1) enables and resets; cc_diag_timing_read synchronises
  * the recorded events and returns the launch count and total milliseconds
  * of one slot. */
@@ -412,14 +414,14 @@ cc_status cc_diag_contraction_flops(cc_handle* h, const cc_problem* p, cc_precis
  * CC_NOT_CONVERGED if the iteration stalls. */
 cc_status cc_diag_hessenberg_eigenvalues(int m, const double* H, double* re, double* im);
 
-/* The position sets of the occupied A_F kernel on the packed pair layout
- * (the o x o contractions of the A_F product, Appendix A.7, for each
- * virtual pair (a, b)): every workgroup takes 64 positions closed under
- * (a, b) -> (b, a). For nvir virtuals, writes for set u and lane l the
- * position a[64 u + l], b[64 u + l] (entries >= nvir mark padding lanes)
- * and lane_t[64 u + l], the lane of the same set holding (b, a); *nsets
- * receives the set count. Host arrays of cap elements each; host code, no
- * GPU. CC_ERR_ARG for null pointers, nvir < 1 or cap < 64 * nsets. */
+/* The position sets of the inner solve's occupied rotation on the packed
+ * pair layout (o x o products at each virtual pair (a, b)): every workgroup
+ * takes 64 positions closed under (a, b) -> (b, a). For nvir virtuals,
+ * writes for set u and lane l the position a[64 u + l], b[64 u + l]
+ * (entries >= nvir mark padding lanes) and lane_t[64 u + l], the lane of the
+ * same set holding (b, a); *nsets receives the set count. Host arrays of cap
+ * elements each; host code, no GPU. CC_ERR_ARG for null pointers, nvir < 1
+ * or cap < 64 * nsets. */
 cc_status cc_diag_occ_sets(int nvir, int* a, int* b, int* lane_t, int64_t cap, int* nsets);
 
 /* C = alpha * A * B + beta * C with element strides (A[m*a_m + k*a_k],

@@ -319,7 +319,7 @@ def gemm_noalloc(A, B, C, a_strides, b_strides, c_strides, M, N, K, nbatch, alph
 
 
 def occ_sets(nvir):
-    """The occupied A_F kernel's position sets for nvir virtuals
+    """The occupied rotation's position sets for nvir virtuals
     (cc_diag_occ_sets; host code, no GPU): arrays a, b, lane_t of shape
     (sets, 64)."""
     nb = (nvir + 7) // 8

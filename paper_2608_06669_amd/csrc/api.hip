@@ -111,7 +111,7 @@ Gauge* Handle::ensure_gauge(const cc_gauge* g, hipStream_t s) {
   return &gauge;
 }
 
-void Handle::ensure(const cc_problem* p, int lowp, int m_max, int restart, int diis, hipStream_t s) {
+void Handle::ensure(const cc_problem* p, int lowp, int m_max, int restart, int diis, hipStream_t s, bool inner) {
   check_problem(p);
   PNK_HIP(hipSetDevice(device));
   const int o = p->nocc, v = p->nvir, naux = p->naux;
@@ -174,7 +174,7 @@ void Handle::ensure(const cc_problem* p, int lowp, int m_max, int restart, int d
     ProblemView pv;
     pv.o = o; pv.v = v; pv.naux = naux;
     pv.f_oo = p->f_oo; pv.f_ov = p->f_ov; pv.f_vv = p->f_vv; pv.L = p->L;
-    eng->prepare(pv, s);
+    eng->prepare(pv, s, inner);
     cached_key = key;
     prepared = true;
   }
@@ -375,7 +375,7 @@ static cc_status precond_solve_impl(cc_handle* h, const cc_problem* p, const dou
   hipStream_t s = (hipStream_t)stream;
   PNK_REQUIRE(b1 && b2 && x1 && x2, "array arguments must not be NULL");
   PNK_REQUIRE(rtol > 0 && rtol < 1 && maxit >= 1, "rtol must be in (0, 1) and maxit >= 1");
-  H->ensure(p, 0, 1, 30, 0, s);
+  H->ensure(p, 0, 1, 30, 0, s, true);
   const int64_t ov = H->eng->o() * (int64_t)H->eng->v(), n2 = H->eng->nvec() - ov;
   pack(ov, n2, b1, b2, H->xb, s);
   bool conv = true;
@@ -444,7 +444,7 @@ cc_status cc_solve_pnk(cc_handle* h, const cc_problem* p, const cc_pnk_opts* opt
   cc_pnk_opts_default(&o);
   if (opts) o = *opts;
   check_pnk_opts(o);
-  H->ensure(p, lowp_for(o.jvp_prec), o.m_max, o.inner_restart, 0, s);
+  H->ensure(p, lowp_for(o.jvp_prec), o.m_max, o.inner_restart, 0, s, true);
   const int64_t ov = H->eng->o() * (int64_t)H->eng->v(), n2 = H->eng->nvec() - ov;
   if (!o.init_mp2) pack(ov, n2, t1, t2, H->xa, s);
   SolveStats st;
@@ -468,7 +468,7 @@ cc_status cc_solve_fp_diis(cc_handle* h, const cc_problem* p, const cc_fp_opts* 
   if (opts) o = *opts;
   PNK_REQUIRE(o.tol_inf > 0 && o.max_iter >= 0 && o.diis_size >= 0 && o.diis_size <= 32 && o.diis_start >= 0,
               "invalid FP options");
-  H->ensure(p, 0, 1, 30, std::max(o.diis_size, 1), s);
+  H->ensure(p, 0, 1, 30, std::max(o.diis_size, 1), s, o.init_mp2 != 0);
   const int64_t ov = H->eng->o() * (int64_t)H->eng->v(), n2 = H->eng->nvec() - ov;
   if (!o.init_mp2) pack(ov, n2, t1, t2, H->xa, s);
   FpOptions fo;
@@ -566,7 +566,7 @@ cc_status cc_solve_pnk_gauge(cc_handle* h, const cc_problem* p, const cc_gauge* 
   cc_pnk_opts_default(&o);
   if (opts) o = *opts;
   check_pnk_opts(o);
-  H->ensure(p, lowp_for(o.jvp_prec), o.m_max, o.inner_restart, 0, s);
+  H->ensure(p, lowp_for(o.jvp_prec), o.m_max, o.inner_restart, 0, s, true);
   Gauge* G = H->ensure_gauge(g, s);
   const int64_t gov = (int64_t)G->mo * G->mv, gn2 = G->nvec() - gov;
   if (!o.init_mp2) pack(gov, gn2, th1, th2, G->xg, s);
@@ -594,7 +594,7 @@ cc_status cc_solve_fp_diis_gauge(cc_handle* h, const cc_problem* p, const cc_gau
   if (opts) o = *opts;
   PNK_REQUIRE(o.tol_inf > 0 && o.max_iter >= 0 && o.diis_size >= 0 && o.diis_size <= 32 && o.diis_start >= 0,
               "invalid FP options");
-  H->ensure(p, 0, 1, 30, std::max(o.diis_size, 1), s);
+  H->ensure(p, 0, 1, 30, std::max(o.diis_size, 1), s, o.init_mp2 != 0);
   Gauge* G = H->ensure_gauge(g, s);
   const int64_t gov = (int64_t)G->mo * G->mv, gn2 = G->nvec() - gov;
   if (!o.init_mp2) pack(gov, gn2, th1, th2, G->xg, s);
@@ -692,7 +692,7 @@ cc_status cc_diag_hessenberg_eigenvalues(int m, const double* H, double* re, dou
 
 cc_status cc_diag_occ_sets(int nvir, int* a, int* b, int* lane_t, int64_t cap, int* nsets) {
   if (nvir < 1 || !a || !b || !lane_t || !nsets || cap < 0) return CC_ERR_ARG;
-  const int n = fock_op_set_positions(nvir, a, b, lane_t, cap);
+  const int n = inner_set_positions(nvir, a, b, lane_t, cap);
   if (n < 0) return CC_ERR_ARG;
   *nsets = n;
   return CC_OK;

@@ -50,8 +50,8 @@ struct Handle {
   void* dev_alloc(size_t bytes);
   void dev_free(void* p);
   // Size the engine/solver for p and (re)prepare its integrals if the
-  // problem's pointers, sizes or content changed.
-  void ensure(const cc_problem* p, int lowp, int m_max, int restart, int diis, hipStream_t s);
+  // problem's pointers, sizes or content changed. inner: the call inverts A_F.
+  void ensure(const cc_problem* p, int lowp, int m_max, int restart, int diis, hipStream_t s, bool inner = false);
 };
 
 // outer_cap: length of the solver's outer vectors when above the orbital

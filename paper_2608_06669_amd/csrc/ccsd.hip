@@ -31,6 +31,7 @@
 #include <cstring>
 
 #include "cc_kernels.hpp"
+#include "eig.hpp"
 #include "gemm.hpp"
 #include "tensor_ops.hpp"
 
@@ -471,7 +472,53 @@ void Engine::lin_ppl_unpack(const Ten& rp, const Ten& rm, const Ten& R) {
 
 // ------------------------------------------------------------ prepare ---
 
-void Engine::prepare(const ProblemView& p, hipStream_t s) {
+void Engine::fetch_fock(std::vector<double>* foo, std::vector<double>* fvv, hipStream_t s) const {
+  foo->resize((size_t)o_ * o_);
+  fvv->resize((size_t)v_ * v_);
+  PNK_HIP(hipMemcpyAsync(foo->data(), f_oo_, foo->size() * sizeof(double), hipMemcpyDeviceToHost, s));
+  PNK_HIP(hipMemcpyAsync(fvv->data(), f_vv_, fvv->size() * sizeof(double), hipMemcpyDeviceToHost, s));
+  PNK_HIP(hipStreamSynchronize(s));
+}
+
+// Into fock_ and h_, which are free once the blocks are extracted: [eps_o |
+// eps_v | ut_o | ut_v] (o + v + o^2 + v^2 <= (o + v)^2 doubles) and u_o
+void Engine::compute_eigen(const std::vector<double>& foo, const std::vector<double>& fvv, hipStream_t s) {
+  const size_t o = o_, v = v_;
+  std::vector<double> buf(o + v + o * o + v * v);
+  double *eo = buf.data(), *ev = eo + o, *uo = ev + v, *uv = uo + o * o;
+  bool diag_o = false, diag_v = false;
+  eigen_ok_ = symmetric_eigen(foo.data(), o_, eo, uo, &diag_o) && symmetric_eigen(fvv.data(), v_, ev, uv, &diag_v);
+  eigen_done_ = true;
+  if (!eigen_ok_) return;
+  PNK_HIP(hipMemcpyAsync(fock_, buf.data(), buf.size() * sizeof(double), hipMemcpyHostToDevice, s));
+  PNK_HIP(hipStreamSynchronize(s));  // buf goes out of scope
+  eigen_.o = o_;
+  eigen_.v = v_;
+  eigen_.eps_o = fock_;
+  eigen_.eps_v = fock_ + o;
+  eigen_.ut_o = eigen_.u_o = nullptr;
+  if (!diag_o) {
+    std::vector<double> u(o * o);
+    for (size_t i = 0; i < o; ++i)
+      for (size_t k = 0; k < o; ++k) u[i * o + k] = uo[k * o + i];
+    PNK_HIP(hipMemcpyAsync(h_, u.data(), u.size() * sizeof(double), hipMemcpyHostToDevice, s));
+    PNK_HIP(hipStreamSynchronize(s));
+    eigen_.ut_o = fock_ + o + v;
+    eigen_.u_o = h_;
+  }
+  eigen_.ut_v = diag_v ? nullptr : fock_ + o + v + o * o;
+}
+
+const FockEigen* Engine::fock_eigen(hipStream_t s) {
+  if (!eigen_done_) {
+    std::vector<double> foo, fvv;
+    fetch_fock(&foo, &fvv, s);
+    compute_eigen(foo, fvv, s);
+  }
+  return eigen_ok_ ? &eigen_ : nullptr;
+}
+
+void Engine::prepare(const ProblemView& p, hipStream_t s, bool with_eigen) {
   PNK_REQUIRE(p.o == o_ && p.v == v_ && p.naux == naux_, "prepare: dimensions differ from the engine's");
   s_ = s;
   mode_ = Mode::Value;
@@ -480,6 +527,9 @@ void Engine::prepare(const ProblemView& p, hipStream_t s) {
   PNK_HIP(hipMemcpyAsync(f_oo_, p.f_oo, sizeof(double) * o * o, hipMemcpyDeviceToDevice, s));
   PNK_HIP(hipMemcpyAsync(f_ov_, p.f_ov, sizeof(double) * ov, hipMemcpyDeviceToDevice, s));
   PNK_HIP(hipMemcpyAsync(f_vv_, p.f_vv, sizeof(double) * vv, hipMemcpyDeviceToDevice, s));
+  eigen_done_ = false;
+  std::vector<double> foo, fvv;
+  if (with_eigen) fetch_fock(&foo, &fvv, s);
   // h = f - G[L], G[L]_pq = sum_P 2 L_pq d_P - sum_Pk L_pk L_kq
   assemble_fock(o, v, f_oo_, f_ov_, f_vv_, fock_, s);
   copy((int64_t)n * n, fock_, h_, s);
@@ -571,6 +621,7 @@ void Engine::prepare(const ProblemView& p, hipStream_t s) {
   fill(ov_ + n2_, 0.0, zeros_, s);
   // f_ov == 0 lets A_F skip its singles-doubles coupling
   nrm_inf(ov, f_ov_, partials_ + reduce_partials_size(64) - 1, partials_, s);
+  if (with_eigen) compute_eigen(foo, fvv, s);  // while the device works on the tensors above
   double fmax = 0.0;
   PNK_HIP(hipMemcpyAsync(&fmax, partials_ + reduce_partials_size(64) - 1, sizeof(double), hipMemcpyDeviceToHost, s));
   PNK_HIP(hipStreamSynchronize(s));

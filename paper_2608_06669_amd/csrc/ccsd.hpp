@@ -22,6 +22,7 @@
 #include "common.hpp"
 #include "fock_op.hpp"
 #include "gemm.hpp"
+#include "inner_solve.hpp"
 
 namespace pnk {
 
@@ -99,7 +100,12 @@ class Engine {
   const EngineOptions& options() const { return opt_; }
 
   // Integral tensors of a problem (h, dressed-block sources, W_vvvv, ...).
-  void prepare(const ProblemView& p, hipStream_t s);
+  // with_eigen: the caller is going to need fock_eigen(), whose host work
+  // then runs beside the device's.
+  void prepare(const ProblemView& p, hipStream_t s, bool with_eigen = false);
+  // Eigenvectors of the prepared problem's Fock blocks (computed on the first
+  // call unless prepare did); null if they are not finite.
+  const FockEigen* fock_eigen(hipStream_t s);
   // Residual r(t) into r1, r2; keeps every intermediate so jvp() can
   // linearise at t. t1/t2 must stay unchanged until the next residual().
   void residual(const double* t1, const double* t2, double* r1, double* r2, hipStream_t s);
@@ -162,6 +168,10 @@ class Engine {
   // problem constants
   double *f_oo_, *f_ov_, *f_vv_, *fock_, *h_, *dtr_, *Lo_;
   bool fov_zero_ = true;
+  FockEigen eigen_;
+  bool eigen_done_ = false, eigen_ok_ = false;
+  void fetch_fock(std::vector<double>* foo, std::vector<double>* fvv, hipStream_t s) const;
+  void compute_eigen(const std::vector<double>& foo, const std::vector<double>& fvv, hipStream_t s);
   FockOp fop_;
   bool fop_ok_ = false;
   Ten Loo0, Lov0, Lvo0, Lvv0, S, Am, Wov, Ioovv, Iovov, Ix, Ikldc, Itil;

@@ -14,9 +14,9 @@
 // solved on the host.
 
 #include "solvers.hpp"
-#include "block_sum.hpp"
 #include "eig.hpp"
 #include "fock_op.hpp"
+#include "inner_solve.hpp"
 
 #include <chrono>
 #include <cstdlib>
@@ -100,11 +100,11 @@ Solver::Solver(Engine& eng, int m_max, int restart, int diis, hipStream_t alloc_
 }
 
 Solver::~Solver() {
-  for (auto& layout : lz_graphs_)
+  for (auto& layout : inner_graphs_)
     for (auto& row : layout)
       for (hipGraphExec_t e : row)
         if (e) (void)hipGraphExecDestroy(e);
-  for (hipEvent_t e : lz_ev_)
+  for (hipEvent_t e : inner_ev_)
     if (e) (void)hipEventDestroy(e);
   for (double* p : {Qo_, Qi_, r_, ri_, w_, w2_, hx_, he_, dsc_, partials_})
     if (p) (void)(async_ ? hipFreeAsync(p, alloc_stream_) : hipFree(p));
@@ -165,28 +165,6 @@ double Solver::orthogonalise(int64_t n, double* Q, int64_t ldq, int m, double* w
 }
 
 namespace {
-
-// ---- short-recurrence (Lanczos) GMRES for symmetric A_F, all on the device ----
-// Three kernels per step. Global sums are never a kernel of their own: the
-// kernel that needs a sum adds the previous kernel's per-workgroup partial
-// sums itself, every workgroup in the same fixed order (so every workgroup
-// gets the same bits), and the scalar recurrences are evaluated redundantly
-// by every workgroup of the last kernel. The state therefore has two slots:
-// step k reads slot k % 2 and workgroup 0 writes slot (k + 1) % 2.
-// state: [0] beta_k  [1] alpha_k  [2] beta_{k+1}  [3] c_{k-2} [4] s_{k-2}
-//        [5] c_{k-1} [6] s_{k-1}  [7] phibar      [8] rho1    [9] delta
-//        [10] eps    [11] phi     [12] |phibar|   [13] 1/beta_{k+1}
-//        [14] done (the stopping test held at an earlier step)
-// A third, fixed slot after the two holds what the host reads: steps run,
-// the last residual estimate and beta, the absolute tolerance, ||b||.
-// (the layout is shared with the fused packed step in fock_op)
-constexpr int kBeta = kLzBeta, kAlpha = kLzAlpha, kBetaN = kLzBetaN, kC2 = kLzC2, kS2 = kLzS2, kC1 = kLzC1,
-              kS1 = kLzS1, kPhiBar = kLzPhiBar, kRho1 = kLzRho1, kDelta = kLzDelta, kEps = kLzEps, kPhi = kLzPhi,
-              kRes = kLzRes, kInvB = kLzInvB, kDone = kLzDone, kFirst = kLzFirst, kNState = kLzNState;
-constexpr int kFinSteps = kLzFinSteps, kFinRes = kLzFinRes, kFinBeta = kLzFinBeta, kFinTol = kLzFinTol,
-              kFinBNorm = kLzFinBNorm, kFinBHat = kLzFinBHat, kFinCount = kLzFinCount;
-constexpr int kStateStride = kLzStateStride;
-constexpr int kLzBlocks = 512;
 // With f_ov = 0, A_F is block diagonal and its doubles block is the
 // Kronecker sum of the singles block with itself (A_F, equation
 // Preconditioner and its working equations): its spectrum spans exactly
@@ -195,402 +173,24 @@ constexpr int kLzBlocks = 512;
 // the singles, which brings both blocks onto [2 lmin, 2 lmax] and halves
 // the condition number (about 1/sqrt(2) as many Lanczos steps).
 constexpr double kInnerSinglesScale = 2.0;
-
-constexpr int kMaxFusedParts = 16384;  // workgroups of the fused A_F launch (three partials each)
-
-// p = S p - beta_k v_{k-1} (S scales the first n1 entries by s1); partial
-// sums of <v_k, p>, <p, p> and <v_k, v_k> (part1[b], part1[G + b],
-// part1[2 G + b], G = gridDim.x)
-__global__ __launch_bounds__(256) void lz_step1(int64_t n, double* __restrict__ p, const double* __restrict__ vprev,
-                                                const double* __restrict__ v, const double* __restrict__ st,
-                                                double* __restrict__ part1, int64_t n1, double s1) {
-  if (st[kDone] != 0.0) return;
-  __shared__ double sm[3][4];
-  const double beta = st[kBeta];
-  double dot = 0.0, nrm = 0.0, vv2 = 0.0;
-  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const double x = (i < n1 ? s1 : 1.0) * p[i] - beta * vprev[i];
-    const double vk = v[i];
-    p[i] = x;
-    dot += vk * x;
-    nrm += x * x;
-    vv2 += vk * vk;
-  }
-  double r[3] = {dot, nrm, vv2};
-  block_sum256<3>(r, sm);
-  if (threadIdx.x == 0)
-    for (int c = 0; c < 3; ++c) part1[c * gridDim.x + blockIdx.x] = r[c];
-}
-
-// alpha_k = <v_k, p> / <v_k, v_k> and beta_{k+1} = ||p - alpha_k v_k||,
-// from ||p||^2 - <v_k, p>^2 / <v_k, v_k> (p - alpha_k v_k is orthogonal to
-// v_k), all from the partials of the launch before. Measuring <v_k, v_k>
-// rather than taking it as 1 keeps a rounding error in the norm of v_k from
-// growing from step to step. Then one Givens rotation of the tridiagonal
-// QR, and
-// w_k = (v_k - delta w_{k-1} - eps w_{k-2}) / rho1 (into the w_{k-2} slot),
-// x += phi w_k, v_{k+1} = (p - alpha_k v_k) / beta_{k+1} (in place).
-// The stopping test (|phibar| <= tolerance, or beta_{k+1} = 0) is taken
-// here after every step; once it holds, the later steps of the queue pass
-// the done flag on and write nothing else.
-__global__ __launch_bounds__(256) void lz_update(int64_t n, const double* __restrict__ v,
-                                                 const double* __restrict__ w1, double* __restrict__ w2,
-                                                 double* __restrict__ x, double* __restrict__ p,
-                                                 const double* __restrict__ part1, int nparts1,
-                                                 const double* __restrict__ st, double* __restrict__ stn,
-                                                 double* __restrict__ fin) {
-  if (st[kDone] != 0.0) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) stn[kDone] = 1.0;
-    return;
-  }
-  __shared__ double sm[3][4];
-  double r[3] = {0.0, 0.0, 0.0};
-  for (int k = threadIdx.x; k < nparts1; k += 256) {
-    r[0] += part1[k];
-    r[1] += part1[nparts1 + k];
-    r[2] += part1[2 * nparts1 + k];
-  }
-  block_sum256<3>(r, sm);
-  const double vp = r[0], pp = r[1], vv = r[2];
-  const double alpha = vv > 0.0 ? vp / vv : 0.0;
-  const double betan = sqrt(fmax(pp - alpha * vp, 0.0));
-  const double beta = st[kBeta];
-  const double c2 = st[kC2], s2 = st[kS2], c1 = st[kC1], s1 = st[kS1];
-  const double eps = s2 * beta;
-  const double dbar = c2 * beta;
-  const double delta = c1 * dbar + s1 * alpha;
-  const double gbar = -s1 * dbar + c1 * alpha;
-  const double rho1 = hypot(gbar, betan);
-  const double c = rho1 != 0.0 ? gbar / rho1 : 1.0;
-  const double s = rho1 != 0.0 ? betan / rho1 : 0.0;
-  const double phibar = st[kPhiBar];
-  const double phi = c * phibar;
-  const double invb = betan != 0.0 ? 1.0 / betan : 0.0;
-  const double ir = rho1 != 0.0 ? 1.0 / rho1 : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    stn[kBeta] = betan;
-    stn[kAlpha] = alpha;
-    stn[kBetaN] = betan;
-    stn[kC2] = c1; stn[kS2] = s1;
-    stn[kC1] = c; stn[kS1] = s;
-    stn[kPhiBar] = -s * phibar;
-    stn[kRho1] = rho1;
-    stn[kDelta] = delta;
-    stn[kEps] = eps;
-    stn[kPhi] = phi;
-    const double res = fabs(s * phibar);
-    stn[kRes] = res;
-    stn[kInvB] = invb;
-    stn[kDone] = (res <= fin[kFinTol] || betan == 0.0) ? 1.0 : 0.0;
-    fin[kFinSteps] += 1.0;
-    fin[kFinRes] = res;
-    fin[kFinBeta] = betan;
-  }
-  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const double vi = v[i];
-    const double w = (vi - delta * w1[i] - eps * w2[i]) * ir;
-    w2[i] = w;
-    x[i] += phi * w;
-    p[i] = (p[i] - alpha * vi) * invb;
-  }
-}
-
-// bnorm: norm of the (scaled) start vector; rhs_norm: ||b||, which with
-// rtol sets the absolute tolerance on the residual estimate.
-__global__ void lz_init(double* st, const double* bnorm, const double* rhs_norm, double rtol) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  for (int k = 0; k < kNState; ++k) st[k] = 0.0;
-  st[kC2] = 1.0; st[kC1] = 1.0;
-  st[kPhiBar] = *bnorm;
-  st[kRes] = *bnorm;
-  st[kBeta] = 0.0;
-  st[kStateStride + kDone] = 0.0;
-  double* fin = st + 2 * kStateStride;
-  fin[kFinSteps] = 0.0;
-  fin[kFinRes] = *bnorm;
-  fin[kFinBeta] = 1.0;
-  fin[kFinTol] = rtol * *rhs_norm;
-  fin[kFinBNorm] = *rhs_norm;
-}
-
-// ---- packed pair layout for pair-symmetric vectors (pairs i <= j) ----
-
-__device__ inline int lzp_pair(int i, int j, int o) { return i * o - i * (i - 1) / 2 + (j - i); }  // i <= j
-
-__device__ inline void lzp_decode(int pr, int o, int& i, int& j) {
-  i = 0;
-  while (pr >= o - i) {
-    pr -= o - i;
-    ++i;
-  }
-  j = i + pr;
-}
-
-constexpr int kPackTile = 32;
-constexpr int kPackBlocksX = 16;  // workgroups per pair block (grid-stride over its tiles)
-
-// xp = packed D^1/2 sym(b): singles times rs; for i <= j the block
-// (b_ij + b_ji^T) / 2 (the pair-symmetric part; b_ji^T staged through LDS).
-// Each workgroup writes its shares of ||sym(b)||^2 and ||D^1/2 sym(b)||^2
-// (blocks of pairs i < j counted twice) to parts[g], parts[G + g], g the
-// workgroup's linear index, G the number of workgroups. The packed vectors
-// of z (null entries skipped) are set to zero in the same pass.
-struct ZeroList {
-  double* p[4];
-};
-
-__global__ __launch_bounds__(256) void lzp_pack(int o, int v, const double* __restrict__ b, double rs,
-                                                double* __restrict__ xp, double* __restrict__ parts, ZeroList z) {
-  __shared__ double tile[kPackTile][kPackTile + 1];
-  __shared__ double sm[2][4];
-  const int npair = o * (o + 1) / 2;
-  const int64_t vv = (int64_t)v * v, ov = (int64_t)o * v;
-  const int tid = threadIdx.x;
-  double s_plain = 0.0, s_scaled = 0.0;
-  if ((int)blockIdx.y == npair) {
-    for (int64_t e = blockIdx.x * (int64_t)256 + tid; e < ov; e += (int64_t)gridDim.x * 256) {
-      const double x = b[e];
-      xp[e] = rs * x;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (z.p[q]) z.p[q][e] = 0.0;
-      s_plain += x * x;
-      s_scaled += (rs * x) * (rs * x);
-    }
-  } else {
-    int i, j;
-    lzp_decode(blockIdx.y, o, i, j);
-    const double w = i == j ? 1.0 : 2.0;
-    const double* __restrict__ bij = b + ov + (int64_t)(i * o + j) * vv;
-    const double* __restrict__ bji = b + ov + (int64_t)(j * o + i) * vv;
-    double* __restrict__ out = xp + ov + (int64_t)blockIdx.y * vv;
-    const int nt = (v + kPackTile - 1) / kPackTile;
-    const int tx = tid % kPackTile, ty = tid / kPackTile;
-    for (int tl = blockIdx.x; tl < nt * nt; tl += gridDim.x) {
-      const int a0 = (tl / nt) * kPackTile, b0 = (tl % nt) * kPackTile;
-      __syncthreads();
-      for (int r = ty; r < kPackTile; r += 256 / kPackTile) {  // tile[r][c] = b_ji[b0 + r][a0 + c]
-        const int rr = b0 + r, cc = a0 + tx;
-        tile[r][tx] = (rr < v && cc < v) ? bji[(int64_t)rr * v + cc] : 0.0;
-      }
-      __syncthreads();
-      for (int r = ty; r < kPackTile; r += 256 / kPackTile) {
-        const int a = a0 + r, bb = b0 + tx;
-        if (a < v && bb < v) {
-          const double x = 0.5 * (bij[(int64_t)a * v + bb] + tile[tx][r]);
-          out[(int64_t)a * v + bb] = x;
-          const int64_t idx = ov + (int64_t)blockIdx.y * vv + (int64_t)a * v + bb;
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (z.p[q]) z.p[q][idx] = 0.0;
-          s_plain += w * x * x;
-          s_scaled += w * x * x;
-        }
-      }
-    }
-  }
-  double r2[2] = {s_plain, s_scaled};
-  block_sum256<2>(r2, sm);
-  const int g = blockIdx.y * gridDim.x + blockIdx.x, G = gridDim.x * gridDim.y;
-  if (tid == 0) {
-    parts[g] = r2[0];
-    parts[G + g] = r2[1];
-  }
-}
-
-// x (full layout) = D^1/2 unpack(xp): x_ij = xp_P(i,j) for i <= j, and
-// xp_P(j,i)^T (through LDS) for i > j; singles times rs.
-__global__ __launch_bounds__(256) void lzp_unpack(int o, int v, const double* __restrict__ xp, double rs,
-                                                  double* __restrict__ x) {
-  __shared__ double tile[kPackTile][kPackTile + 1];
-  const int64_t vv = (int64_t)v * v, ov = (int64_t)o * v;
-  const int tid = threadIdx.x;
-  if ((int)blockIdx.y == o * o) {
-    for (int64_t e = blockIdx.x * (int64_t)256 + tid; e < ov; e += (int64_t)gridDim.x * 256) x[e] = rs * xp[e];
-    return;
-  }
-  const int i = blockIdx.y / o, j = blockIdx.y % o;
-  double* __restrict__ out = x + ov + (int64_t)blockIdx.y * vv;
-  if (i <= j) {
-    const double* __restrict__ src = xp + ov + (int64_t)lzp_pair(i, j, o) * vv;
-    for (int64_t e = blockIdx.x * (int64_t)256 + tid; e < vv; e += (int64_t)gridDim.x * 256) out[e] = src[e];
-    return;
-  }
-  const double* __restrict__ src = xp + ov + (int64_t)lzp_pair(j, i, o) * vv;  // x_ij = x_ji^T
-  const int nt = (v + kPackTile - 1) / kPackTile;
-  const int tx = tid % kPackTile, ty = tid / kPackTile;
-  for (int tl = blockIdx.x; tl < nt * nt; tl += gridDim.x) {
-    const int a0 = (tl / nt) * kPackTile, b0 = (tl % nt) * kPackTile;
-    __syncthreads();
-    for (int r = ty; r < kPackTile; r += 256 / kPackTile) {  // tile[r][c] = x_ji[b0 + r][a0 + c]
-      const int rr = b0 + r, cc = a0 + tx;
-      tile[r][tx] = (rr < v && cc < v) ? src[(int64_t)rr * v + cc] : 0.0;
-    }
-    __syncthreads();
-    for (int r = ty; r < kPackTile; r += 256 / kPackTile) {
-      const int a = a0 + r, bb = b0 + tx;
-      if (a < v && bb < v) out[(int64_t)a * v + bb] = tile[tx][r];
-    }
-  }
-}
-
-// Set-up of the packed solve: the two norms from lzp_pack's partials
-// (nparts each, summed in a fixed order by one workgroup); the state before
-// step 0 (slot 1) with the first flag; and, in place of the shares of an
-// occupied launch (occ_parts, occ_nparts each), (0, ||start||^2, 0), from
-// which the first fused step normalises the start vector.
-// Packed three-launch form: the state before the first step (slot 0) from
-// the packing's partial sums of ||b||^2 and ||D^1/2 b||^2; the start vector
-// is then normalised by ||D^1/2 b|| (fin's kFinBHat).
-__global__ __launch_bounds__(256) void lzp_init_normalised(const double* __restrict__ parts, int nparts, double* st,
-                                                           double rtol) {
-  __shared__ double sm[2][4];
-  double r[2] = {0.0, 0.0};
-  for (int k = threadIdx.x; k < nparts; k += 256) {
-    r[0] += parts[k];
-    r[1] += parts[nparts + k];
-  }
-  block_sum256<2>(r, sm);
-  if (threadIdx.x != 0) return;
-  const double bn = sqrt(r[0]), bhat = sqrt(r[1]);
-  for (int k = 0; k < kNState; ++k) st[k] = 0.0;
-  st[kC2] = 1.0;
-  st[kC1] = 1.0;
-  st[kPhiBar] = bhat;
-  st[kRes] = bhat;
-  st[kStateStride + kDone] = 0.0;
-  double* fin = st + 2 * kStateStride;
-  fin[kFinSteps] = 0.0;
-  fin[kFinRes] = bhat;
-  fin[kFinBeta] = 1.0;
-  fin[kFinTol] = rtol * bn;
-  fin[kFinBNorm] = bn;
-  fin[kFinBHat] = bhat;
-}
-
-__global__ __launch_bounds__(256) void lzp_init_fused(const double* __restrict__ parts, int nparts, double* st,
-                                                      double* __restrict__ occ_parts, int occ_nparts, double rtol) {
-  __shared__ double sm[2][4];
-  double r[2] = {0.0, 0.0};
-  for (int k = threadIdx.x; k < nparts; k += 256) {
-    r[0] += parts[k];
-    r[1] += parts[nparts + k];
-  }
-  block_sum256<2>(r, sm);
-  for (int k = threadIdx.x; k < 3 * occ_nparts; k += 256) occ_parts[k] = 0.0;
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  const double bn = sqrt(r[0]), bhat = sqrt(r[1]);
-  occ_parts[occ_nparts] = r[1];
-  double* s1 = st + kStateStride;  // the state before step 0
-  for (int k = 0; k < kNState; ++k) s1[k] = 0.0;
-  s1[kFirst] = 1.0;
-  st[kDone] = 0.0;
-  double* fin = st + 2 * kStateStride;
-  fin[kFinSteps] = 0.0;
-  fin[kFinRes] = bhat;
-  fin[kFinBeta] = 1.0;
-  fin[kFinTol] = rtol * bn;
-  fin[kFinBNorm] = bn;
-  fin[kFinBHat] = bhat;
-}
-
-inline int grid_n(int64_t n) {
-  int64_t g = ceil_div(n, 256);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(g, 4096));
-}
-
 }  // namespace
 
-// A_F symmetric (f_ov = 0): the Arnoldi process of GMRES reduces to the
-// three-term Lanczos recurrence and the Hessenberg least-squares problem to
-// a tridiagonal one, updated with one Givens rotation per step (GMRES and
-// MINRES coincide in exact arithmetic). Everything stays on the device,
-// including the stopping test; the host reads the outcome once per batch
-// of queued steps.
-// One Lanczos step on fixed buffers (see precond_solve_sym).
-// Device scalars: [0, kMaxBasis) and [kMaxBasis, 2 kMaxBasis) projections,
-// then norms; the Lanczos state's three slots start at 3.5 kMaxBasis.
-double* Solver::lanczos_state() const { return dsc_ + 3 * kMaxBasis + kMaxBasis / 2; }
-
-void Solver::lanczos_step(double* vprev, double* v, double* p, double* w1, double* w2, double* x, double* st,
-                          double* stn, hipStream_t s) {
-  int64_t n = n_;
-  const int64_t ov = (int64_t)eng_.o() * eng_.v();
-  double* part1 = partials_;
-  const FockOp* op = eng_.fock_op();
-  int nparts1 = kLzBlocks;
-  if (lz_mode_ == kLzPacked3) {
-    // packed pair layout (see precond_solve_sym): the same three launches
-    n = ov + (int64_t)op->npair * eng_.v() * eng_.v();
-    Timers* tm = eng_.timers();
-    fock_op_lanczos_vir_packed(*op, v, p, st + kDone, s);
-    if (tm) tm->begin(kTimerFock, s);
-    fock_op_lanczos_occ_packed(*op, v, vprev, st + kBeta, p, part1, kInnerSinglesScale, st + kDone, s);
-    if (tm) tm->end(kTimerFock, s);
-    nparts1 = (int)op->nparts_packed();
-  } else if (op && op->nparts() <= kMaxFusedParts) {
-    // p = A_F v_k - beta_k v_{k-1} and the partials of <v_k, p>; the timer
-    // covers the occupied launch
-    Timers* tm = eng_.timers();
-    fock_op_lanczos_vir(*op, v, p, st + kDone, s);
-    if (tm) tm->begin(kTimerFock, s);
-    fock_op_lanczos_occ(*op, v, vprev, st + kBeta, p, part1, kInnerSinglesScale, st + kDone, s);
-    if (tm) tm->end(kTimerFock, s);
-    nparts1 = (int)op->nparts();
-  } else {
-    eng_.fock_apply(v, v + ov, p, p + ov, s);
-    lz_step1<<<kLzBlocks, 256, 0, s>>>(n, p, vprev, v, st, part1, ov, kInnerSinglesScale);
-  }
-  lz_update<<<kLzBlocks, 256, 0, s>>>(n, v, w1, w2, x, p, part1, nparts1, st, stn,
-                                      lanczos_state() + 2 * kStateStride);
-  PNK_CHECK_LAUNCH();
-}
-
-// Six steps: the buffer rotation (v: period 3, w: period 2, state slot:
-// period 2) returns to its start, so the block can be recorded once as a
-// HIP graph and replayed.
-int Solver::lz_block_len() const { return lz_mode_ == kLzFused ? kPackedBlock : kLanczosBlock; }
-
-void Solver::lanczos_block(hipStream_t s) {
+// The symmetric solve's buffers: vectors in Qi_, sums and scalars in
+// partials_, state in the scalars after the projections, norms and staging
+// ([0, kMaxBasis) and [kMaxBasis, 2 kMaxBasis) projections, then norms, then
+// the staging area).
+InnerSolve Solver::inner_buffers(const FockEigen& eig, bool packed) const {
+  static_assert(kInnerPartsElems <= (int64_t)kReduceBlocks * kMaxBasis, "partials_ holds the inner solve's sums");
+  InnerSolve q;
+  q.eig = eig;
+  inner_shape(q, packed);
   const int64_t n = n_;
-  double* st = lanczos_state();
-  if (lz_mode_ == kLzFused) {
-    // packed: two launches per step, the update fused into the next step's
-    // virtual launch; four vectors rotate (P = p_{k-1}, V = v_{k-1}, N = v_k,
-    // Y = y_k -> p_k), period 4; w rotates with period 2
-    const FockOp& op = *eng_.fock_op();
-    const int np = (int)op.nparts_packed();
-    double *P = Qi_, *V = Qi_ + n, *N = Qi_ + 2 * n, *Y = Qi_ + 3 * n;
-    double *w1 = Qi_ + 4 * n, *w2 = Qi_ + 5 * n, *x = Qi_ + 6 * n;
-    double* fin = st + 2 * kStateStride;
-    Timers* tm = eng_.timers();
-    for (int k = 0; k < kPackedBlock; ++k) {
-      double* prev = st + ((k + 1) % 2) * kStateStride;  // state after step k-1
-      double* cur = st + (k % 2) * kStateStride;         // state after step k
-      // the timer covers the fused launch (the larger of the two)
-      if (tm) tm->begin(kTimerFock, s);
-      fock_op_lanczos_vir_fused(op, P, V, N, Y, w1, w2, x, partials_, np, prev, cur, fin, s);
-      if (tm) tm->end(kTimerFock, s);
-      fock_op_lanczos_occ_packed(op, N, V, cur + kBeta, Y, partials_, kInnerSinglesScale, cur + kDone, s);
-      double* oldP = P;
-      P = Y;     // p_k
-      Y = V;     // free
-      V = N;     // v_k
-      N = oldP;  // free
-      std::swap(w1, w2);
-    }
-    return;
-  }
-  double *vprev = Qi_, *v = Qi_ + n, *p = Qi_ + 2 * n, *w1 = Qi_ + 3 * n, *w2 = Qi_ + 4 * n, *x = Qi_ + 5 * n;
-  for (int k = 0; k < kLanczosBlock; ++k) {
-    double* cur = st + (k % 2) * kStateStride;
-    double* nxt = st + ((k + 1) % 2) * kStateStride;
-    lanczos_step(vprev, v, p, w1, w2, x, cur, nxt, s);
-    std::swap(vprev, v);  // v_{k-1} <- v_k
-    std::swap(v, p);      // v_k <- v_{k+1}; p <- free buffer
-    std::swap(w1, w2);    // w_{k-1} <- w_k
-  }
+  q.v0 = Qi_; q.v1 = Qi_ + n; q.w1 = Qi_ + 2 * n; q.w2 = Qi_ + 3 * n; q.x = Qi_ + 4 * n;
+  q.parts = partials_;
+  q.coef = partials_ + 2 * 3 * kInnerMaxParts;
+  q.norm_parts = q.coef + kInnerSegment * kInnerCoef;
+  q.state = dsc_ + 3 * kMaxBasis + kMaxBasis / 2;
+  return q;
 }
 
 namespace {
@@ -617,11 +217,11 @@ std::vector<hipGraphNode_t> chain_order(hipGraph_t g) {
   return out;
 }
 
-// Inserts event record nodes before and after each timed A_F kernel node
-// (fock_op_is_timed_lanczos_kernel) of a chain graph: pair k (events ev[2k],
-// ev[2k+1]) brackets the k-th such launch in stream order, so its duration
-// can be read after a replay. Returns the number of pairs, -1 on failure.
-int bracket_fock_nodes(hipGraph_t g, const hipEvent_t* ev, int max_pairs, bool fused) {
+// Inserts event record nodes before and after each step kernel of the inner
+// solve in a chain graph: pair k (events ev[2k], ev[2k+1]) brackets the k-th
+// such launch in stream order, so its duration can be read after a replay.
+// Returns the number of pairs, -1 on failure.
+int bracket_step_nodes(hipGraph_t g, const hipEvent_t* ev, int max_pairs) {
   const std::vector<hipGraphNode_t> nodes = chain_order(g);
   if (nodes.empty()) return -1;
   int k = 0;
@@ -631,7 +231,7 @@ int bracket_fock_nodes(hipGraph_t g, const hipEvent_t* ev, int max_pairs, bool f
     if (type != hipGraphNodeTypeKernel) continue;
     hipKernelNodeParams kp{};
     if (hipGraphKernelNodeGetParams(node, &kp) != hipSuccess) return -1;
-    if (!fock_op_is_timed_lanczos_kernel(kp.func, fused)) continue;
+    if (!inner_is_step_kernel(kp.func)) continue;
     if (k >= max_pairs) return -1;
     size_t nd = 0, ns = 0;
     if (hipGraphNodeGetDependencies(node, nullptr, &nd) != hipSuccess) return -1;
@@ -657,25 +257,23 @@ int bracket_fock_nodes(hipGraph_t g, const hipEvent_t* ev, int max_pairs, bool f
 
 }  // namespace
 
-// Records nb six-step blocks as one HIP graph. The timed variant also holds
-// event record nodes around each fused A_F launch (used only while the
-// engine's timers are on).
-bool Solver::ensure_lanczos_graph(bool timed, int nb) {
+// Records nb blocks of step launches as one HIP graph. The timed variant also
+// holds event record nodes around each launch (used only while the engine's
+// timers are on).
+bool Solver::ensure_inner_graph(const InnerSolve& q, bool timed, int nb) {
   if (nb < 1 || nb > kMaxBatchBlocks) return false;
-  hipGraphExec_t& exec = lz_graphs_[lz_mode_][timed ? 1 : 0][nb];
-  bool& failed = lz_graph_failed_[lz_mode_][timed ? 1 : 0][nb];
+  hipGraphExec_t& exec = inner_graphs_[q.packed][timed][nb];
+  bool& failed = inner_graph_failed_[q.packed][timed][nb];
   if (exec) return true;
   if (failed) return false;
-  const int pairs = nb * lz_block_len();
+  const int pairs = nb * kInnerBlock;
   if (timed) {
-    while ((int)lz_ev_.size() < 2 * pairs) {
+    while ((int)inner_ev_.size() < 2 * pairs) {
       hipEvent_t e = nullptr;
       if (hipEventCreate(&e) != hipSuccess) { failed = true; return false; }
-      lz_ev_.push_back(e);
+      inner_ev_.push_back(e);
     }
   }
-  Timers* tm = eng_.timers();
-  eng_.set_timers(nullptr);  // no host-side timer events inside a graph
   bool ok = false;
   hipStream_t cs = nullptr;
   hipGraph_t g = nullptr;
@@ -684,20 +282,19 @@ bool Solver::ensure_lanczos_graph(bool timed, int nb) {
     // a failure while recording must not leave a partial graph behind
     bool threw = false;
     try {
-      for (int q = 0; q < nb; ++q) lanczos_block(cs);
+      for (int k = 0; k < pairs; ++k) inner_step(q, k % 2, kInnerSinglesScale, cs);
     } catch (const std::exception& e) {
       threw = true;
       if (std::getenv("PNK_DEBUG")) std::fprintf(stderr, "pnk: graph capture failed: %s\n", e.what());
     }
     if (hipStreamEndCapture(cs, &g) == hipSuccess && g && !threw &&
-        (!timed || bracket_fock_nodes(g, lz_ev_.data(), pairs, lz_mode_ == kLzFused) == pairs) &&
+        (!timed || bracket_step_nodes(g, inner_ev_.data(), pairs) == pairs) &&
         hipGraphInstantiate(&exec, g, nullptr, nullptr, 0) == hipSuccess)
       ok = true;
   }
   if (g) (void)hipGraphDestroy(g);
   if (cs) (void)hipStreamDestroy(cs);
   (void)hipGetLastError();
-  eng_.set_timers(tm);
   if (!ok) {
     if (std::getenv("PNK_DEBUG"))
       std::fprintf(stderr, "pnk: no %s inner-solve graph of %d blocks\n", timed ? "timed" : "plain", nb);
@@ -710,119 +307,80 @@ bool Solver::ensure_lanczos_graph(bool timed, int nb) {
 // A_F symmetric (f_ov = 0): the Arnoldi process of GMRES reduces to the
 // three-term Lanczos recurrence and the Hessenberg least-squares problem to
 // a tridiagonal one, updated with one Givens rotation per step (GMRES and
-// MINRES coincide in exact arithmetic). Everything stays on the device:
-// blocks of six steps are replayed as one HIP graph, and the host reads the
-// residual estimate after each block (so up to five extra steps run past
-// convergence; they only lower the residual further).
-int Solver::precond_solve_sym(const double* b, double* x, double rtol, int maxit, hipStream_t s, bool* converged,
-                              bool packed) {
+// MINRES coincide in exact arithmetic). It runs in the eigenvectors of the
+// Fock blocks (inner_solve.hpp): b is rotated into them and x back. Everything
+// stays on the device, including the stopping test; the host reads the
+// outcome once per batch of queued steps. At o = 20, v = 180 and rtol 1e-12
+// this takes 1440 us, a third of them the rotations; on the given orbitals,
+// with the Fock products in every step, it took 7900 (o = 10, v = 90: 400
+// and 960).
+int Solver::precond_solve_sym(const FockEigen& eig, const double* b, double* x, double rtol, int maxit, hipStream_t s,
+                              bool* converged, bool packed) {
   const int64_t n = n_;
-  const int o = eng_.o(), vir = eng_.v();
-  const int64_t ov = (int64_t)o * vir;
-  const double rs = std::sqrt(kInnerSinglesScale);
-  double* st = lanczos_state();
-  const double* fin = st + 2 * kStateStride;
-  const FockOp* op = eng_.fock_op();
-  const int mode = !packed ? kLzFull : (fock_op_fused_step(*op) ? kLzFused : kLzPacked3);
-  lz_mode_ = mode;
+  InnerSolve q = inner_buffers(eig, packed);
   // scaled system D^1/2 A_F D^1/2 z = D^1/2 b, x = D^1/2 z, D = diag(s I, I).
   // ||b|| stays on the device (b = 0 gives a zero start and a stop at the
   // first step).
-  double* xi;  // the iterate z
-  if (mode == kLzPacked3) {
-    // pair-symmetric b: the recurrence runs on pairs i <= j, with inner
-    // products that count the blocks of pairs i < j twice (those of the full
-    // vectors), so its steps are those of the full-layout recurrence; the
-    // buffers are those of the full layout, n_l of each used
-    const int64_t nl = ov + (int64_t)op->npair * vir * vir;
-    double *vprev = Qi_, *v = Qi_ + n, *w1 = Qi_ + 3 * n, *w2 = Qi_ + 4 * n;
-    xi = Qi_ + 5 * n;
-    double* parts = partials_ + 3 * kMaxFusedParts;
-    lzp_pack<<<dim3(kPackBlocksX, op->npair + 1), 256, 0, s>>>(o, vir, b, rs, xi, parts,
-                                                                 ZeroList{{vprev, w1, w2, nullptr}});
-    lzp_init_normalised<<<1, 256, 0, s>>>(parts, kPackBlocksX * (op->npair + 1), st, rtol);
-    scale_by_inverse(nl, xi, fin + kFinBHat, v, s);  // v_1 = D^1/2 b / ||D^1/2 b||
-    fill(nl, 0.0, xi, s);
-  } else if (mode == kLzFused) {
-    // the same on the two-launch form: the first fused step normalises the
-    // start vector P = D^1/2 b (V = 0)
-    double *P0 = Qi_, *V0 = Qi_ + n, *w1 = Qi_ + 4 * n, *w2 = Qi_ + 5 * n;
-    xi = Qi_ + 6 * n;
-    double* parts = partials_ + 3 * kMaxFusedParts;
-    lzp_pack<<<dim3(kPackBlocksX, op->npair + 1), 256, 0, s>>>(o, vir, b, rs, P0, parts,
-                                                                 ZeroList{{V0, w1, w2, xi}});
-    lzp_init_fused<<<1, 256, 0, s>>>(parts, kPackBlocksX * (op->npair + 1), st, partials_,
-                                      (int)op->nparts_packed(), rtol);
-  } else {
-    double *vprev = Qi_, *v = Qi_ + n, *w1 = Qi_ + 3 * n, *w2 = Qi_ + 4 * n;
-    xi = Qi_ + 5 * n;
-    nrm2(n, b, dsc_ + 2, partials_, s);
-    copy(n, b, xi, s);
-    axpby(ov, rs, b, 0.0, xi, s);
-    nrm2(n, xi, dsc_ + 1, partials_, s);
-    lz_init<<<1, 1, 0, s>>>(st, dsc_ + 1, dsc_ + 2, rtol);
-    scale_by_inverse(n, xi, dsc_ + 1, v, s);  // v_1 = D^1/2 b / ||D^1/2 b||
-    fill(n, 0.0, vprev, s);
-    fill(n, 0.0, w1, s);
-    fill(n, 0.0, w2, s);
-    fill(n, 0.0, xi, s);
-  }
-  PNK_CHECK_LAUNCH();
+  const int nshares = inner_load(q, b, Qi_ + 2 * n, Qi_ + 3 * n, kInnerSinglesScale, s);
+  const int64_t rows = (q.n - (int64_t)eig.o * eig.v) / ((int64_t)eig.v * eig.v);
+  if (eig.ut_v) inner_rotate_vir(eig, true, rows, q.v0, q.v1, s);
+  // the cap, in whole blocks of steps: six, or four less the first one's
+  // normalising launch where the packed step is of the short form
+  const FockOp* op = eng_.fock_op();
+  const int64_t cap = packed && op && op->bm == 32 ? 4 * ceil_div(maxit, 4) - 1 : 6 * ceil_div(maxit, 6);
+  const int limit = (int)std::min<int64_t>(cap, 0x7fffffff);
+  inner_begin(q, nshares, rtol, limit, s);
+  const double* fin = q.state + 2 * kInnerState;
   Timers* tm = eng_.timers();
   // the event pairs are read for a sample of the solves: each bracketed
   // launch pays for its two event nodes, which would slow every solve
-  const bool timeable = (packed || (op && op->nparts() <= kMaxFusedParts)) && lz_solves_++ % kTimedEvery == 0;
-  const int len = lz_block_len();
-  // The first batch queues as many blocks as the last solve needed steps
-  // (as one recorded graph), later ones a block each. The device stops the
-  // recurrence at the first step that meets the test, so the batch size
-  // changes the cost only, never the result. With timing on, the event
-  // pairs of the timed launches that ran are read: the occupied launches
-  // of the three-launch forms (one per step), the fused first launches of
-  // the two-launch form (one per step plus the normalising first launch; a
-  // step's update completes in the next step's first launch).
-  const bool two = mode == kLzFused;
-  int batch = std::min(std::max(1, (int)ceil_div(lz_steps_hint_ + (two ? 1 : 0), len)), (int)kMaxBatchBlocks);
-  int launched = 0, steps = 0;
+  const bool timeable = inner_solves_++ % kTimedEvery == 0;
+  // The first batch queues the launches that the last solve needed (as one
+  // recorded graph), later ones a block each. The device stops the recurrence
+  // at the first step that meets the test, so the batch size changes the cost
+  // only, never the result. k steps take k + 1 launches.
+  constexpr int kSegBlocks = kInnerSegment / kInnerBlock;
+  int batch = std::max(1, (int)ceil_div(inner_steps_hint_ + 1, kInnerBlock));
+  int launched = 0, seg_launched = 0, seg_base = 0, steps = 0;
   bool conv = false;
-  while (launched < maxit) {
-    const int nb = (int)std::min<int64_t>(batch, ceil_div(maxit - launched, len));
+  while (true) {
+    const int nb = std::min(batch, kSegBlocks - seg_launched / kInnerBlock);
     bool timed = false, graph = false;
     if (use_graphs_) {
-      timed = tm && timeable && ensure_lanczos_graph(true, nb);
-      graph = timed || ensure_lanczos_graph(false, nb);
+      timed = tm && timeable && ensure_inner_graph(q, true, nb);
+      graph = timed || ensure_inner_graph(q, false, nb);
     }
-    if (graph) PNK_HIP(hipGraphLaunch(lz_graphs_[mode][timed ? 1 : 0][nb], s));
+    if (graph) PNK_HIP(hipGraphLaunch(inner_graphs_[packed][timed][nb], s));
     else
-      for (int q = 0; q < nb; ++q) lanczos_block(s);
+      for (int k = 0; k < nb * kInnerBlock; ++k) inner_step(q, k % 2, kInnerSinglesScale, s);
     const int before = launched;
-    launched += nb * len;
+    launched += nb * kInnerBlock;
+    seg_launched += nb * kInnerBlock;
     batch = 1;
-    read_scalars(host_, fin, kFinCount, s);  // synchronises the stream
-    steps = (int)host_[kFinSteps];
+    read_scalars(host_, fin, kInnerFinRead, s);  // synchronises the stream
+    steps = (int)host_[kInnerFinSteps];
     // ||b - A_F x|| <= ||D^1/2 (b - A_F x)|| = the scaled residual (D >= I)
-    const double res = host_[kFinRes], bn = host_[kFinBNorm];
-    const bool ok = std::isfinite(res) && (res <= rtol * bn || host_[kFinBeta] == 0.0);
+    const double res = host_[kInnerFinRes], bn = host_[kInnerFinBNorm];
+    conv = std::isfinite(res) && steps > 0 && (res <= rtol * bn || host_[kInnerFinBeta] == 0.0);
     if (timed) {
-      const int ran_total = std::min(launched, two ? steps + 1 : steps);
-      const int ran = std::min(nb * len, ran_total - before);
+      const int ran = std::min(nb * kInnerBlock, std::min(launched, steps + 1) - before);
       for (int k = 0; k < ran; ++k) {
         float ms = 0.f;
-        if (hipEventElapsedTime(&ms, lz_ev_[2 * k], lz_ev_[2 * k + 1]) == hipSuccess) tm->add(kTimerFock, 1, ms);
+        if (hipEventElapsedTime(&ms, inner_ev_[2 * k], inner_ev_[2 * k + 1]) == hipSuccess) tm->add(kTimerFock, 1, ms);
         else (void)hipGetLastError();
       }
     }
-    if (!std::isfinite(res)) break;
-    if (ok) { conv = true; break; }
+    if (conv || !std::isfinite(res) || steps >= limit) break;
+    if (seg_launched == kInnerSegment) {
+      inner_finish(q, steps - seg_base, seg_base == 0, true, 0, kInnerSinglesScale, s);
+      seg_base = steps;
+      seg_launched = 0;
+    }
   }
-  lz_steps_hint_ = steps;
-  if (packed) {
-    lzp_unpack<<<dim3(kPackBlocksX, o * o + 1), 256, 0, s>>>(o, vir, xi, rs, x);
-    PNK_CHECK_LAUNCH();
-  } else {
-    copy(n, xi, x, s);
-    axpby(ov, rs, xi, 0.0, x, s);
-  }
+  inner_steps_hint_ = steps;
+  inner_finish(q, steps - seg_base, seg_base == 0, false, 0, kInnerSinglesScale, s);
+  if (eig.ut_v) inner_rotate_vir(eig, false, rows, q.x, Qi_ + 5 * n, s);
+  inner_unload(q, Qi_, Qi_ + n, kInnerSinglesScale, x, s);
   if (converged) *converged = conv;
   return steps;
 }
@@ -839,9 +397,10 @@ int Solver::precond_solve(const double* b, double* x, double rtol, int maxit, in
     ~EndTimer() { if (t) t->end(kTimerPrecond, s); }
   } end_timer{tm, s};
   if (eng_.fov_zero() && sym_inner_ && restart_ >= 5) {
-    const FockOp* op = eng_.fock_op();
-    const bool packed = pair_symmetric && op && op->pt > 0 && op->nparts_packed() <= kMaxFusedParts && restart_ >= 6;
-    return precond_solve_sym(b, x, rtol, maxit, s, converged, packed);
+    // (no eigenvectors, for Fock blocks that are not finite: GMRES below)
+    const FockEigen* eig = eng_.fock_eigen(s);
+    const bool packed = pair_symmetric && eng_.fock_op() && restart_ >= 6;
+    if (eig) return precond_solve_sym(*eig, b, x, rtol, maxit, s, converged, packed);
   }
   double bn, dummy;
   norms(n, b, &dummy, &bn, s);

@@ -7,6 +7,7 @@
 
 #include "ccsd.hpp"
 #include "gauge.hpp"
+#include "inner_solve.hpp"
 
 namespace pnk {
 
@@ -88,15 +89,13 @@ class Solver {
                             std::vector<double>* ritz_re, std::vector<double>* ritz_im);
   // Symmetric A_F (f_ov = 0): device-resident Lanczos form of GMRES, on
   // the full or the packed pair layout.
-  int precond_solve_sym(const double* b, double* x, double rtol, int maxit, hipStream_t s, bool* converged,
-                        bool packed);
+  int precond_solve_sym(const FockEigen& eig, const double* b, double* x, double rtol, int maxit, hipStream_t s,
+                        bool* converged, bool packed);
   // Use the short-recurrence form when A_F is symmetric (default on).
   void set_symmetric_inner(bool on) { sym_inner_ = on; }
   // Replay recorded HIP graphs for the inner iterations (default on).
   void set_graphs(bool on) { use_graphs_ = on; }
-  static constexpr int kLanczosBlock = 6;  // steps per recorded block (full layout)
-  static constexpr int kPackedBlock = 4;   // steps per recorded block (packed layout, fused update)
-  // (the packed three-launch form uses kLanczosBlock)
+  static constexpr int kInnerBlock = 4;  // launches per recorded block of the inner solve (even: the state alternates)
   void solve_pnk(double* x, const PnkOptions& opt, SolveStats* st, hipStream_t s);
   void solve_fp_diis(double* x, const FpOptions& opt, SolveStats* st, hipStream_t s);
   // Solve for the amplitudes of a non-orthogonal or redundant gauge
@@ -142,27 +141,18 @@ class Solver {
   // one line per outer iteration on stderr when PNK_VERBOSE is set
   bool verbose_ = std::getenv("PNK_VERBOSE") != nullptr;
   bool use_graphs_ = true;
-  // recorded runs of nb blocks, nb = 1 .. kMaxBatchBlocks
-  static constexpr int kMaxBatchBlocks = 16;
-  // form of the current symmetric solve: full layout; packed pairs, three
-  // launches per step; packed pairs, two launches (fused update)
-  enum { kLzFull = 0, kLzPacked3 = 1, kLzFused = 2, kLzModes = 3 };
-  hipGraphExec_t lz_graphs_[kLzModes][2][kMaxBatchBlocks + 1] = {};  // [mode][timed][nb]
-  bool lz_graph_failed_[kLzModes][2][kMaxBatchBlocks + 1] = {};
-  int lz_mode_ = kLzFull;
-  std::vector<hipEvent_t> lz_ev_;  // event pairs around the A_F launches of a timed run
-  int lz_steps_hint_ = 0;          // steps the last symmetric solve ran
+  // recorded runs of nb blocks, nb = 1 .. kMaxBatchBlocks (a segment at most)
+  static constexpr int kMaxBatchBlocks = kInnerSegment / kInnerBlock;
+  hipGraphExec_t inner_graphs_[2][2][kMaxBatchBlocks + 1] = {};  // [packed][timed][nb]
+  bool inner_graph_failed_[2][2][kMaxBatchBlocks + 1] = {};
+  std::vector<hipEvent_t> inner_ev_;  // event pairs around the step launches of a timed run
+  int inner_steps_hint_ = 0;          // steps the last symmetric solve ran
   // With timing on, one symmetric solve in kTimedEvery replays the graphs
   // with event nodes (they cost several microseconds per bracketed launch)
   static constexpr int kTimedEvery = 8;
-  int64_t lz_solves_ = 0;
-  void lanczos_step(double* vprev, double* v, double* p, double* w1, double* w2, double* x, double* st,
-                    double* stn, hipStream_t s);
-  // state slots of the Lanczos recurrence (device scalars)
-  double* lanczos_state() const;
-  void lanczos_block(hipStream_t s);
-  int lz_block_len() const;
-  bool ensure_lanczos_graph(bool timed, int nb);
+  int64_t inner_solves_ = 0;
+  InnerSolve inner_buffers(const FockEigen& eig, bool packed) const;
+  bool ensure_inner_graph(const InnerSolve& q, bool timed, int nb);
   std::vector<double> hist_;
   const Gauge* gauge_ = nullptr;
   // the maps the solvers iterate on, in the gauge when one is set
