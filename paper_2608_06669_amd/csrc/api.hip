@@ -158,14 +158,12 @@ void Handle::ensure(const cc_problem* p, int lowp, int m_max, int restart, int d
     sol_r = R;
     sol_d = Dd;
   }
-  if (!hash_buf) hash_buf = (uint64_t*)dev_alloc((kReduceBlocks + 8) * sizeof(uint64_t));
+  if (!hash_buf) hash_buf = (uint64_t*)dev_alloc((kHashArrays * kHashBlocks + 8) * sizeof(uint64_t));
   // content key of the problem
   const int64_t n = o + v;
-  uint64_t* parts = hash_buf + 8;
-  hash64((int64_t)o * o, p->f_oo, hash_buf + 0, parts, s);
-  hash64((int64_t)o * v, p->f_ov, hash_buf + 1, parts, s);
-  hash64((int64_t)v * v, p->f_vv, hash_buf + 2, parts, s);
-  hash64((int64_t)naux * n * n, p->L, hash_buf + 3, parts, s);
+  const double* arrays[kHashArrays] = {p->f_oo, p->f_ov, p->f_vv, p->L};
+  const int64_t lens[kHashArrays] = {(int64_t)o * o, (int64_t)o * v, (int64_t)v * v, (int64_t)naux * n * n};
+  hash_arrays(arrays, lens, hash_buf, hash_buf + 8, s);
   uint64_t hv[4];
   PNK_HIP(hipMemcpyAsync(hv, hash_buf, sizeof(hv), hipMemcpyDeviceToHost, s));
   PNK_HIP(hipStreamSynchronize(s));
@@ -376,11 +374,8 @@ static cc_status precond_solve_impl(cc_handle* h, const cc_problem* p, const dou
   PNK_REQUIRE(b1 && b2 && x1 && x2, "array arguments must not be NULL");
   PNK_REQUIRE(rtol > 0 && rtol < 1 && maxit >= 1, "rtol must be in (0, 1) and maxit >= 1");
   H->ensure(p, 0, 1, 30, 0, s, true);
-  const int64_t ov = H->eng->o() * (int64_t)H->eng->v(), n2 = H->eng->nvec() - ov;
-  pack(ov, n2, b1, b2, H->xb, s);
   bool conv = true;
-  const int it = H->sol->precond_solve(H->xb, H->xa, rtol, maxit, 30, s, &conv, pair_symmetric);
-  unpack(ov, n2, H->xa, x1, x2, s);
+  const int it = H->sol->precond_solve({b1, b2}, {x1, x2}, H->xb, H->xa, rtol, maxit, 30, s, &conv, pair_symmetric);
   PNK_HIP(hipStreamSynchronize(s));
   if (iters_out) *iters_out = it;
   return conv ? CC_OK : CC_NOT_CONVERGED;

@@ -108,7 +108,7 @@ __device__ inline double diagonal(const Args& p, const Block& b, const double* e
 // it; E elements per thread run side by side, since each one's recurrence is a
 // dependent chain. The scalars of the steps behind and eps_v come from LDS
 // (read from memory inside the chain, a step took 27 us plus 2 us for each
-// step behind; now @STEP@). Each workgroup adds the partial sums of the launch
+// step behind; now 15 us plus 0.65). Each workgroup adds the partial sums of the launch
 // before in the same fixed order, so all take the same scalars and no
 // reduction needs a launch of its own.
 template <bool PACKED, int E>
@@ -391,8 +391,8 @@ __global__ void inner_rebase_state(double* st) {
 constexpr int kPackTile = 32;
 constexpr int kPackBlocksX = 16;  // workgroups per pair block (grid-stride over its tiles)
 
-__global__ __launch_bounds__(256) void inner_pack(int o, int v, const double* __restrict__ b, double rs,
-                                                  double* __restrict__ xp, double* __restrict__ parts) {
+__global__ __launch_bounds__(256) void inner_pack(int o, int v, VecIn b, double rs, double* __restrict__ xp,
+                                                  double* __restrict__ parts) {
   __shared__ double tile[kPackTile][kPackTile + 1];
   __shared__ double sm[2][4];
   const int npair = o * (o + 1) / 2;
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256) void inner_pack(int o, int v, const double* __
   for (int y = blockIdx.y; y <= npair; y += gridDim.y) {
     if (y == npair) {
       for (int64_t e = blockIdx.x * (int64_t)256 + tid; e < ov; e += (int64_t)gridDim.x * 256) {
-        const double x = b[e];
+        const double x = b.x1[e];
         xp[e] = rs * x;
         s_plain += x * x;
         s_scaled += (rs * x) * (rs * x);
@@ -412,8 +412,8 @@ __global__ __launch_bounds__(256) void inner_pack(int o, int v, const double* __
     int i, j;
     decode_pair(y, o, true, i, j);
     const double w = i == j ? 1.0 : 2.0;
-    const double* __restrict__ bij = b + ov + (int64_t)(i * o + j) * vv;
-    const double* __restrict__ bji = b + ov + (int64_t)(j * o + i) * vv;
+    const double* __restrict__ bij = b.x2 + (int64_t)(i * o + j) * vv;
+    const double* __restrict__ bji = b.x2 + (int64_t)(j * o + i) * vv;
     double* __restrict__ out = xp + ov + (int64_t)y * vv;
     const int nt = (v + kPackTile - 1) / kPackTile;
     const int tx = tid % kPackTile, ty = tid / kPackTile;
@@ -446,12 +446,12 @@ __global__ __launch_bounds__(256) void inner_pack(int o, int v, const double* __
 }
 
 // The full layout: v0 = D^1/2 b, with the same shares.
-__global__ __launch_bounds__(256) void inner_copy_in(int64_t n, int64_t ov, const double* __restrict__ b, double rs,
-                                                     double* __restrict__ x, double* __restrict__ parts) {
+__global__ __launch_bounds__(256) void inner_copy_in(int64_t n, int64_t ov, VecIn b, double rs, double* __restrict__ x,
+                                                     double* __restrict__ parts) {
   __shared__ double sm[2][4];
   double r2[2] = {0.0, 0.0};
   for (int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-    const double y = b[e], z = e < ov ? rs * y : y;
+    const double y = e < ov ? b.x1[e] : b.x2[e - ov], z = e < ov ? rs * y : y;
     x[e] = z;
     r2[0] += y * y;
     r2[1] += z * z;
@@ -463,25 +463,25 @@ __global__ __launch_bounds__(256) void inner_copy_in(int64_t n, int64_t ov, cons
   }
 }
 __global__ __launch_bounds__(256) void inner_copy_out(int64_t n, int64_t ov, const double* __restrict__ x, double rs,
-                                                      double* __restrict__ y) {
+                                                      VecOut y) {
   for (int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256)
-    y[e] = e < ov ? rs * x[e] : x[e];
+    if (e < ov) y.x1[e] = rs * x[e];
+    else y.x2[e - ov] = x[e];
 }
 
 // x (full layout) = D^1/2 unpack(xp): x_ij = xp_P(i,j) for i <= j, and
 // xp_P(j,i)^T (through LDS) for i > j; singles times rs.
-__global__ __launch_bounds__(256) void inner_unpack(int o, int v, const double* __restrict__ xp, double rs,
-                                                    double* __restrict__ x) {
+__global__ __launch_bounds__(256) void inner_unpack(int o, int v, const double* __restrict__ xp, double rs, VecOut x) {
   __shared__ double tile[kPackTile][kPackTile + 1];
   const int64_t vv = (int64_t)v * v, ov = (int64_t)o * v;
   const int tid = threadIdx.x;
   if ((int)blockIdx.y == o * o) {
-    for (int64_t e = blockIdx.x * (int64_t)256 + tid; e < ov; e += (int64_t)gridDim.x * 256) x[e] = rs * xp[e];
+    for (int64_t e = blockIdx.x * (int64_t)256 + tid; e < ov; e += (int64_t)gridDim.x * 256) x.x1[e] = rs * xp[e];
     return;
   }
   const int i = blockIdx.y / o, j = blockIdx.y % o;
   auto pair = [&](int a, int b) { return a * o - a * (a - 1) / 2 + (b - a); };  // a <= b
-  double* __restrict__ out = x + ov + (int64_t)blockIdx.y * vv;
+  double* __restrict__ out = x.x2 + (int64_t)blockIdx.y * vv;
   if (i <= j) {
     const double* __restrict__ src = xp + ov + (int64_t)pair(i, j) * vv;
     for (int64_t e = blockIdx.x * (int64_t)256 + tid; e < vv; e += (int64_t)gridDim.x * 256) out[e] = src[e];
@@ -534,14 +534,14 @@ __global__ __launch_bounds__(256) void inner_begin_kernel(const double* __restri
   fin[kInnerFinBHat] = bhat;
 }
 
-// x_ij = x_ji^T for i > j of a full-layout vector, in place (through LDS).
-__global__ __launch_bounds__(256) void inner_mirror_kernel(int o, int v, double* __restrict__ x) {
+// x_ij = x_ji^T for i > j of a full-layout vector's doubles, in place (through LDS).
+__global__ __launch_bounds__(256) void inner_mirror_kernel(int o, int v, double* __restrict__ x2) {
   __shared__ double tile[kPackTile][kPackTile + 1];
   const int i = blockIdx.y / o, j = blockIdx.y % o;
   if (i <= j) return;
-  const int64_t vv = (int64_t)v * v, ov = (int64_t)o * v;
-  double* __restrict__ out = x + ov + (int64_t)blockIdx.y * vv;
-  const double* __restrict__ src = x + ov + (int64_t)(j * o + i) * vv;
+  const int64_t vv = (int64_t)v * v;
+  double* __restrict__ out = x2 + (int64_t)blockIdx.y * vv;
+  const double* __restrict__ src = x2 + (int64_t)(j * o + i) * vv;
   const int tid = threadIdx.x;
   const int nt = (v + kPackTile - 1) / kPackTile;
   const int tx = tid % kPackTile, ty = tid / kPackTile;
@@ -649,8 +649,8 @@ constexpr int kOccMax = 24;  // 64 positions of o (o + 1) / 2 pairs fit a workgr
 struct OccArgs {
   int o, v, nb, units, dwg;  // dwg: units rounded up to a multiple of 8; then workgroups of singles
   const double* rot;         // row j: coefficients of the rotated index j
-  const double* src;
-  double* dst;
+  VecIn src;
+  VecOut dst;
   double rs;
   double* parts;
 };
@@ -670,17 +670,18 @@ __global__ __launch_bounds__(32 * KMAX < 64 ? 64 : 32 * KMAX) void inner_occ_ker
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nw = blockDim.x >> 6;
   const int o = p.o, v = p.v, npair = o * (o + 1) / 2;
-  const int64_t vv = (int64_t)v * v, ov = (int64_t)o * v;
+  const int64_t vv = (int64_t)v * v;
+  const int ov = o * v;
   double s_plain = 0.0, s_scaled = 0.0;
   auto row_of = [&](int k) { return k * o - k * (k - 1) / 2 - k; };  // P(k, l) = row_of(k) + l, k <= l
   if ((int)blockIdx.x >= p.dwg) {
     const int q = (blockIdx.x - p.dwg) * blockDim.x + tid;
-    if (q < (int)ov) {
+    if (q < ov) {
       const int j = q / v, a = q - j * v;
       double y = 0.0;
-      for (int l = 0; l < o; ++l) y += p.rot[j * o + l] * p.src[l * v + a];
-      p.dst[q] = p.rs * y;
-      const double x = p.src[q];
+      for (int l = 0; l < o; ++l) y += p.rot[j * o + l] * p.src.x1[l * v + a];
+      p.dst.x1[q] = p.rs * y;
+      const double x = p.src.x1[q];
       s_plain = x * x;
       s_scaled = (p.rs * x) * (p.rs * x);
     }
@@ -704,11 +705,11 @@ __global__ __launch_bounds__(32 * KMAX < 64 ? 64 : 32 * KMAX) void inner_occ_ker
           x[c] = w[c] = 0.0;
           if (P + c * nw < npair) {
             if constexpr (IN) {
-              const double m = p.src[ov + (int64_t)(k * o + l) * vv + e], mt = p.src[ov + (int64_t)(l * o + k) * vv + et];
+              const double m = p.src.x2[(int64_t)(k * o + l) * vv + e], mt = p.src.x2[(int64_t)(l * o + k) * vv + et];
               x[c] = 0.5 * (m + mt);
               w[c] = k == l ? 1.0 : 2.0;
             } else {
-              x[c] = p.src[ov + (int64_t)(P + c * nw) * vv + e];
+              x[c] = p.src.x2[(int64_t)(P + c * nw) * vv + e];
             }
           }
           l += nw;
@@ -753,11 +754,11 @@ __global__ __launch_bounds__(32 * KMAX < 64 ? 64 : 32 * KMAX) void inner_occ_ker
           }
           if (!in) continue;
           if constexpr (IN) {
-            double* out = p.dst + ov + e;
+            double* out = p.dst.x2 + e;
             if (i <= j0) out[(int64_t)(row_of(i) + j0) * vv] = y0;
             if (j1 > j0) out[(int64_t)(row_of(i) + j1) * vv] = y1;
           } else {
-            double *out = p.dst + ov + e, *outt = p.dst + ov + et;
+            double *out = p.dst.x2 + e, *outt = p.dst.x2 + et;
             if (i <= j0) out[(int64_t)(i * o + j0) * vv] = y0;
             if (i < j0) outt[(int64_t)(j0 * o + i) * vv] = y0;
             if (j1 > j0) {
@@ -802,7 +803,7 @@ void launch_occ(const OccArgs& p, unsigned grid, hipStream_t s) {
   PNK_CHECK_LAUNCH();
 }
 template <bool IN>
-int occ_rotation(const FockEigen& e, const double* src, double* dst, double rs, double* parts, hipStream_t s) {
+int occ_rotation(const FockEigen& e, VecIn src, VecOut dst, double rs, double* parts, hipStream_t s) {
   OccArgs p;
   p.o = e.o; p.v = e.v;
   p.nb = (e.v + 7) / 8;
@@ -851,15 +852,15 @@ GemmDesc product(int M, int N, int K, int64_t am, int64_t ak, int64_t bk, int64_
 
 // The occupied indices of a full-layout vector, through tmp.
 // forward: y[i'] = sum_i U[i][i'] x[i], U[i][i'] = ut[i' o + i]
-void rotate_occ(const FockEigen& e, bool forward, const double* in, double* tmp, double* out, hipStream_t s) {
+void rotate_occ(const FockEigen& e, bool forward, VecIn in, double* tmp, VecOut out, hipStream_t s) {
   const int o = e.o, v = e.v;
-  const int64_t vv = (int64_t)v * v, ov = (int64_t)o * v, am = forward ? o : 1, ak = forward ? 1 : o;
-  gemm64(product(o, v, o, am, ak, v, 1, v), e.ut_o, in, out, s);
+  const int64_t vv = (int64_t)v * v, am = forward ? o : 1, ak = forward ? 1 : o;
+  gemm64(product(o, v, o, am, ak, v, 1, v), e.ut_o, in.x1, out.x1, s);
   GemmDesc d = product(o, (int)(o * vv), o, am, ak, o * vv, 1, o * vv);
-  gemm64(d, e.ut_o, in + ov, tmp + ov, s);
+  gemm64(d, e.ut_o, in.x2, tmp, s);
   d = product(o, (int)vv, o, am, ak, vv, 1, vv);
   d.nb0 = o; d.b_b0 = o * vv; d.c_b0 = o * vv;
-  gemm64(d, e.ut_o, tmp + ov, out + ov, s);
+  gemm64(d, e.ut_o, tmp, out.x2, s);
 }
 
 }  // namespace
@@ -882,12 +883,13 @@ bool occ_sets_apply(const InnerSolve& q) {
   return q.packed && q.eig.o <= kOccMax && nb * nb + 8 + q.eig.v <= 16 * kInnerMaxRows;
 }
 
-int inner_load(const InnerSolve& q, const double* b, double* tmp1, double* tmp2, double singles_scale, hipStream_t s) {
+int inner_load(const InnerSolve& q, VecIn b, double* tmp1, double* tmp2, double singles_scale, hipStream_t s) {
   const double rs = std::sqrt(singles_scale);
+  const int64_t ov = (int64_t)q.eig.o * q.eig.v;
   if (q.eig.ut_o) {
-    if (occ_sets_apply(q)) return occ_rotation<true>(q.eig, b, q.v0, rs, q.norm_parts, s);
-    rotate_occ(q.eig, true, b, tmp1, tmp2, s);
-    b = tmp2;
+    if (occ_sets_apply(q)) return occ_rotation<true>(q.eig, b, {q.v0, q.v0 + ov}, rs, q.norm_parts, s);
+    rotate_occ(q.eig, true, b, tmp1, {tmp2, tmp2 + ov}, s);
+    b = {tmp2, tmp2 + ov};
   }
   int np;
   if (q.packed) {
@@ -895,7 +897,7 @@ int inner_load(const InnerSolve& q, const double* b, double* tmp1, double* tmp2,
     inner_pack<<<dim3(kPackBlocksX, pair_rows(q)), 256, 0, s>>>(q.eig.o, q.eig.v, b, rs, q.v0, q.norm_parts);
   } else {
     np = full_groups(q);
-    inner_copy_in<<<np, 256, 0, s>>>(q.n, (int64_t)q.eig.o * q.eig.v, b, rs, q.v0, q.norm_parts);
+    inner_copy_in<<<np, 256, 0, s>>>(q.n, ov, b, rs, q.v0, q.norm_parts);
   }
   PNK_CHECK_LAUNCH();
   return np;
@@ -949,21 +951,22 @@ void inner_finish(const InnerSolve& q, int steps, bool first_segment, bool rebas
   PNK_CHECK_LAUNCH();
 }
 
-void inner_unload(const InnerSolve& q, double* tmp1, double* tmp2, double singles_scale, double* out, hipStream_t s) {
+void inner_unload(const InnerSolve& q, double* tmp1, double* tmp2, double singles_scale, VecOut out, hipStream_t s) {
   const double rs = std::sqrt(singles_scale);
   const int o = q.eig.o, v = q.eig.v;
+  const int64_t ov = (int64_t)o * v;
   if (q.eig.ut_o && occ_sets_apply(q)) {
-    occ_rotation<false>(q.eig, q.x, out, rs, nullptr, s);
+    occ_rotation<false>(q.eig, {q.x, q.x + ov}, out, rs, nullptr, s);
     return;
   }
-  double* full = q.eig.ut_o ? tmp1 : out;
+  const VecOut full = q.eig.ut_o ? VecOut{tmp1, tmp1 + ov} : out;
   if (q.packed) inner_unpack<<<dim3(kPackBlocksX, o * o + 1), 256, 0, s>>>(o, v, q.x, rs, full);
-  else inner_copy_out<<<full_groups(q), 256, 0, s>>>(q.n, (int64_t)o * v, q.x, rs, full);
+  else inner_copy_out<<<full_groups(q), 256, 0, s>>>(q.n, ov, q.x, rs, full);
   PNK_CHECK_LAUNCH();
   if (q.eig.ut_o) {
-    rotate_occ(q.eig, false, full, tmp2, out, s);
+    rotate_occ(q.eig, false, {full.x1, full.x2}, tmp2, out, s);
     if (q.packed) {
-      inner_mirror_kernel<<<dim3(kPackBlocksX, o * o), 256, 0, s>>>(o, v, out);
+      inner_mirror_kernel<<<dim3(kPackBlocksX, o * o), 256, 0, s>>>(o, v, out.x2);
       PNK_CHECK_LAUNCH();
     }
   }

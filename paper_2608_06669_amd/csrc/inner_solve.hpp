@@ -25,6 +25,15 @@ struct FockEigen {
   const double *eps_o = nullptr, *eps_v = nullptr, *ut_o = nullptr, *u_o = nullptr, *ut_v = nullptr;
 };
 
+// A vector of the full layout: its singles and its doubles (one array, or two
+// of a caller's).
+struct VecIn {
+  const double *x1 = nullptr, *x2 = nullptr;
+};
+struct VecOut {
+  double *x1 = nullptr, *x2 = nullptr;
+};
+
 constexpr int kInnerSegment = 64;  // steps before the recurrence is based anew
 constexpr int kInnerCoef = 10;     // scalars kept for each step
 constexpr int kInnerState = 16;    // doubles per state slot: two slots, then `fin`
@@ -57,9 +66,9 @@ void inner_shape(InnerSolve& q, bool packed);
 // v0 = D^1/2 b in the packed layout (the pair-symmetric part of b) or the full
 // one, the occupied indices rotated into the eigenvectors of f_oo, D =
 // singles_scale on the singles and 1 on the doubles, with the sums of squares
-// of both; b is the full layout [b1 | b2]. tmp1, tmp2: vectors of the full
-// layout. Returns the number of shares of the sums.
-int inner_load(const InnerSolve& q, const double* b, double* tmp1, double* tmp2, double singles_scale, hipStream_t s);
+// of both; b is in the full layout. tmp1, tmp2: vectors of the full layout.
+// Returns the number of shares of the sums.
+int inner_load(const InnerSolve& q, VecIn b, double* tmp1, double* tmp2, double singles_scale, hipStream_t s);
 // The state before the first step; rtol ||b|| is the absolute tolerance, and
 // `limit` the step the recurrence ends at whatever its residual.
 void inner_begin(const InnerSolve& q, int nshares, double rtol, int limit, hipStream_t s);
@@ -76,7 +85,7 @@ void inner_finish(const InnerSolve& q, int steps, bool first_segment, bool rebas
                   hipStream_t s);
 // out = D^1/2 x in the full layout, the occupied indices rotated back (from a
 // packed solve, x_ji = x_ij^T exactly)
-void inner_unload(const InnerSolve& q, double* tmp1, double* tmp2, double singles_scale, double* out, hipStream_t s);
+void inner_unload(const InnerSolve& q, double* tmp1, double* tmp2, double singles_scale, VecOut out, hipStream_t s);
 
 // Rotates the virtual indices of `rows` v x v blocks and the singles, in place
 // through tmp, into (forward) or out of the eigenvectors of f_vv.

@@ -314,9 +314,10 @@ bool Solver::ensure_inner_graph(const InnerSolve& q, bool timed, int nb) {
 // this takes 1440 us, a third of them the rotations; on the given orbitals,
 // with the Fock products in every step, it took 7900 (o = 10, v = 90: 400
 // and 960).
-int Solver::precond_solve_sym(const FockEigen& eig, const double* b, double* x, double rtol, int maxit, hipStream_t s,
-                              bool* converged, bool packed) {
+int Solver::precond_solve_sym(const FockEigen& eig, VecIn b, VecOut x, double rtol, int maxit, hipStream_t s,
+                              bool* converged, bool pair_symmetric) {
   const int64_t n = n_;
+  const bool packed = pair_symmetric && eng_.fock_op() && restart_ >= 6;
   InnerSolve q = inner_buffers(eig, packed);
   // scaled system D^1/2 A_F D^1/2 z = D^1/2 b, x = D^1/2 z, D = diag(s I, I).
   // ||b|| stays on the device (b = 0 gives a zero start and a stop at the
@@ -385,23 +386,48 @@ int Solver::precond_solve_sym(const FockEigen& eig, const double* b, double* x, 
   return steps;
 }
 
+namespace {
+struct PrecondTimer {
+  Timers* t;
+  hipStream_t s;
+  PrecondTimer(Timers* timers, hipStream_t stream) : t(timers), s(stream) {
+    if (t) t->begin(kTimerPrecond, s);
+  }
+  ~PrecondTimer() {
+    if (t) t->end(kTimerPrecond, s);
+  }
+};
+}  // namespace
+
+// The eigenvectors the symmetric form works in; null where it does not apply
+// (f_ov, a short basis, Fock blocks that are not finite).
+const FockEigen* Solver::symmetric_form(hipStream_t s) {
+  return eng_.fov_zero() && sym_inner_ && restart_ >= 5 ? eng_.fock_eigen(s) : nullptr;
+}
+
+int Solver::precond_solve(VecIn b, VecOut x, double* bp, double* xp, double rtol, int maxit, int restart, hipStream_t s,
+                          bool* converged, bool pair_symmetric) {
+  const int64_t ov = (int64_t)eng_.o() * eng_.v(), n2 = n_ - ov;
+  if (const FockEigen* eig = symmetric_form(s)) {
+    PrecondTimer timer(eng_.timers(), s);
+    return precond_solve_sym(*eig, b, x, rtol, maxit, s, converged, pair_symmetric);
+  }
+  PNK_HIP(hipMemcpyAsync(bp, b.x1, ov * sizeof(double), hipMemcpyDeviceToDevice, s));
+  PNK_HIP(hipMemcpyAsync(bp + ov, b.x2, n2 * sizeof(double), hipMemcpyDeviceToDevice, s));
+  const int it = precond_solve(bp, xp, rtol, maxit, restart, s, converged, pair_symmetric);
+  PNK_HIP(hipMemcpyAsync(x.x1, xp, ov * sizeof(double), hipMemcpyDeviceToDevice, s));
+  PNK_HIP(hipMemcpyAsync(x.x2, xp + ov, n2 * sizeof(double), hipMemcpyDeviceToDevice, s));
+  return it;
+}
+
 int Solver::precond_solve(const double* b, double* x, double rtol, int maxit, int restart, hipStream_t s,
                           bool* converged, bool pair_symmetric) {
   PNK_REQUIRE(restart >= 1 && restart <= restart_, "precond_solve: restart exceeds the allocated basis");
   const int64_t n = n_;
   const int64_t ov = (int64_t)eng_.o() * eng_.v();
-  Timers* tm = eng_.timers();
-  if (tm) tm->begin(kTimerPrecond, s);
-  struct EndTimer {
-    Timers* t; hipStream_t s;
-    ~EndTimer() { if (t) t->end(kTimerPrecond, s); }
-  } end_timer{tm, s};
-  if (eng_.fov_zero() && sym_inner_ && restart_ >= 5) {
-    // (no eigenvectors, for Fock blocks that are not finite: GMRES below)
-    const FockEigen* eig = eng_.fock_eigen(s);
-    const bool packed = pair_symmetric && eng_.fock_op() && restart_ >= 6;
-    if (eig) return precond_solve_sym(*eig, b, x, rtol, maxit, s, converged, packed);
-  }
+  PrecondTimer timer(eng_.timers(), s);
+  if (const FockEigen* eig = symmetric_form(s))
+    return precond_solve_sym(*eig, {b, b + ov}, {x, x + ov}, rtol, maxit, s, converged, pair_symmetric);
   double bn, dummy;
   norms(n, b, &dummy, &bn, s);
   fill(n, 0.0, x, s);

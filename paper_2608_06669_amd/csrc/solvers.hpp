@@ -80,6 +80,10 @@ class Solver {
   // (it solves for the pair-symmetric part of b).
   int precond_solve(const double* b, double* x, double rtol, int maxit, int restart, hipStream_t s,
                     bool* converged = nullptr, bool pair_symmetric = false);
+  // The same for vectors in two arrays each; bp and xp: packed vectors for the
+  // paths that need them in one.
+  int precond_solve(VecIn b, VecOut x, double* bp, double* xp, double rtol, int maxit, int restart, hipStream_t s,
+                    bool* converged, bool pair_symmetric);
   // Spectral radius of the Jacobian of the (S)FP map, G = I - diag(D +
   // shift)^-1 J(t), on pair-symmetric vectors: m Arnoldi steps from q0
   // (device, packed, pair-symmetric, nonzero) with the Jacobian linearised
@@ -89,8 +93,8 @@ class Solver {
                             std::vector<double>* ritz_re, std::vector<double>* ritz_im);
   // Symmetric A_F (f_ov = 0): device-resident Lanczos form of GMRES, on
   // the full or the packed pair layout.
-  int precond_solve_sym(const FockEigen& eig, const double* b, double* x, double rtol, int maxit, hipStream_t s,
-                        bool* converged, bool packed);
+  int precond_solve_sym(const FockEigen& eig, VecIn b, VecOut x, double rtol, int maxit, hipStream_t s,
+                        bool* converged, bool pair_symmetric);
   // Use the short-recurrence form when A_F is symmetric (default on).
   void set_symmetric_inner(bool on) { sym_inner_ = on; }
   // Replay recorded HIP graphs for the inner iterations (default on).
@@ -111,6 +115,7 @@ class Solver {
   const std::vector<double>& history() const { return hist_; }
 
  private:
+  const FockEigen* symmetric_form(hipStream_t s);
   void read_scalars(double* host, const double* dev, int n, hipStream_t s);
   void upload(double* dev, const double* src, int n, hipStream_t s);
   // CGS2 of w (length n) against Q[0..m-1] (stride ldq), returns h (m

@@ -3,6 +3,8 @@
 
 #include "tensor_ops.hpp"
 
+#include <algorithm>
+
 namespace pnk {
 namespace {
 
@@ -274,33 +276,57 @@ __device__ inline uint64_t mix64(uint64_t z) {
   return z ^ (z >> 31);
 }
 
-__global__ __launch_bounds__(256) void hash_stage1(int64_t n, const double* __restrict__ x, uint64_t* partials) {
-  __shared__ uint64_t sm[256];
-  uint64_t acc = 0;
-  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const uint64_t bits = (uint64_t)__double_as_longlong(x[i]);
-    acc += mix64(bits ^ mix64((uint64_t)i + 0x9e3779b97f4a7c15ull));
-  }
-  sm[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sm[threadIdx.x] += sm[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partials[blockIdx.x] = sm[0];
-}
-__global__ __launch_bounds__(256) void hash_stage2(int nparts, const uint64_t* partials, int64_t n, uint64_t* out) {
+// Content hashes of up to kHashArrays arrays in one pair of launches: an array
+// takes a workgroup for every 2048 elements, kHashBlocks at most. Bound by memory (192 MB of factors at o = 20, v = 180): eight
+// loads in flight per thread (one at a time, over 512 workgroups, 97 us; now
+// 48).
+struct HashArgs {
+  const double* x[kHashArrays];
+  int64_t n[kHashArrays];
+  int first[kHashArrays + 1];  // workgroups of array a: first[a] .. first[a + 1] - 1
+  uint64_t* partials;
+  uint64_t* out;
+};
+
+__device__ inline uint64_t hash_sum(uint64_t acc, uint64_t* sm) {
   // integer addition is exact, so the summation order does not matter
-  __shared__ uint64_t sm[256];
-  uint64_t acc = 0;
-  for (int i = threadIdx.x; i < nparts; i += 256) acc += partials[i];
   sm[threadIdx.x] = acc;
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) {
     if (threadIdx.x < s) sm[threadIdx.x] += sm[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = mix64(sm[0] + mix64((uint64_t)n));
+  return sm[0];
+}
+
+__global__ __launch_bounds__(256) void hash_stage1(HashArgs p) {
+  __shared__ uint64_t sm[256];
+  int a = 0;
+  while ((int)blockIdx.x >= p.first[a + 1]) ++a;
+  const double* __restrict__ x = p.x[a];
+  const int64_t n = p.n[a], step = (int64_t)(p.first[a + 1] - p.first[a]) * 256;
+  uint64_t acc = 0;
+  constexpr int U = 8;
+  for (int64_t i0 = (int64_t)(blockIdx.x - p.first[a]) * 256 + threadIdx.x; i0 < n; i0 += U * step) {
+    uint64_t bits[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) bits[u] = (uint64_t)__double_as_longlong(x[min(i0 + u * step, n - 1)]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + u * step;
+      if (i < n) acc += mix64(bits[u] ^ mix64((uint64_t)i + 0x9e3779b97f4a7c15ull));
+    }
+  }
+  const uint64_t sum = hash_sum(acc, sm);
+  if (threadIdx.x == 0) p.partials[blockIdx.x] = sum;
+}
+__global__ __launch_bounds__(256) void hash_stage2(HashArgs p) {
+  __shared__ uint64_t sm[256];
+  const int a = blockIdx.x;
+  uint64_t acc = 0;
+  for (int i = p.first[a] + threadIdx.x; i < p.first[a + 1]; i += 256) acc += p.partials[i];
+  const uint64_t sum = hash_sum(acc, sm);
+  if (threadIdx.x == 0) p.out[a] = mix64(sum + mix64((uint64_t)p.n[a]));
 }
 
 inline int grid_for(int64_t n, int cap = 4096) {
@@ -435,9 +461,19 @@ void combine(int64_t n, int m, const double* Q, int64_t ldq, const double* y, do
   multi_axpy_kernel<<<grid_for(n), 256, 0, s>>>(n, m, Q, ldq, y, sign, x);
   PNK_CHECK_LAUNCH();
 }
-void hash64(int64_t n, const double* x, uint64_t* out, uint64_t* partials, hipStream_t s) {
-  hash_stage1<<<kReduceBlocks, 256, 0, s>>>(n, x, partials);
-  hash_stage2<<<1, 256, 0, s>>>(kReduceBlocks, partials, n, out);
+void hash_arrays(const double* const x[kHashArrays], const int64_t n[kHashArrays], uint64_t* out, uint64_t* partials,
+                 hipStream_t s) {
+  HashArgs p;
+  p.first[0] = 0;
+  for (int a = 0; a < kHashArrays; ++a) {
+    p.x[a] = x[a];
+    p.n[a] = n[a];
+    p.first[a + 1] = p.first[a] + (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n[a], 2048), kHashBlocks));
+  }
+  p.partials = partials;
+  p.out = out;
+  hash_stage1<<<p.first[kHashArrays], 256, 0, s>>>(p);
+  hash_stage2<<<kHashArrays, 256, 0, s>>>(p);
   PNK_CHECK_LAUNCH();
 }
 

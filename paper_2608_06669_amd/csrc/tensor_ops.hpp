@@ -45,7 +45,10 @@ void multi_axpy(int64_t n, int m, const double* Q, int64_t ldq, const double* h,
 void combine(int64_t n, int m, const double* Q, int64_t ldq, const double* y, double sign, double* x,
              hipStream_t s);
 
-// 64-bit content hash of n doubles (bit patterns), deterministic.
-void hash64(int64_t n, const double* x, uint64_t* out, uint64_t* partials, hipStream_t s);
+// 64-bit content hashes of kHashArrays arrays of n[a] >= 1 doubles (bit
+// patterns), deterministic; partials: kHashArrays * kHashBlocks words.
+constexpr int kHashArrays = 4, kHashBlocks = 1024;
+void hash_arrays(const double* const x[kHashArrays], const int64_t n[kHashArrays], uint64_t* out, uint64_t* partials,
+                 hipStream_t s);
 
 }  // namespace pnk
