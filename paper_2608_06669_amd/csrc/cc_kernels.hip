@@ -48,7 +48,7 @@ __global__ void extract_blocks_kernel(int naux, int o, int v, const double* L, c
     const double x = (P < naux) ? L[e] : h[r];
     if (p < o && q < o) Loo[(P * o + p) * o + q] = x;
     else if (p < o) Lov[(P * o + p) * v + (q - o)] = x;
-    else if (q < o) Lvo[(P * v + (p - o)) * o + q] = x;
+    else if (q < o) Lvo[(P * o + q) * v + (p - o)] = x;
     else Lvv[(P * v + (p - o)) * v + (q - o)] = x;
   }
 }
@@ -182,64 +182,215 @@ __global__ void ppl_pack_w_kernel(int v, int a0, int na, const double* __restric
   }
 }
 
-__global__ void ppl_pack_t_kernel(int o, int v, const double* __restrict__ t2, const int* __restrict__ pa,
-                                  const int* __restrict__ pb, const int* __restrict__ ma,
-                                  const int* __restrict__ mb, double* __restrict__ Tp, double* __restrict__ Tm) {
-  const int64_t P2 = (int64_t)v * (v + 1) / 2, P2m = (int64_t)v * (v - 1) / 2;
-  const int64_t O2 = (int64_t)o * (o + 1) / 2, O2m = (int64_t)o * (o - 1) / 2;
+// Pair (x <= y) number k of n, in upair order.
+__device__ inline void upair_inverse(int k, int n, int* x, int* y) {
+  int r = 0;
+  while (k >= n - r) {
+    k -= n - r;
+    ++r;
+  }
+  *x = r;
+  *y = r + k;
+}
+
+// Every layout of the doubles that the contractions read, from one pass over
+// t: a workgroup takes the 32 x 32 tiles (A, B) and (B, A), A <= B, of one
+// pair (i, j), so each element meets its exchange partner t_ij^ba in LDS and
+// all writes run along rows. HBM-bound: at o = 20, v = 180 (104 MB per
+// array; one read, four written without U, Uklca, Uail) 97 us, in place of a
+// pass per layout and the ladder's packing (ten launches, 0.46 ms).
+constexpr int kT = 32;
+
+__global__ __launch_bounds__(256) void amp_layouts_kernel(int o, int v, int tiles, AmpLayouts p) {
+  __shared__ double s1[kT][kT + 1], s2[kT][kT + 1];
+  int A, B;
+  upair_inverse(blockIdx.x, tiles, &A, &B);
+  const int ij = blockIdx.y, i = ij / o, j = ij % o;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int64_t vv = (int64_t)v * v;
-  const int64_t np = O2 * P2, nm = O2m * P2m;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < np + nm; e += (int64_t)gridDim.x * blockDim.x) {
-    const bool plus = e < np;
-    const int64_t f = plus ? e : e - np;
-    const int64_t width = plus ? P2 : P2m;
-    const int64_t ij = f / width, q = f % width;
-    // occupied pair (i <= j) from its index (opair order)
-    int i, j;
-    if (ij < O2m) {
-      i = 0;
-      while (i + 2 < o && spair(i + 1, i + 2, o) <= ij) ++i;
-      j = i + 1 + (int)(ij - spair(i, i + 1, o));
-    } else {
-      i = j = (int)(ij - O2m);
+  const double* __restrict__ t = p.t + ij * vv;
+  const bool same = A == B;
+#pragma unroll
+  for (int r = 0; r < kT; r += 8) {
+    const int a = A * kT + ty + r, b = B * kT + tx;
+    if (a < v && b < v) s1[ty + r][tx] = t[(int64_t)a * v + b];
+    const int c = B * kT + ty + r, d = A * kT + tx;
+    if (!same && c < v && d < v) s2[ty + r][tx] = t[(int64_t)c * v + d];
+  }
+  __syncthreads();
+  const double(*sx)[kT + 1] = same ? s1 : s2;
+  const int64_t P2 = (int64_t)v * (v + 1) / 2, P2m = (int64_t)v * (v - 1) / 2;
+  const int64_t pij = i <= j ? opair(i, j, o) : 0;
+  // x = t_ij^ab, y = t_ij^ba
+  auto emit = [&](int a, int b, double x, double y) {
+    const int64_t m = (((int64_t)i * v + a) * o + j) * v + b;
+    const double u = 2.0 * x - y;
+    p.Tia[m] = x;
+    p.Tsia[m] = y;
+    p.Uia[m] = u;
+    if (p.U) {
+      const int64_t q = ij * vv + (int64_t)a * v + b;
+      p.U[q] = u;
+      p.Uklca[q] = 2.0 * y - x;
+      p.Uail[(((int64_t)a * o + i) * o + j) * v + b] = u;
     }
-    const double* t = t2 + ((int64_t)i * o + j) * vv;
-    if (plus) {
-      const int c = pa[q], d = pb[q];
-      Tp[f] = (c == d) ? 0.5 * t[(int64_t)c * v + c] : 0.5 * (t[(int64_t)c * v + d] + t[(int64_t)d * v + c]);
-    } else {
-      const int c = ma[q], d = mb[q];
-      Tm[f] = 0.5 * (t[(int64_t)c * v + d] - t[(int64_t)d * v + c]);
+    if (i <= j && a <= b) {
+      p.Tp[pij * P2 + upair(a, b, v)] = a == b ? 0.5 * x : 0.5 * (x + y);
+      if (i < j && a < b) p.Tm[pij * P2m + spair(a, b, v)] = 0.5 * (x - y);
     }
+  };
+#pragma unroll
+  for (int r = 0; r < kT; r += 8) {
+    const int a = A * kT + ty + r, b = B * kT + tx;
+    if (a < v && b < v) emit(a, b, s1[ty + r][tx], sx[tx][ty + r]);
+  }
+  if (same) return;
+#pragma unroll
+  for (int r = 0; r < kT; r += 8) {
+    const int b = B * kT + ty + r, a = A * kT + tx;
+    if (a < v && b < v) emit(b, a, s2[ty + r][tx], s1[tx][ty + r]);
   }
 }
 
-__global__ void ppl_unpack_kernel(int o, int v, const double* __restrict__ Rp, const double* __restrict__ Rm,
-                                  double* __restrict__ R) {
-  const int64_t P2 = (int64_t)v * (v + 1) / 2, P2m = (int64_t)v * (v - 1) / 2;
+// The doubles residual from its parts,
+//   R_ij^ab += E[(i,a)][(j,b)] + P_ij^ab V_ij^ab + ladder_ij^ab,
+//   V_ij^ab = X[i][j][a][b] + T[(i,a)][(j,b)] + S[(j,a)][(i,b)],
+// the ladder unpacked from its symmetric and antisymmetric combinations (E
+// may be null). A workgroup takes the tiles (A, B), (B, A), A <= B, of (i, j)
+// and (j, i), i <= j: each part is read once, along rows, transposed
+// partners meet in LDS. HBM-bound: at o = 20, v = 180 126 us for five arrays
+// of 104 MB read and one written, in place of two permutations into X, one
+// into R, the unpacking and the pair sum (five launches, 0.40 ms).
+__global__ __launch_bounds__(256) void doubles_sum_kernel(int o, int v, int tiles, DoublesParts p) {
+  __shared__ double st[kT][kT + 1], sx[kT][kT + 1];
+  int A, B, i, j;
+  upair_inverse(blockIdx.x, tiles, &A, &B);
+  upair_inverse(blockIdx.y, o, &i, &j);
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int64_t vv = (int64_t)v * v;
-  const int64_t total = (int64_t)o * o * vv;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t ijx = e / vv;
-    const int ab = (int)(e % vv);
-    int i = (int)(ijx / o), j = (int)(ijx % o);
-    int a = ab / v, b = ab % v;
-    if (i > j) {  // X_ij^ab = X_ji^ba
-      const int t = i; i = j; j = t;
-      const int u = a; a = b; b = u;
+  const int64_t P2 = (int64_t)v * (v + 1) / 2, P2m = (int64_t)v * (v - 1) / 2;
+  const int64_t pij = opair(i, j, o);
+  const bool offd = i < j;  // the antisymmetric part has rows i < j only
+  auto ia = [&](int x, int a, int y, int b) { return (((int64_t)x * v + a) * o + y) * v + b; };
+  auto ij = [&](int x, int y, int a, int b) { return ((int64_t)x * o + y) * vv + (int64_t)a * v + b; };
+  auto V = [&](int x, int y, int a, int b) { return p.X[ij(x, y, a, b)] + p.T[ia(x, a, y, b)] + p.S[ia(y, a, x, b)]; };
+  // tiles (P, Q) of (i, j) and (Q, P) of (j, i)
+  auto half = [&](int P, int Q, bool first) {
+    double d[kT / 8], r1[kT / 8], r2[kT / 8];
+#pragma unroll
+    for (int q = 0; q < kT / 8; ++q) {
+      const int a = P * kT + ty + 8 * q, b = Q * kT + tx;
+      d[q] = r1[q] = 0.0;
+      if (a < v && b < v) {
+        d[q] = V(i, j, a, b);
+        r1[q] = p.R[ij(i, j, a, b)];
+        if (p.E) r1[q] += p.E[ia(i, a, j, b)];
+      }
+      const int c = Q * kT + ty + 8 * q, e = P * kT + tx;
+      r2[q] = 0.0;
+      if (c < v && e < v) {
+        st[ty + 8 * q][tx] = V(j, i, c, e);
+        r2[q] = p.R[ij(j, i, c, e)];
+        if (p.E) r2[q] += p.E[ia(j, c, i, e)];
+      }
     }
-    const int64_t ij = opair(i, j, o);
-    const bool offd = i < j;  // the antisymmetric part has rows i < j only
-    double x;
-    if (a <= b) {
-      x = Rp[ij * P2 + upair(a, b, v)];
-      if (a < b && offd) x += Rm[ij * P2m + spair(a, b, v)];
+    double x[kT / 8];  // the ladder
+    if (first) {
+#pragma unroll
+      for (int q = 0; q < kT / 8; ++q) {
+        const int a = P * kT + ty + 8 * q, b = Q * kT + tx;
+        double xs = 0.0, xa = 0.0;
+        if (a < v && b < v) {
+          const int lo = min(a, b), hi = max(a, b);
+          xs = p.Rp[pij * P2 + upair(lo, hi, v)];
+          if (offd && a != b) xa = p.Rm[pij * P2m + spair(lo, hi, v)];
+          if (a > b) xa = -xa;
+        }
+        x[q] = xs + xa;
+        sx[ty + 8 * q][tx] = xs - xa;
+      }
     } else {
-      x = Rp[ij * P2 + upair(b, a, v)];
-      if (offd) x -= Rm[ij * P2m + spair(b, a, v)];
+#pragma unroll
+      for (int q = 0; q < kT / 8; ++q) x[q] = sx[tx][ty + 8 * q];
     }
-    R[e] += x;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kT / 8; ++q) {
+      const int a = P * kT + ty + 8 * q, b = Q * kT + tx;
+      d[q] += st[tx][ty + 8 * q];
+      d[q] += x[q];
+      if (a < v && b < v) p.R[ij(i, j, a, b)] = r1[q] + d[q];
+    }
+    if (i == j && P == Q) return;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kT / 8; ++q) st[ty + 8 * q][tx] = d[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kT / 8; ++q) {
+      const int c = Q * kT + ty + 8 * q, e = P * kT + tx;
+      if (c < v && e < v) p.R[ij(j, i, c, e)] = r2[q] + st[tx][ty + 8 * q];
+    }
+  };
+  half(A, B, true);
+  if (i < j && A < B) {
+    __syncthreads();
+    half(B, A, false);
   }
+}
+
+// F = L[naux] + 2 sum_P D_P L[P] of the four dressed blocks, D_P = tr Loo[P],
+// or the tangent dL[naux] + 2 sum_P (dD_P L[P] + D_P dL[P]). A workgroup
+// takes 64 columns of one block, its four waves every fourth slice; the
+// traces of 256 slices at a time are formed by each workgroup for itself.
+// HBM-bound (one pass over the blocks, 192 MB at o = 20, v = 180, 600 slices:
+// 72 us), in place of a trace, four copies and four one-row products with
+// their reductions (thirteen launches, which at o = 4, v = 16 cost 60 us).
+constexpr int kSlices = 256;
+
+__global__ __launch_bounds__(256) void fock_sum_kernel(int naux, int o, FockSum p) {
+  __shared__ double D[kSlices], dD[kSlices], sm[4][64];
+  int blk = blockIdx.x, q = 0;
+  while (q < 3 && blk >= (p.n[q] + 63) / 64) blk -= (p.n[q++] + 63) / 64;
+  const int n = p.n[q], c = blk * 64 + (threadIdx.x & 63), w = threadIdx.x >> 6;
+  const int64_t oo = (int64_t)o * o;
+  const bool tangent = p.dLoo != nullptr, in = c < n;
+  const double* __restrict__ L = p.L[q] + min(c, n - 1);
+  const double* __restrict__ dL = p.dL[q] ? p.dL[q] + min(c, n - 1) : nullptr;
+  auto trace = [&](const double* x) {
+    double t = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < o; ++k) t += x[(int64_t)k * (o + 1)];
+    return t;
+  };
+  double acc = 0.0;
+  for (int P0 = 0; P0 < naux; P0 += kSlices) {
+    const int np = min(kSlices, naux - P0), t = threadIdx.x;
+    __syncthreads();
+    if (t < np) {
+      D[t] = trace(p.Loo + (P0 + t) * oo);
+      if (tangent) dD[t] = trace(p.dLoo + (P0 + t) * oo);
+      if (p.D && blockIdx.x == 0) p.D[P0 + t] = D[t];
+    }
+    __syncthreads();
+    if (tangent) {
+#pragma unroll 8
+      for (int s = w; s < np; s += 4) acc += dD[s] * L[(int64_t)(P0 + s) * n];
+      if (dL) {
+#pragma unroll 8
+        for (int s = w; s < np; s += 4) acc += D[s] * dL[(int64_t)(P0 + s) * n];
+      }
+    } else {
+#pragma unroll 8
+      for (int s = w; s < np; s += 4) acc += D[s] * L[(int64_t)(P0 + s) * n];
+    }
+  }
+  sm[w][threadIdx.x & 63] = acc;
+  __syncthreads();
+  if (w != 0 || !in) return;
+  acc = sm[0][threadIdx.x] + sm[1][threadIdx.x] + sm[2][threadIdx.x] + sm[3][threadIdx.x];
+  const double last = !tangent ? L[(int64_t)naux * n] : dL ? dL[(int64_t)naux * n] : 0.0;
+  p.F[q][c] = 2.0 * acc + last;
 }
 
 }  // namespace
@@ -251,15 +402,21 @@ void ppl_pack_w(int v, int a0, int na, const double* Wblk, const int* pair_a, co
                                                                           mpair_b, S, A);
   PNK_CHECK_LAUNCH();
 }
-void ppl_pack_t(int o, int v, const double* t2, const int* pair_a, const int* pair_b, const int* mpair_a,
-                const int* mpair_b, double* Tp, double* Tm, hipStream_t s) {
-  const int64_t n = (int64_t)o * (o + 1) / 2 * ((int64_t)v * v);
-  ppl_pack_t_kernel<<<grid_for(n, 16384), 256, 0, s>>>(o, v, t2, pair_a, pair_b, mpair_a, mpair_b, Tp, Tm);
+void amp_layouts(int o, int v, const AmpLayouts& p, hipStream_t s) {
+  const int64_t tiles = ceil_div(v, kT), g = tiles * (tiles + 1) / 2;
+  PNK_REQUIRE((int64_t)o * o <= 65535 && g < (1ll << 31), "amplitude layouts: extents too large");
+  amp_layouts_kernel<<<dim3((unsigned)g, (unsigned)(o * o)), 256, 0, s>>>(o, v, (int)tiles, p);
   PNK_CHECK_LAUNCH();
 }
-void ppl_unpack_add(int o, int v, const double* Rp, const double* Rm, double* R, hipStream_t s) {
-  const int64_t n = (int64_t)o * o * v * v;
-  ppl_unpack_kernel<<<grid_for(n, 16384), 256, 0, s>>>(o, v, Rp, Rm, R);
+void doubles_sum(int o, int v, const DoublesParts& p, hipStream_t s) {
+  const int64_t tiles = ceil_div(v, kT), g = tiles * (tiles + 1) / 2;
+  doubles_sum_kernel<<<dim3((unsigned)g, (unsigned)(o * (o + 1) / 2)), 256, 0, s>>>(o, v, (int)tiles, p);
+  PNK_CHECK_LAUNCH();
+}
+void fock_sum(int naux, int o, const FockSum& p, hipStream_t s) {
+  int64_t g = 0;
+  for (int q = 0; q < 4; ++q) g += ceil_div(p.n[q], 64);
+  fock_sum_kernel<<<(unsigned)g, 256, 0, s>>>(naux, o, p);
   PNK_CHECK_LAUNCH();
 }
 

@@ -13,7 +13,7 @@ void assemble_fock(int o, int v, const double* f_oo, const double* f_ov, const d
 // Lo[P][k][q] = L[P][k][q] for k < o (rows of the occupied orbitals)
 void extract_occ_rows(int naux, int o, int n, const double* L, double* Lo, hipStream_t s);
 // Blocks of the np = naux + 1 slices [L[0..naux-1]; h]: oo [np][o][o],
-// ov [np][o][v], vo [np][v][o], vv [np][v][v]
+// ov [np][o][v], vo transposed [np][o][v], vv [np][v][v]
 void extract_blocks(int naux, int o, int v, const double* L, const double* h, double* Loo, double* Lov,
                     double* Lvo, double* Lvv, hipStream_t s);
 // D[P] = sum_k X[P][k][k] for P < nslices, X of shape [.][o][o]
@@ -34,12 +34,38 @@ void jacobi_update(int o, int v, const double* f_oo, const double* f_vv, double 
 // rows whose a lies in [a0, a0 + na); Wblk[a - a0][b][c][d] = (ac|bd).
 void ppl_pack_w(int v, int a0, int na, const double* Wblk, const int* pair_a, const int* pair_b,
                 const int* mpair_a, const int* mpair_b, double* S, double* A, hipStream_t s);
-// Tp[ij][q] = (t_ij^cd + t_ij^dc)/2 (c < d) or t_ij^cc / 2 (c = d);
-// Tm[ij][q'] = (t_ij^cd - t_ij^dc)/2, for i <= j.
-void ppl_pack_t(int o, int v, const double* t2, const int* pair_a, const int* pair_b, const int* mpair_a,
-                const int* mpair_b, double* Tp, double* Tm, hipStream_t s);
-// R[i][j][a][b] += sum_cd (ac|bd) t_ij^cd rebuilt from Rp = Tp S, Rm = Tm A.
-void ppl_unpack_add(int o, int v, const double* Rp, const double* Rm, double* R, hipStream_t s);
+
+// Layouts of doubles t[i][j][a][b] (u = 2 t_ij^ab - t_ij^ba):
+struct AmpLayouts {
+  const double* t;
+  double *Tia, *Tsia, *Uia;  // [(i,a)][(j,b)]: t_ij^ab, t_ij^ba, u_ij^ab
+  // Tp[ij][q] = (t_ij^cd + t_ij^dc)/2 (c < d) or t_ij^cc / 2 (c = d), i <= j;
+  // Tm[ij][q'] = (t_ij^cd - t_ij^dc)/2, i < j
+  double *Tp, *Tm;
+  double *U, *Uklca, *Uail;  // (null: not wanted) [i][j][a][b]: u_ij^ab, u_ij^ba; [a][i][j][b]: u_ij^ab
+};
+void amp_layouts(int o, int v, const AmpLayouts& p, hipStream_t s);
+
+// R[i][j][a][b] += E[(i,a)][(j,b)] + V_ij^ab + V_ji^ba + sum_cd (ac|bd) t_ij^cd,
+// V_ij^ab = X[i][j][a][b] + T[(i,a)][(j,b)] + S[(j,a)][(i,b)], the ladder
+// rebuilt from Rp = Tp S, Rm = Tm A; E may be null.
+struct DoublesParts {
+  const double *X, *T, *S, *Rp, *Rm, *E;
+  double* R;
+};
+void doubles_sum(int o, int v, const DoublesParts& p, hipStream_t s);
+
+// F[q][c] = L[q][naux][c] + 2 sum_P D_P L[q][P][c], c < n[q], P < naux, D_P = tr
+// Loo[P] (also written to D unless null). With dLoo, the tangent instead,
+// dL[q][naux][c] + 2 sum_P (dD_P L[q][P][c] + D_P dL[q][P][c]); null dL[q]: zero.
+struct FockSum {
+  const double *Loo, *dLoo;
+  int n[4];
+  const double *L[4], *dL[4];
+  double* F[4];
+  double* D;
+};
+void fock_sum(int naux, int o, const FockSum& p, hipStream_t s);
 
 // y = x / *s_dev (the divisor stays on the device; y = 0 when it is 0)
 void scale_by_inverse(int64_t n, const double* x, const double* s_dev, double* y, hipStream_t s);

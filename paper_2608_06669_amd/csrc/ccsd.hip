@@ -175,7 +175,7 @@ void for_each_buffer(const Sizes& z, const EngineOptions& opt, F f, G g) {
   f(np * o * o); f(np * ov); f(np * ov); f(np * v * v);
   const int64_t p2 = z.p2, p2m = z.p2m, o2 = z.o2;
   f(p2 * p2); f(p2m * p2m); f(z.wna * v * v * v); g(4 * (2 * p2 + 2 * p2m));
-  f(o * v * v * v); f(n2); f(n2); f(n2); f(n2); f(n2);
+  f(o * v * v * v); f(n2); f(n2); f(n2); f(n2);
   if (opt.lowp_f32) {
     g(4 * p2 * pad_to(p2, 4)); g(4 * p2m * pad_to(p2m, 4));
     g(4 * o * v * v * v); g(4 * n2); g(4 * n2); g(4 * n2); g(4 * n2);
@@ -187,14 +187,14 @@ void for_each_buffer(const Sizes& z, const EngineOptions& opt, F f, G g) {
   g(cast_bytes(z, opt));
   // intermediates, value and tangent
   for (int rep = 0; rep < 2; ++rep) {
-    f(np * o * o); f(np * ov); f(np * v * v); f(naux); f(naux * o * o); f(naux * ov);
-    f(o * o); f(ov); f(ov); f(v * v);
-    for (int k = 0; k < 7; ++k) f(n2);  // U, Tail, Tsail, Uail, Ukdic, Uklca, Uiakc
-    f(n2); f(n2);                       // Tmp, X
+    f(np * o * o); f(np * ov); f(np * v * v); f(naux); f(naux * o * o);
+    f(o * o); f(ov); f(v * v);
+    for (int k = 0; k < 5; ++k) f(n2);  // Tia, Tsia, Uia, Tmp, X
     f(v * v); f(o * o); f(o * o * o * o); f(o * o * o * o); f(o * o * o * o); f(o * o * ov);
-    f(n2); f(n2);                       // J, Kp
-    f(naux * ov); f(naux * ov); f(naux * v * v); f(o * o * ov); f(o * o * ov);
+    f(n2); f(n2);                       // J, K
+    f(naux * ov); f(naux * ov); f(o * o * ov);
     f(o2 * p2); f(o2 * p2m); f(o2 * p2); f(o2 * p2m);  // Tp, Tm, Rp, Rm
+    if (opt.lowp_f32 || opt.lowp_bf16) { f(n2); f(n2); f(n2); f(o * o * ov); }  // U, Uklca, Uail, KilcT
   }
   f(reduce_partials_size(64));
   f(ov + n2);  // zeros
@@ -229,7 +229,7 @@ Engine::Engine(int o, int v, int naux, const EngineOptions& opt)
   pair_a_ = arena_.take<int>(z.p2); pair_b_ = arena_.take<int>(z.p2);
   mpair_a_ = arena_.take<int>(z.p2m); mpair_b_ = arena_.take<int>(z.p2m);
   Wov.v = take(O * V * V * V);
-  Ioovv.v = take(N2); Iovov.v = take(N2); Ix.v = take(N2); Ikldc.v = take(N2); Itil.v = take(N2);
+  Ioovv.v = take(N2); Iovov.v = take(N2); Ix.v = take(N2); Itil.v = take(N2);
   // the low-precision ladder tensors keep rows of a 16-byte multiple (the
   // pair counts v(v+1)/2, v(v-1)/2 need not be), for vector loads
   ld32_ = pad_to(z.p2, 4); ld32m_ = pad_to(z.p2m, 4);
@@ -253,18 +253,21 @@ Engine::Engine(int o, int v, int naux, const EngineOptions& opt)
   }
   cast_bytes_ = cast_bytes(z, opt);
   if (cast_bytes_) cast_ws_ = arena_.take<char>((size_t)cast_bytes_);
-  Ten* inter[] = {&Loo, &Lvo, &Lvv, &this->D, &LooT, &LvoT, &Foo, &Fov, &Fvo, &Fvv,
-                  &U, &Tail, &Tsail, &Uail, &Ukdic, &Uklca, &Uiakc, &Tmp, &X,
-                  &Gv, &Go, &Kilj, &Wkl, &Y, &Z, &J, &Kp, &Q, &QT, &LvvT, &Kilc, &KilcT,
-                  &Tp, &Tm, &Rp, &Rm};
-  const int64_t isz[] = {NP * O * O, NP * OV, NP * V * V, NA, NA * O * O, NA * OV, O * O, OV, OV, V * V,
-                         N2, N2, N2, N2, N2, N2, N2, N2, N2,
+  Ten* inter[] = {&Loo, &Lvo, &Lvv, &this->D, &LooT, &Foo, &Fov, &Fvv,
+                  &Tia, &Tsia, &Uia, &Tmp, &X,
+                  &Gv, &Go, &Kilj, &Wkl, &Y, &Z, &J, &K, &Q, &QT, &Kilc,
+                  &Tp, &Tm, &Rp, &Rm,
+                  &U, &Uklca, &Uail, &KilcT};
+  const int64_t isz[] = {NP * O * O, NP * OV, NP * V * V, NA, NA * O * O, O * O, OV, V * V,
+                         N2, N2, N2, N2, N2,
                          V * V, O * O, O * O * O * O, O * O * O * O, O * O * O * O, O * O * OV, N2, N2,
-                         NA * OV, NA * OV, NA * V * V, O * O * OV, O * O * OV,
-                         z.o2 * z.p2, z.o2 * z.p2m, z.o2 * z.p2, z.o2 * z.p2m};
+                         NA * OV, NA * OV, O * O * OV,
+                         z.o2 * z.p2, z.o2 * z.p2m, z.o2 * z.p2, z.o2 * z.p2m,
+                         N2, N2, N2, O * O * OV};
+  const size_t nlow = opt.lowp_f32 || opt.lowp_bf16 ? 0 : 4;  // the last four: FP32 / BF16 only
   static_assert(sizeof(inter) / sizeof(inter[0]) == sizeof(isz) / sizeof(isz[0]), "buffer table");
   for (int rep = 0; rep < 2; ++rep)
-    for (size_t k = 0; k < sizeof(isz) / sizeof(isz[0]); ++k) {
+    for (size_t k = 0; k + nlow < sizeof(isz) / sizeof(isz[0]); ++k) {
       if (rep == 0) inter[k]->v = take(isz[k]);
       else inter[k]->d = take(isz[k]);
       inter[k]->var = true;
@@ -372,22 +375,27 @@ void Engine::operand(const Ten& t, bool tangent, const void** p, Prec* prec) con
   *prec = Prec::F64;
 }
 
-// C = alpha A B + beta C, or its tangent dC = alpha (dA B + A dB) + beta dC
-void Engine::mm(const GemmDesc& d, const Ten& A, const Ten& B, const Ten& C) {
+// C = alpha A B + beta C, or its tangent dC = alpha (dA B + A dB) + beta dC;
+// with src, beta is 1 and takes src in place of C
+void Engine::mm(const GemmDesc& d, const Ten& A, const Ten& B, const Ten& C, const Ten* src, int64_t off) {
   const double f = 2.0 * d.M * d.N * d.K * (double)d.nb0 * d.nb1;
+  GemmDesc e = with_ws(d);
+  if (src) {
+    const bool there = mode_ == Mode::Value || src->var;  // (the tangent of a constant is zero)
+    e.beta = there ? 1.0 : 0.0;
+    e.Cin = there ? out(*src) + off : nullptr;
+  }
   if (mode_ == Mode::Value) {
     mm_flops_ += f;
-    gemm64(with_ws(d), A.v, B.v, C.v, s_);
+    gemm64(e, A.v, B.v, C.v, s_);
     return;
   }
-  if (!C.var) return;
   // the tangent of a product with one varying operand is one product, with
   // two varying operands two
   mm_flops_ += (A.var && B.var) ? 2.0 * f : f;
   PNK_REQUIRE(A.var || B.var, "internal: variable output of a constant product");
   const void *pa, *pb;
   Prec qa, qb;
-  GemmDesc e = with_ws(d);
   if (A.var && B.var) {
     // dA B + A dB as one launch when the operand precisions agree
     const void *pa2, *pb2;
@@ -409,65 +417,22 @@ void Engine::mm(const GemmDesc& d, const Ten& A, const Ten& B, const Ten& C) {
     first = false;
   }
   if (B.var) {
-    if (!first) e.beta = 1.0;
+    if (!first) {
+      e.beta = 1.0;
+      e.Cin = nullptr;
+    }
     operand(A, false, &pa, &qa);
     operand(B, true, &pb, &qb);
     gemm(e, pa, qa, pb, qb, C.d, Prec::F64, jprec_, s_);
   }
 }
 
-void Engine::perm(const Ten& in, const Ten& out, int d0, int d1, int d2, int d3, int p0, int p1, int p2, int p3,
-                  double alpha, double beta) {
+// (in, out and src depend on the amplitudes)
+void Engine::perm(const Ten& in, const Ten& to, int d0, int d1, int d2, int d3, int p0, int p1, int p2, int p3,
+                  double alpha, double beta, const Ten* src) {
   const int dims[4] = {d0, d1, d2, d3};
   const int pm[4] = {p0, p1, p2, p3};
-  if (mode_ == Mode::Value) {
-    permute4(in.v, out.v, dims, pm, alpha, beta, s_);
-    return;
-  }
-  if (!out.var) return;
-  if (in.var) permute4(in.d, out.d, dims, pm, alpha, beta, s_);
-  else if (beta == 0.0) fill((int64_t)d0 * d1 * d2 * d3, 0.0, out.d, s_);
-}
-
-void Engine::lin_copy(const Ten& in, int64_t in_off, const Ten& out, int64_t n) {
-  if (mode_ == Mode::Value) {
-    copy(n, in.v + in_off, out.v, s_);
-    return;
-  }
-  if (!out.var) return;
-  if (in.var) copy(n, in.d + in_off, out.d, s_);
-  else fill(n, 0.0, out.d, s_);
-}
-
-void Engine::lin_axpby(int64_t n, double a, const Ten& x, double b, const Ten& y) {
-  if (mode_ == Mode::Value) {
-    axpby(n, a, x.v, b, y.v, s_);
-    return;
-  }
-  if (!y.var) return;
-  if (x.var) axpby(n, a, x.d, b, y.d, s_);
-  else if (b == 0.0) fill(n, 0.0, y.d, s_);
-  else if (b != 1.0) axpby(n, 0.0, y.d, b, y.d, s_);
-}
-
-void Engine::lin_trace(const Ten& in, int nslices, const Ten& out) {
-  if (mode_ == Mode::Value) trace_slices(nslices, o_, in.v, out.v, s_);
-  else trace_slices(nslices, o_, in.d, out.d, s_);
-}
-
-void Engine::lin_pairsym(const Ten& Xs, const Ten& R) {
-  if (mode_ == Mode::Value) pair_symmetrize_add(o_, v_, Xs.v, 1.0, R.v, s_);
-  else pair_symmetrize_add(o_, v_, Xs.d, 1.0, R.d, s_);
-}
-
-void Engine::lin_ppl_pack(const Ten& t2, const Ten& tp, const Ten& tm) {
-  if (mode_ == Mode::Value) ppl_pack_t(o_, v_, t2.v, pair_a_, pair_b_, mpair_a_, mpair_b_, tp.v, tm.v, s_);
-  else ppl_pack_t(o_, v_, t2.d, pair_a_, pair_b_, mpair_a_, mpair_b_, tp.d, tm.d, s_);
-}
-
-void Engine::lin_ppl_unpack(const Ten& rp, const Ten& rm, const Ten& R) {
-  if (mode_ == Mode::Value) ppl_unpack_add(o_, v_, rp.v, rm.v, R.v, s_);
-  else ppl_unpack_add(o_, v_, rp.d, rm.d, R.d, s_);
+  permute4(out(in), out(to), dims, pm, alpha, beta, s_, src ? out(*src) : nullptr);
 }
 
 // ------------------------------------------------------------ prepare ---
@@ -593,22 +558,22 @@ void Engine::prepare(const ProblemView& p, hipStream_t s, bool with_eigen) {
     permute4(Iovov.v, Ix.v, dims, pm, 1.0, 0.0, s);
     const int dims2[4] = {o, o, v, v};
     const int pm2[4] = {0, 1, 3, 2};
-    permute4(Ioovv.v, Ikldc.v, dims2, pm2, 1.0, 0.0, s);
-    permute4(Ioovv.v, Itil.v, dims2, pm2, -1.0, 0.0, s);
-    axpby(n2_, 2.0, Ioovv.v, 1.0, Itil.v, s);
+    permute4(Ioovv.v, Itil.v, dims2, pm2, -1.0, 2.0, s, Ioovv.v);
+    if (Ikldc.lp32 || Ikldc.lp16) {  // (kc|ld) as [k][l][d][c], staged in Tmp
+      permute4(Ioovv.v, Tmp.v, dims2, pm2, 1.0, 0.0, s);
+      if (Ikldc.lp32) cast_f64_to_f32(n2_, Tmp.v, (float*)Ikldc.lp32, s);
+      if (Ikldc.lp16) cast_f64_to_bf16(n2_, Tmp.v, (uint16_t*)Ikldc.lp16, s);
+    }
   }
   // the ladder tensors with padded rows, the others flat
   if (S.lp32) cast_f64_to_f32_rows(p2_, p2_, ld32_, S.v, (float*)S.lp32, s);
   if (S.lp16) cast_f64_to_bf16_rows(p2_, p2_, ld16_, S.v, (uint16_t*)S.lp16, s);
   if (Am.lp32) cast_f64_to_f32_rows(p2m_, p2m_, ld32m_, Am.v, (float*)Am.lp32, s);
   if (Am.lp16) cast_f64_to_bf16_rows(p2m_, p2m_, ld16m_, Am.v, (uint16_t*)Am.lp16, s);
-  Ten* lows[] = {&Wov, &Ioovv, &Iovov, &Ix, &Ikldc};
-  const int64_t lsz[] = {(int64_t)o * v * vv, n2_, n2_, n2_, n2_};
-  for (int k = 0; k < 5; ++k) {
-    if (lows[k]->lp32) cast_f64_to_f32(lsz[k], lows[k]->v, (float*)lows[k]->lp32, s);
-    if (lows[k]->lp16 && lows[k] != &Iovov && lows[k] != &Ix && lows[k] != &Wov)
-      cast_f64_to_bf16(lsz[k], lows[k]->v, (uint16_t*)lows[k]->lp16, s);
-  }
+  if (Wov.lp32) cast_f64_to_f32((int64_t)o * v * vv, Wov.v, (float*)Wov.lp32, s);
+  for (Ten* t : {&Ioovv, &Iovov, &Ix})
+    if (t->lp32) cast_f64_to_f32(n2_, t->v, (float*)t->lp32, s);
+  if (Ioovv.lp16) cast_f64_to_bf16(n2_, Ioovv.v, (uint16_t*)Ioovv.lp16, s);
   if (Wov.lp16) cast_f64_to_bf16_rows(ov, (int64_t)v * v, ldw16_, Wov.v, (uint16_t*)Wov.lp16, s);
   if (Iovov.lp16) {
     cast_f64_to_bf16_rows(ov, ov, ldov16_, Iovov.v, (uint16_t*)Iovov.lp16, s);
@@ -633,51 +598,39 @@ void Engine::prepare(const ProblemView& p, hipStream_t s, bool with_eigen) {
 void Engine::run(Mode m) {
   mode_ = m;
   const int o = o_, v = v_, naux = naux_, np = np_;
-  const int64_t O = o, V = v, ov = ov_, vv = V * V, oo = O * O, n2 = n2_;
+  const int64_t O = o, V = v, ov = ov_, vv = V * V, oo = O * O;
   const int OV = (int)ov, OO = (int)oo, VV = (int)vv;
 
-  // ---- T1 dressing: L~ = (1 - tau) L (1 + tau), slice naux is h ----
-  lin_copy(Loo0, 0, Loo, np * oo);
-  mm(gd(np * o, o, v, v, 1, 1, v, o, 1, 1.0, 1.0), Lov0, T1, Loo);            // + L_kc t_i^c
-  lin_copy(Lvo0, 0, Lvo, np * ov);
-  mm(gd(np * v, o, v, v, 1, 1, v, o, 1, 1.0, 1.0), Lvv0, T1, Lvo);            // + L_ab t_i^b
-  mm(batch0(gd(v, o, o, 1, v, o, 1, o, 1, -1.0, 1.0), np, 0, oo, ov), T1, Loo, Lvo);  // - t_k^a L~_ki
-  lin_copy(Lvv0, 0, Lvv, np * vv);
-  mm(batch0(gd(v, v, o, 1, v, v, 1, v, 1, -1.0, 1.0), np, 0, ov, vv), T1, Lov0, Lvv); // - t_k^a L_kc
+  const bool lowp = this->lowp();  // FP32 / BF16: the same sums, in the order the layouts below give
+  const bool lowp_engine = opt_.lowp_f32 || opt_.lowp_bf16;
 
-  // ---- dressed Fock F~ = h~ + sum_P [2 L~ D - L~_{:,o} L~_{o,:}] ----
-  lin_trace(Loo, naux, D);
+  // ---- T1 dressing: L~ = (1 - tau) L (1 + tau), slice naux is h ----
+  mm(gd(np * o, o, v, v, 1, 1, v, o, 1, 1.0), Lov0, T1, Loo, &Loo0);                            // + L_kc t_i^c
+  mm(batch0(gd(o, v, v, v, 1, 1, v, v, 1), np, 0, vv, ov), T1, Lvv0, Lvo, &Lvo0);               // + L_ab t_i^b
+  mm(batch0(gd(v, o, o, 1, v, o, 1, 1, v, -1.0, 1.0), np, 0, oo, ov), T1, Loo, Lvo);            // - t_k^a L~_ki
+  mm(batch0(gd(v, v, o, 1, v, v, 1, v, 1, -1.0), np, ov, 0, vv), Lov0, T1, Lvv, &Lvv0);         // - L_kc t_k^a
+
+  // ---- dressed Fock F~ = h~ + sum_P [2 L~ D - L~_{:,o} L~_{o,:}] (F~_ai in R1) ----
   perm(Loo, LooT, 1, naux, o, o, 0, 2, 1, 3, 1.0, 0.0);
-  perm(Lvo, LvoT, 1, naux, v, o, 0, 2, 1, 3, 1.0, 0.0);
-  lin_copy(Loo, naux * oo, Foo, oo);
-  mm(gd(1, OO, naux, 0, 1, oo, 1, 0, 1, 2.0, 1.0), D, Loo, Foo);
+  dressed_fock_sums();
   mm(gd(o, o, naux * o, naux * O, 1, o, 1, o, 1, -1.0, 1.0), LooT, Loo, Foo);
-  lin_copy(Lov0, naux * ov, Fov, ov);
-  mm(gd(1, OV, naux, 0, 1, ov, 1, 0, 1, 2.0, 1.0), D, Lov0, Fov);
   mm(gd(o, v, naux * o, naux * O, 1, v, 1, v, 1, -1.0, 1.0), LooT, Lov0, Fov);
-  lin_copy(Lvo, naux * ov, Fvo, ov);
-  mm(gd(1, OV, naux, 0, 1, ov, 1, 0, 1, 2.0, 1.0), D, Lvo, Fvo);
-  mm(gd(v, o, naux * o, naux * O, 1, o, 1, o, 1, -1.0, 1.0), LvoT, Loo, Fvo);
-  lin_copy(Lvv, naux * vv, Fvv, vv);
-  mm(gd(1, VV, naux, 0, 1, vv, 1, 0, 1, 2.0, 1.0), D, Lvv, Fvv);
-  mm(gd(v, v, naux * o, naux * O, 1, v, 1, v, 1, -1.0, 1.0), LvoT, Lov0, Fvv);
+  mm(gd(v, o, naux * o, 1, v, o, 1, 1, v, -1.0, 1.0), Lvo, Loo, R1);
+  mm(gd(v, v, naux * o, 1, v, v, 1, v, 1, -1.0, 1.0), Lov0, Lvo, Fvv);                          // [c][a]
 
   // ---- amplitude layouts ----
-  perm(T2, U, o, o, v, v, 0, 1, 3, 2, -1.0, 0.0);
-  lin_axpby(n2, 2.0, T2, 1.0, U);                                  // u = 2t - t_swap
-  perm(T2, Tail, o, o, v, v, 2, 0, 1, 3, 1.0, 0.0);                // [a][i][l][d] = t_il^ad
-  perm(T2, Tsail, o, o, v, v, 3, 0, 1, 2, 1.0, 0.0);               // [a][i][l][d] = t_il^da
-  perm(U, Uail, o, o, v, v, 2, 0, 1, 3, 1.0, 0.0);                 // [a][i][l][d] = u_il^ad
-  perm(U, Ukdic, o, o, v, v, 1, 3, 0, 2, 1.0, 0.0);                // [k][d][i][c] = u_ik^cd
-  perm(U, Uklca, o, o, v, v, 0, 1, 3, 2, 1.0, 0.0);                // [k][l][c][a] = u_kl^ac
-  perm(U, Uiakc, o, o, v, v, 0, 2, 1, 3, 1.0, 0.0);                // [i][a][k][c] = u_ik^ac
+  {
+    AmpLayouts p{};
+    p.t = out(T2);
+    p.Tia = out(Tia); p.Tsia = out(Tsia); p.Uia = out(Uia);
+    p.Tp = out(Tp); p.Tm = out(Tm);
+    // (an FP64 tangent has no use for the last three)
+    if (lowp_engine && (lowp || mode_ == Mode::Value)) { p.U = out(U); p.Uklca = out(Uklca); p.Uail = out(Uail); }
+    amp_layouts(o, v, p, s_);
+  }
 
-  // ---- r2 = (ai|bj)~ ----
-  mm(gd(OV, OV, naux, 1, ov, ov, 1, ov, 1), Lvo, Lvo, Tmp);        // [(a,i)][(b,j)]
-  perm(Tmp, R2, v, o, v, o, 1, 3, 0, 2, 1.0, 0.0);
   // ---- particle-particle ladder, symmetry-adapted: for i <= j and the
   // (anti)symmetric combinations of c,d, R+ = T+ S, R- = T- A ----
-  lin_ppl_pack(T2, Tp, Tm);
   {
     // S and A are symmetric matrices: read them along the contiguous index
     // the compute type stages best (n for FP64/FP32, k for BF16)
@@ -701,20 +654,23 @@ void Engine::run(Mode m) {
     }
     if (timers_) timers_->end(kTimerPPL, s_);
   }
-  lin_ppl_unpack(Rp, Rm, R2);
   // ---- hole-hole ladder ----
-  mm(gd(OO, OO, naux, 1, oo, oo, 1, oo, 1), Loo, Loo, Kilj);       // [(k,i)][(l,j)]
-  perm(Kilj, Wkl, o, o, o, o, 0, 2, 1, 3, 1.0, 0.0);               // [(k,l)][(i,j)]
   mm(gd(OO, OO, VV, vv, 1, 1, vv, oo, 1), Ioovv, T2, Y);           // Y[(k,l)][(i,j)]
-  lin_axpby(oo * oo, 1.0, Y, 1.0, Wkl);
-  mm(gd(OO, VV, OO, 1, oo, vv, 1, vv, 1, 1.0, 1.0), Wkl, T2, R2);
+  mm(gd(OO, OO, naux, 1, oo, oo, 1, oo, 1), Loo, Loo, Kilj);       // [(k,i)][(l,j)]
+  perm(Kilj, Wkl, o, o, o, o, 0, 2, 1, 3, 1.0, 1.0, &Y);           // [(k,l)][(i,j)]
+  mm(gd(OO, VV, OO, 1, oo, vv, 1, vv, 1), Wkl, T2, R2);
 
-  // ---- Fock-type intermediates ----
-  lin_copy(Fvv, 0, Gv, vv);
-  mm(gd(v, v, (int)(oo * v), oo * V, 1, v, 1, v, 1, -1.0, 1.0), Uail, Ikldc, Gv);
-  lin_copy(Foo, 0, Go, oo);
-  mm(gd(o, o, (int)(O * vv), O * vv, 1, 1, O * vv, o, 1, 1.0, 1.0), Ioovv, U, Go);
-  mm(gd((int)(oo * v), v, v, v, 1, 1, v, v, 1), T2, Gv, X);        // X = sum_c Gv_bc t_ij^ac
+  // ---- Fock-type intermediates, Gv as [c][b] ----
+  if (lowp) {
+    mm(gd(v, v, (int)(oo * v), 1, v, 1, oo * V, v, 1, -1.0), Ikldc, Uail, Gv, &Fvv);
+    mm(gd(o, o, (int)(O * vv), O * vv, 1, 1, O * vv, o, 1), Ioovv, U, Go, &Foo);
+  } else {
+    // u is symmetric in (k,b), (l,d): the sums over (l,d,k) and (c,l,d) run
+    // along the rows of the ring's operands
+    mm(gd(v, v, (int)(oo * v), 1, v, v, 1, v, 1, -1.0), Iovov, Uia, Gv, &Fvv);
+    mm(gd(o, o, (int)(O * vv), O * vv, 1, 1, O * vv, o, 1), Iovov, Uia, Go, &Foo);
+  }
+  mm(gd((int)(oo * v), v, v, v, 1, v, 1, v, 1), T2, Gv, X);        // X = sum_c Gv_bc t_ij^ac
   mm(batch0(gd(o, VV, o, 1, o, vv, 1, vv, 1, -1.0, 1.0), o, 0, O * vv, O * vv), Go, T2, X);
 
   // ---- T1 part of the dressed ladder ----
@@ -728,7 +684,7 @@ void Engine::run(Mode m) {
   mm(batch0(gd(OO, v, o, 1, oo, v, 1, ov, 1, -0.5, 1.0), o, O * oo, 0, v), Y, T1, Z);
   mm(batch0(gd(v, v, o, 1, v, v, 1, v, 1, -1.0, 1.0), OO, 0, ov, vv), T1, Z, X);
 
-  // ---- ring terms ----
+  // ---- ring terms, rows and columns (i,a) ----
   mm(gd(OV, OV, naux, 1, ov, ov, 1, ov, 1), Lvo, Lov0, J);         // (ai|kc)~
   // (BF16 tangents read the ring integrals along k: Iovov is symmetric, and
   // the BF16 copy of Ix holds its transpose)
@@ -738,30 +694,74 @@ void Engine::run(Mode m) {
     if (kc16) g.b_kzero = ldov16_;
     return g;
   };
-  mm(ring(0.5), Uail, Iovov, J);
-  mm(ring(-0.5), Tail, Ix, J);
-  mm(gd(OO, VV, naux, 1, oo, vv, 1, vv, 1), Loo, Lvv, Tmp);        // (ki|ac)~ as [(k,i)][(a,c)]
-  perm(Tmp, Kp, o, o, v, v, 2, 1, 0, 3, 1.0, 0.0);                 // K'[(a,i)][(k,c)]
-  mm(ring(-0.5), Tsail, Ix, Kp);
-  mm(gd(OV, OV, OV, ov, 1, 1, ov, ov, 1), J, Uail, Tmp);           // J u_jk^bc
-  mm(gd(OV, OV, OV, ov, 1, 1, ov, ov, 1, -1.0, 1.0), Kp, Tail, Tmp);  // - K t_kj^cb
-  perm(Tmp, X, v, o, v, o, 1, 3, 0, 2, 1.0, 1.0);
-  mm(gd(OV, OV, OV, ov, 1, 1, ov, ov, 1), Kp, Tsail, Tmp);         // K_ki,bc t_kj^ac as [(b,i)][(a,j)]
-  perm(Tmp, X, v, o, v, o, 1, 3, 2, 0, -1.0, 1.0);
+  mm(ring(0.5), Uia, Iovov, J);
+  mm(ring(-0.5), Tia, Ix, J);
+  mm(gd(OO, VV, naux, 1, oo, vv, 1, vv, 1), Loo, Lvv, Tmp);        // (ki|ac)~ as [(k,i)][(c,a)]
+  perm(Tmp, K, o, o, v, v, 1, 3, 0, 2, 1.0, 0.0);                  // [(i,a)][(k,c)]
+  mm(ring(-0.5), Tsia, Ix, K);
+  // (ai|bj)~: pair-symmetric, so half of it joins the sum that P_ij^ab
+  // doubles; in FP32 / BF16 (i,a),(j,b) and (j,b),(i,a) may differ by a
+  // rounding, and it stays apart, in the tangent of U, read above only
+  const Ten* E = lowp ? &U : nullptr;
+  mm(gd(OV, OV, naux, 1, ov, ov, 1, ov, 1, lowp ? 1.0 : 0.5), Lvo, Lvo, lowp ? U : Tmp);
+  GemmDesc gk = gd(OV, OV, OV, ov, 1, 1, ov, ov, 1, 1.0, lowp ? 0.0 : 1.0);
+  mm(gk, J, Uia, Tmp);                                             // J u_jk^bc
+  gk.alpha = -1.0;
+  gk.beta = 1.0;
+  mm(gk, K, Tia, Tmp);                                             // - K t_kj^cb
+  // - K_ki,bc t_kj^ac as [(i,b)][(j,a)], into J's tangent (free: a value
+  // pass has none yet, a tangent has just read it)
+  Ten KT = J;
+  KT.v = KT.d;
+  gk.beta = 0.0;
+  mm(gk, K, Tsia, KT);
 
-  // ---- r2 += P_ij^ab X ----
-  lin_pairsym(X, R2);
+  // ---- r2 ----
+  {
+    DoublesParts p{};
+    p.X = out(X); p.T = out(Tmp); p.S = out(KT); p.Rp = out(Rp); p.Rm = out(Rm);
+    p.E = E ? out(*E) : nullptr;
+    p.R = out(R2);
+    doubles_sum(o, v, p, s_);
+  }
 
   // ---- singles ----
-  perm(Fvo, R1, 1, 1, v, o, 0, 1, 3, 2, 1.0, 0.0);                 // F~_ai
-  mm(gd(naux, OV, OV, ov, 1, ov, 1, ov, 1), Lov0, Ukdic, Q);       // Q[P][(i,c)]
+  mm(gd(naux, OV, OV, ov, 1, ov, 1, ov, 1), Lov0, Uia, Q);         // Q[P][(i,c)]
   perm(Q, QT, 1, naux, o, v, 0, 2, 1, 3, 1.0, 0.0);
-  perm(Lvv, LvvT, 1, naux, v, v, 0, 1, 3, 2, 1.0, 0.0);
-  mm(gd(o, v, naux * v, naux * V, 1, v, 1, v, 1, 1.0, 1.0), QT, LvvT, R1);
-  mm(gd(OO, OV, naux, 1, oo, ov, 1, ov, 1), Loo, Lov0, Kilc);      // (ki|lc)~ as [(k,i)][(l,c)]
-  perm(Kilc, KilcT, o, o, o, v, 1, 0, 2, 3, 1.0, 0.0);
-  mm(gd(o, v, (int)(oo * v), oo * V, 1, v, 1, v, 1, -1.0, 1.0), KilcT, Uklca, R1);
-  mm(gd(OV, 1, OV, ov, 1, 1, 1, 1, 1, 1.0, 1.0), Uiakc, Fov, R1);
+  mm(gd(o, v, naux * v, naux * V, 1, v, 1, v, 1, 1.0, 1.0), QT, Lvv, R1);
+  mm(gd(OV, OO, naux, 1, ov, oo, 1, oo, 1), Lov0, Loo, Kilc);      // (ki|lc)~ as [(l,c)][(k,i)]
+  if (lowp_engine && (lowp || mode_ == Mode::Value)) perm(Kilc, KilcT, o, v, o, o, 3, 2, 0, 1, 1.0, 0.0);
+  if (lowp)  // sums over (k,l,c); over (l,c,k) in FP64, u symmetric as above
+    mm(gd(o, v, (int)(oo * v), oo * V, 1, v, 1, v, 1, -1.0, 1.0), KilcT, Uklca, R1);
+  else
+    mm(gd(o, v, (int)(oo * v), 1, o, v, 1, v, 1, -1.0, 1.0), Kilc, Uia, R1);
+  mm(gd(OV, 1, OV, ov, 1, 1, 1, 1, 1, 1.0, 1.0), Uia, Fov, R1);
+}
+
+// L~[naux] + 2 sum_P D_P L~[P] into Foo, Fov, R1 (F~_ai) and Fvv
+void Engine::dressed_fock_sums() {
+  const int naux = naux_, OV = (int)ov_;
+  const Ten* L[4] = {&Loo, &Lov0, &Lvo, &Lvv};
+  const Ten* F[4] = {&Foo, &Fov, &R1, &Fvv};
+  const int n[4] = {o_ * o_, OV, OV, v_ * v_};
+  if (lowp()) {
+    trace_slices(naux, o_, Loo.d, D.d, s_);
+    for (int q = 0; q < 4; ++q)
+      mm(gd(1, n[q], naux, 0, 1, n[q], 1, 0, 1, 2.0), D, *L[q], *F[q], L[q], (int64_t)naux * n[q]);
+    return;
+  }
+  FockSum p{};
+  p.Loo = Loo.v;
+  p.dLoo = mode_ == Mode::Tangent ? Loo.d : nullptr;
+  for (int q = 0; q < 4; ++q) {
+    p.n[q] = n[q];
+    p.L[q] = L[q]->v;
+    p.dL[q] = L[q]->d;
+    p.F[q] = out(*F[q]);
+    mm_flops_ += 2.0 * naux * n[q] * (p.dLoo && p.dL[q] ? 2.0 : 1.0);  // as one-row products
+  }
+  p.D = mode_ == Mode::Value ? D.v : nullptr;
+  fock_sum(naux, o_, p, s_);
 }
 
 void Engine::residual(const double* t1, const double* t2, double* r1, double* r2, hipStream_t s) {
@@ -778,6 +778,8 @@ void Engine::residual(const double* t1, const double* t2, double* r1, double* r2
 
 void Engine::jvp(const double* x1, const double* x2, double* y1, double* y2, Prec prec, hipStream_t s) {
   PNK_REQUIRE(T1.v && T2.v, "jvp before any residual evaluation");
+  PNK_REQUIRE(prec == Prec::F64 || (prec == Prec::F32 ? opt_.lowp_f32 : opt_.lowp_bf16),
+              "internal: jvp in a precision the engine has no copies for");
   s_ = s;
   jprec_ = prec;
   if (timers_) timers_->begin(kTimerJvp, s);

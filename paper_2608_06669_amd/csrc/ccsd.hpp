@@ -5,8 +5,9 @@
 // singles amplitudes are folded into the DF factors, L~ = (1 - tau) L
 // (1 + tau), after which the doubles keep the CCD form of the paper's
 // working equations (Appendix A, MO representation), built from dressed
-// quantities. Every contraction is a strided matrix-core product; index
-// permutations between them are bandwidth-bound LDS-tiled transposes.
+// quantities. Every contraction is a strided matrix-core product; one
+// bandwidth-bound pass writes the layouts of the doubles they read, another
+// gathers their results.
 //
 // The Jacobian-vector product is the exact directional derivative of the
 // same sequence of operations (forward-mode tangents; the analytic product
@@ -146,15 +147,14 @@ class Engine {
   enum class Mode { Value, Tangent };
 
   void run(Mode m);
-  void mm(const GemmDesc& d, const Ten& A, const Ten& B, const Ten& C);
+  // products in FP32 / BF16, which keep their order of accumulation
+  bool lowp() const { return mode_ == Mode::Tangent && jprec_ != Prec::F64; }
+  double* out(const Ten& t) const { return mode_ == Mode::Value ? t.v : t.d; }
+  // C = alpha A B + beta C, or (beta 1) alpha A B + src[off..]
+  void mm(const GemmDesc& d, const Ten& A, const Ten& B, const Ten& C, const Ten* src = nullptr, int64_t off = 0);
   void perm(const Ten& in, const Ten& out, int d0, int d1, int d2, int d3, int p0, int p1, int p2, int p3,
-            double alpha, double beta);
-  void lin_copy(const Ten& in, int64_t in_off, const Ten& out, int64_t n);
-  void lin_axpby(int64_t n, double a, const Ten& x, double b, const Ten& y);
-  void lin_trace(const Ten& in, int nslices, const Ten& out);
-  void lin_pairsym(const Ten& X, const Ten& R);
-  void lin_ppl_pack(const Ten& t2, const Ten& Tp, const Ten& Tm);
-  void lin_ppl_unpack(const Ten& Rp, const Ten& Rm, const Ten& R);
+            double alpha, double beta, const Ten* src = nullptr);
+  void dressed_fock_sums();
   void operand(const Ten& t, bool tangent, const void** p, Prec* prec) const;
 
   int o_, v_, naux_, np_;
@@ -186,9 +186,12 @@ class Engine {
   // amplitudes and outputs
   Ten T1, T2, R1, R2;
   // intermediates
-  Ten Loo, Lvo, Lvv, D, LooT, LvoT, Foo, Fov, Fvo, Fvv;
-  Ten U, Tail, Tsail, Uail, Ukdic, Uklca, Uiakc;
-  Ten Tmp, X, Gv, Go, Kilj, Wkl, Y, Z, J, Kp, Q, QT, LvvT, Kilc, KilcT;
+  // (dressed vo blocks as [P][i][a], vv ones as [P][c][a] = (ac|, so Fvv and
+  // Gv are transposed too)
+  Ten Loo, Lvo, Lvv, D, LooT, Foo, Fov, Fvv;
+  Ten Tia, Tsia, Uia;
+  Ten U, Uklca, Uail, KilcT;  // for FP32 / BF16 products only
+  Ten Tmp, X, Gv, Go, Kilj, Wkl, Y, Z, J, K, Q, QT, Kilc;
   Ten Tp, Tm, Rp, Rm;
   double* partials_;
   double* zeros_;  // zero t-vector for the residual at t = 0

@@ -62,6 +62,7 @@ struct KArgs {
   const void* A2;  // optional second product A2 B2 (same strides as A, B)
   const void* B2;
   void* C;
+  const void* Cin;  // what beta multiplies
   int64_t c_m, c_n, c_b0, c_b1;
   double alpha, beta;
 };
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(KArgs p) {
   const bool dual = p.A2 != nullptr;
   const TA* __restrict__ Ag2 = dual ? (const TA*)p.A2 + b0 * p.a_b0 + b1 * p.a_b1 : Ag;
   const TB* __restrict__ Bg2 = dual ? (const TB*)p.B2 + b0 * p.b_b0 + b1 * p.b_b1 : Bg;
-  TC* __restrict__ Cg = (TC*)p.C + b0 * p.c_b0 + b1 * p.c_b1;
+  const int64_t coff = b0 * p.c_b0 + b1 * p.c_b1;
 
   Acc acc[TMI][TNI];
 #pragma unroll
@@ -225,10 +226,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(KArgs p) {
           const int64_t b = (int64_t)b1 * p.nb0 + b0;
           p.ws[(((int64_t)split * p.nbtot + b) * p.M + gm) * p.N + gn] = acc_get(acc[i][j], r);
         } else {
-          TC* c = Cg + gm * p.c_m + gn * p.c_n;
+          const int64_t at = coff + gm * p.c_m + gn * p.c_n;
           double v = alpha * acc_get(acc[i][j], r);
-          if (beta != 0.0) v += beta * load_c<TC>(c);
-          *c = from_acc<TC>(v);
+          if (beta != 0.0) v += beta * load_c<TC>((const TC*)p.Cin + at);
+          ((TC*)p.C)[at] = from_acc<TC>(v);
         }
       }
 }
@@ -253,18 +254,16 @@ __global__ __launch_bounds__(256) void splitk_reduce(KArgs p) {
       acc += x3;
     }
     for (; s < p.splits; ++s) acc += p.ws[(int64_t)s * total + e];
-    TC* c;
-    if (flat) {
-      c = (TC*)p.C + e;
-    } else {
+    int64_t at = e;
+    if (!flat) {
       const int64_t b = e / MN;
       const int m = (int)((e % MN) / p.N), n = (int)(e % p.N);
       const int b0 = (int)(b % p.nb0), b1 = (int)(b / p.nb0);
-      c = (TC*)p.C + b0 * p.c_b0 + b1 * p.c_b1 + m * p.c_m + n * p.c_n;
+      at = b0 * p.c_b0 + b1 * p.c_b1 + m * p.c_m + n * p.c_n;
     }
     double v = p.alpha * acc;
-    if (p.beta != 0.0) v += p.beta * load_c<TC>(c);
-    *c = from_acc<TC>(v);
+    if (p.beta != 0.0) v += p.beta * load_c<TC>((const TC*)p.Cin + at);
+    ((TC*)p.C)[at] = from_acc<TC>(v);
   }
 }
 
@@ -290,10 +289,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_wide(KArgs p) {
       const int64_t b = e / MN;
       const int m = (int)((e % MN) / p.N), n = (int)(e % p.N);
       const int b0 = (int)(b % p.nb0), b1 = (int)(b / p.nb0);
-      TC* c = (TC*)p.C + b0 * p.c_b0 + b1 * p.c_b1 + m * p.c_m + n * p.c_n;
+      const int64_t at = b0 * p.c_b0 + b1 * p.c_b1 + m * p.c_m + n * p.c_n;
       double v = p.alpha * sum;
-      if (p.beta != 0.0) v += p.beta * load_c<TC>(c);
-      *c = from_acc<TC>(v);
+      if (p.beta != 0.0) v += p.beta * load_c<TC>((const TC*)p.Cin + at);
+      ((TC*)p.C)[at] = from_acc<TC>(v);
     }
     __syncthreads();
   }
@@ -351,7 +350,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_pipe(KArgs p) {
   const int nk = (min(p.K, kbeg + p.kchunk) - kbeg) / BK;  // >= 1
   const uint16_t* __restrict__ Ag = (const uint16_t*)p.A + b0 * p.a_b0 + b1 * p.a_b1 + kbeg;
   const uint16_t* __restrict__ Bg = (const uint16_t*)p.B + b0 * p.b_b0 + b1 * p.b_b1 + kbeg;
-  double* __restrict__ Cg = (double*)p.C + b0 * p.c_b0 + b1 * p.c_b1;
+  double* Cg = (double*)p.C + b0 * p.c_b0 + b1 * p.c_b1;
+  const double* Ci = (const double*)p.Cin + b0 * p.c_b0 + b1 * p.c_b1;
 
   // this thread's chunks c = j NT + tid (row c / 8, slot c % 8) of A (j <
   // CA) and of B (j < CB) (rows past the matrix read its last row; those
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_pipe(KArgs p) {
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          cv[j][r] = Cg[min(row_of(i, r), p.M - 1) * p.c_m + min(col_of(j), p.N - 1) * p.c_n];
+          cv[j][r] = Ci[min(row_of(i, r), p.M - 1) * p.c_m + min(col_of(j), p.N - 1) * p.c_n];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -497,7 +497,8 @@ __global__ __launch_bounds__(256) void gemm_smallk(KArgs p) {
   const int b1 = blockIdx.y / p.nb0 + blockIdx.z * (gridDim.y / p.nb0);
   const double* __restrict__ A = (const double*)p.A + b0 * p.a_b0 + b1 * p.a_b1;
   const double* __restrict__ B = (const double*)p.B + b0 * p.b_b0 + b1 * p.b_b1;
-  double* __restrict__ C = (double*)p.C + b0 * p.c_b0 + b1 * p.c_b1;
+  double* C = (double*)p.C + b0 * p.c_b0 + b1 * p.c_b1;
+  const double* Cin = (const double*)p.Cin + b0 * p.c_b0 + b1 * p.c_b1;
   const int L = LONG_N ? p.N : p.M;
   const int S = LONG_N ? p.M : p.N;
   // the short side is split over p.splits groups of workgroups. With at
@@ -533,10 +534,10 @@ __global__ __launch_bounds__(256) void gemm_smallk(KArgs p) {
 #pragma unroll
     for (int k = 0; k < kSmallK; ++k)
       if (k < p.K) acc += sh[s * kSmallK + k] * r[k];
-    double* c = LONG_N ? C + s * p.c_m + l * p.c_n : C + l * p.c_m + s * p.c_n;
+    const int64_t at = LONG_N ? s * p.c_m + l * p.c_n : l * p.c_m + s * p.c_n;
     double v = p.alpha * acc;
-    if (p.beta != 0.0) v += p.beta * *c;
-    *c = v;
+    if (p.beta != 0.0) v += p.beta * Cin[at];
+    C[at] = v;
   }
 }
 
@@ -546,6 +547,7 @@ void launch_smallk(const GemmDesc& d, const void* A, const void* B, void* C, hip
   p.A = A; p.a_m = d.a_m; p.a_k = d.a_k; p.a_b0 = d.a_b0; p.a_b1 = d.a_b1;
   p.B = B; p.b_k = d.b_k; p.b_n = d.b_n; p.b_b0 = d.b_b0; p.b_b1 = d.b_b1;
   p.C = C; p.c_m = d.c_m; p.c_n = d.c_n; p.c_b0 = d.c_b0; p.c_b1 = d.c_b1;
+  p.Cin = d.Cin ? d.Cin : (double*)C;
   p.alpha = d.alpha; p.beta = d.beta;
   // the long side is the one with more elements; ties go to N (usually the
   // contiguous index of C)
@@ -589,6 +591,7 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
   p.A = A; p.a_m = d.a_m; p.a_k = d.a_k; p.a_b0 = d.a_b0; p.a_b1 = d.a_b1;
   p.B = B; p.b_k = d.b_k; p.b_n = d.b_n; p.b_b0 = d.b_b0; p.b_b1 = d.b_b1;
   p.C = C; p.c_m = d.c_m; p.c_n = d.c_n; p.c_b0 = d.c_b0; p.c_b1 = d.c_b1;
+  p.Cin = d.Cin ? d.Cin : (double*)C;
   p.alpha = d.alpha; p.beta = d.beta;
   const int64_t nb = (int64_t)d.nb0 * d.nb1;
   p.nbtot = (int)nb;
@@ -801,6 +804,7 @@ bool launch_f64(const GemmDesc& d, const double* A, const double* B, const doubl
   p.lda = la.ld; p.a_b0 = d.a_b0; p.a_b1 = d.a_b1;
   p.ldb = lb.ld; p.b_b0 = d.b_b0; p.b_b1 = d.b_b1;
   p.C = C; p.c_m = d.c_m; p.c_n = d.c_n; p.c_b0 = d.c_b0; p.c_b1 = d.c_b1;
+  p.Cin = d.Cin ? d.Cin : (double*)C;
   p.alpha = d.alpha; p.beta = d.beta;
   p.ws = d.ws;
   const int64_t nb = (int64_t)d.nb0 * d.nb1, ws = d.ws ? d.ws_elems : 0;
@@ -1057,6 +1061,7 @@ void gemm_impl(const GemmDesc& d, const void* A, const void* B, const void* A2, 
       if (A2) {
         GemmDesc e = d;
         e.beta = 1.0;
+        e.Cin = nullptr;
         launch_smallk(e, A2, B2, C, s);
       }
       return;

@@ -22,6 +22,7 @@ struct GemmDesc {
   int64_t b_k = 0, b_n = 0, b_b0 = 0, b_b1 = 0;
   int64_t c_m = 0, c_n = 0, c_b0 = 0, c_b1 = 0;
   double alpha = 1.0, beta = 0.0;
+  const double* Cin = nullptr;  // C = alpha A B + beta Cin, at C's strides (null: C itself)
   // Optional scratch for split-K: products with too few output tiles to
   // fill the GPU split the contraction into S chunks whose partial sums go
   // here and are then added in a fixed order (deterministic). Needs S *

@@ -19,6 +19,7 @@ struct Args {
   int64_t lda, a_b0, a_b1;
   int64_t ldb, b_b0, b_b1;
   double* C;
+  const double* Cin;  // C = alpha sum + beta Cin, at C's strides
   int64_t c_m, c_n, c_b0, c_b1;
   double alpha, beta;
   double* ws;      // chunk sums [chunk][tail tile][wr * wc]
@@ -301,7 +302,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
         if (row_of(i) < p.wr && col_of(j) < p.wc) W[row_of(i) * p.wc + col_of(j)] = acc[i][j];
     return;
   }
-  double* __restrict__ Cg = p.C + b0 * p.c_b0 + b1 * p.c_b1 + m0 * p.c_m + n0 * p.c_n;
+  const int64_t coff = b0 * p.c_b0 + b1 * p.c_b1 + m0 * p.c_m + n0 * p.c_n;
+  double* Cg = p.C + coff;
+  const double* Ci = p.Cin + coff;
   const int mr = p.M - m0, nr = p.N - n0;
   const double alpha = p.alpha, beta = p.beta;
   if (beta == 0.0) {
@@ -316,7 +319,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
 #pragma unroll
     for (int i = 0; i < TMI; ++i)
 #pragma unroll
-      for (int j = 0; j < TNI; ++j) cv[i][j] = Cg[min(row_of(i), mr - 1) * p.c_m + min(col_of(j), nr - 1) * p.c_n];
+      for (int j = 0; j < TNI; ++j) cv[i][j] = Ci[min(row_of(i), mr - 1) * p.c_m + min(col_of(j), nr - 1) * p.c_n];
 #pragma unroll
     for (int i = 0; i < TMI; ++i)
 #pragma unroll
@@ -335,12 +338,12 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce(Args p) {
   const int n = p.wr * p.wc;
   const int64_t step = (int64_t)p.ntail * n;
   const double* __restrict__ W = p.ws + (int64_t)blockIdx.x * n;
-  double* __restrict__ Cg = p.C + (b % p.nb0) * p.c_b0 + (b / p.nb0) * p.c_b1;
+  const int64_t coff = (b % p.nb0) * p.c_b0 + (b / p.nb0) * p.c_b1;
   for (int e = blockIdx.y * 256 + threadIdx.x; e < n; e += gridDim.y * 256) {
     const int m = im * BM + e / p.wc, c = in * BN + e % p.wc;
     if (m >= p.M || c >= p.N) continue;
-    double* dst = Cg + m * p.c_m + c * p.c_n;
-    const double old = p.beta != 0.0 ? *dst : 0.0;
+    const int64_t at = coff + m * p.c_m + c * p.c_n;
+    const double old = p.beta != 0.0 ? p.Cin[at] : 0.0;
     double acc = 0.0;
     int s = 0;
     for (; s + 4 <= p.ts; s += 4) {  // four chunks' loads in flight
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce(Args p) {
     for (; s < p.ts; ++s) acc += W[s * step + e];
     double v = p.alpha * acc;
     if (p.beta != 0.0) v += p.beta * old;
-    *dst = v;
+    p.C[at] = v;
   }
 }
 
@@ -367,7 +370,7 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce_wide(Args p) {
   const int n = p.wr * p.wc;
   const int64_t step = (int64_t)p.ntail * n;
   const double* __restrict__ W = p.ws + (int64_t)blockIdx.x * n;
-  double* __restrict__ Cg = p.C + (b % p.nb0) * p.c_b0 + (b / p.nb0) * p.c_b1;
+  const int64_t coff = (b % p.nb0) * p.c_b0 + (b / p.nb0) * p.c_b1;
   const int eo = threadIdx.x & 15, sg = threadIdx.x >> 4;
   for (int e0 = blockIdx.y * 16; e0 < n; e0 += gridDim.y * 16) {
     const int e = e0 + eo;
@@ -390,10 +393,10 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce_wide(Args p) {
     if (sg == 0 && e < n && m < p.M && c < p.N) {
       double sum = 0.0;
       for (int q = 0; q < 16; ++q) sum += sm[q][eo];
-      double* dst = Cg + m * p.c_m + c * p.c_n;
+      const int64_t at = coff + m * p.c_m + c * p.c_n;
       double v = p.alpha * sum;
-      if (p.beta != 0.0) v += p.beta * *dst;
-      *dst = v;
+      if (p.beta != 0.0) v += p.beta * p.Cin[at];
+      p.C[at] = v;
     }
     __syncthreads();
   }

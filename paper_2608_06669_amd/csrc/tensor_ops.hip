@@ -13,6 +13,7 @@ constexpr int kTile = 32;
 // ---- permutation with both fastest axes different: 32 x 32 LDS tile ----
 struct PermArgs {
   const double* in;
+  const double* src;
   double* out;
   int E3, Eq;         // extents of output axis 3 and output axis q
   int64_t in_s3;      // input stride of output axis 3 (input stride of q is 1)
@@ -30,7 +31,7 @@ __global__ __launch_bounds__(256) void permute_tiled_kernel(PermArgs p) {
   const int u = blockIdx.y;
   const int w = blockIdx.z;
   const double* in = p.in + u * p.in_su + w * p.in_sw;
-  double* out = p.out + u * p.out_su + w * p.out_sw;
+  const int64_t base = u * p.out_su + w * p.out_sw;
   const int tx = threadIdx.x & 31;
   const int ty = threadIdx.x >> 5;  // 0..7
   // read: x runs along q (input-contiguous), y along axis 3
@@ -47,9 +48,9 @@ __global__ __launch_bounds__(256) void permute_tiled_kernel(PermArgs p) {
     const int i3 = t3 * kTile + tx;
     const int iq = tq * kTile + ty + r;
     if (iq < p.Eq && i3 < p.E3) {
-      double* o = out + (int64_t)iq * p.out_sq + i3;
+      const int64_t at = base + (int64_t)iq * p.out_sq + i3;
       const double v = p.alpha * tile[tx][ty + r];
-      *o = (p.beta == 0.0) ? v : v + p.beta * *o;
+      p.out[at] = (p.beta == 0.0) ? v : v + p.beta * p.src[at];
     }
   }
 }
@@ -57,6 +58,7 @@ __global__ __launch_bounds__(256) void permute_tiled_kernel(PermArgs p) {
 // ---- permutation that keeps the fastest axis: plain streaming ----
 struct PermFlatArgs {
   const double* in;
+  const double* src;
   double* out;
   int od[4];
   int64_t is[4];  // input stride of each output axis
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(256) void permute_flat_kernel(PermFlatArgs p) {
       const uint32_t i1 = r % od1; r /= od1;
       const uint32_t i0 = r;
       const double v = p.alpha * p.in[i0 * p.is[0] + i1 * p.is[1] + i2 * p.is[2] + i3 * p.is[3]];
-      p.out[e] = (p.beta == 0.0) ? v : v + p.beta * p.out[e];
+      p.out[e] = (p.beta == 0.0) ? v : v + p.beta * p.src[e];
     }
     return;
   }
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(256) void permute_flat_kernel(PermFlatArgs p) {
     const int i1 = (int)(r % p.od[1]); r /= p.od[1];
     const int i0 = (int)r;
     const double v = p.alpha * p.in[i0 * p.is[0] + i1 * p.is[1] + i2 * p.is[2] + i3 * p.is[3]];
-    p.out[e] = (p.beta == 0.0) ? v : v + p.beta * p.out[e];
+    p.out[e] = (p.beta == 0.0) ? v : v + p.beta * p.src[e];
   }
 }
 
@@ -339,7 +341,8 @@ inline int grid_for(int64_t n, int cap = 4096) {
 }  // namespace
 
 void permute4(const double* in, double* out, const int d[4], const int perm[4], double alpha, double beta,
-              hipStream_t s) {
+              hipStream_t s, const double* src) {
+  if (!src) src = out;
   int64_t is[4];
   is[3] = 1;
   for (int k = 2; k >= 0; --k) is[k] = is[k + 1] * d[k + 1];
@@ -355,7 +358,7 @@ void permute4(const double* in, double* out, const int d[4], const int perm[4], 
     if (perm[k] == 3) q = k;
   if (q == 3 || od[3] == 1 || od[q] == 1) {
     PermFlatArgs p;
-    p.in = in; p.out = out; p.total = total; p.alpha = alpha; p.beta = beta;
+    p.in = in; p.src = src; p.out = out; p.total = total; p.alpha = alpha; p.beta = beta;
     for (int k = 0; k < 4; ++k) { p.od[k] = od[k]; p.is[k] = is[perm[k]]; }
     permute_flat_kernel<<<grid_for(total, 16384), 256, 0, s>>>(p);
     PNK_CHECK_LAUNCH();
@@ -365,7 +368,7 @@ void permute4(const double* in, double* out, const int d[4], const int perm[4], 
   for (int k = 0; k < 3; ++k)
     if (k != q) rest[nr++] = k;
   PermArgs p;
-  p.in = in; p.out = out;
+  p.in = in; p.src = src; p.out = out;
   p.E3 = od[3]; p.Eq = od[q];
   p.in_s3 = is[perm[3]];
   p.out_sq = os[q];

@@ -5,12 +5,13 @@
 
 namespace pnk {
 
-// out[perm(idx)] = alpha * in[idx] + beta * out[perm(idx)] for a row-major
+// out[perm(idx)] = alpha * in[idx] + beta * src[perm(idx)] for a row-major
 // 4-index tensor `in` of shape d[0..3]; output axis k is input axis perm[k].
+// src, laid out like out, is out itself if null.
 // Tiles through LDS whenever the two fastest axes differ, so both the reads
 // and the writes are coalesced.
 void permute4(const double* in, double* out, const int d[4], const int perm[4], double alpha,
-              double beta, hipStream_t s);
+              double beta, hipStream_t s, const double* src = nullptr);
 
 // y = a * x + b * y (b == 0: y is not read)
 void axpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t s);

@@ -1,0 +1,65 @@
+"""The passes that write the layouts of the doubles, sum the dressed Fock
+blocks and gather the residual, at the edges of their tiles (32 x 32 virtual
+pairs, 64 columns, 256 auxiliary slices): residual and J v against the oracle.
+
+FP64: the same polynomial in another order of summation, a few ulps of the
+largest intermediate; 1e-10 of the largest component. FP32 / BF16: unit
+roundoff (2^-24, 2^-8) over contractions of a few thousand terms."""
+
+import numpy as np
+import pytest
+
+from gen import make_general, make_problem, random_amplitudes
+from oracle import ccsd
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SIZES = [(1, 1, 2), (1, 32, 3), (2, 31, 5), (3, 33, 7), (2, 64, 256), (4, 65, 257)]
+
+
+@pytest.fixture(scope="module")
+def handle():
+    import paper_2608_06669_amd as pk
+    h = pk.Handle(0)
+    yield h
+    h.close()
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda")
+
+
+def problem(p):
+    import paper_2608_06669_amd as pk
+    return pk.DeviceProblem.from_problem(p)
+
+
+def rel_max(got, want):
+    scale = max(np.abs(w).max() for w in want)
+    return max(np.abs(g.cpu().numpy() - w).max() for g, w in zip(got, want)) / scale
+
+
+@pytest.mark.parametrize("o,v,naux", SIZES)
+def test_fp64_residual_and_tangent(handle, o, v, naux):
+    p = make_general(o, v, naux, 60 + v)
+    t1, t2 = random_amplitudes(o, v, 61, scale=0.05)
+    v1, v2 = random_amplitudes(o, v, 62, scale=1.0)
+    P = problem(p)
+    args = (p.f_oo, p.f_ov, p.f_vv, p.L, t1, t2)
+    assert rel_max(handle.residual(P, dev(t1), dev(t2)), ccsd.residual(*args)) <= 1e-10
+    got = handle.jvp(P, dev(t1), dev(t2), dev(v1), dev(v2), prec="fp64")
+    assert rel_max(got, ccsd.jvp_complex_step(*args, v1, v2)) <= 1e-10
+
+
+@pytest.mark.parametrize("prec,rel", [("fp32", 5e-5), ("bf16", 3e-2)])
+@pytest.mark.parametrize("o,v,naux", SIZES[2:])
+def test_low_precision_tangent(handle, o, v, naux, prec, rel):
+    p = make_problem(o, v, naux, 63 + v, gauge="haar")
+    t1, t2 = random_amplitudes(o, v, 64, scale=0.02)
+    v1, v2 = random_amplitudes(o, v, 65, scale=1.0)
+    got = handle.jvp(problem(p), dev(t1), dev(t2), dev(v1), dev(v2), prec=prec)
+    want = ccsd.jvp_complex_step(p.f_oo, p.f_ov, p.f_vv, p.L, t1, t2, v1, v2)
+    num = sum(np.sum((g.cpu().numpy() - w) ** 2) for g, w in zip(got, want))
+    assert np.sqrt(num / sum(np.sum(w ** 2) for w in want)) < rel
