@@ -48,6 +48,12 @@ RESIDUAL_TRAFFIC_BYTES = None
 INNER_STEP_TRAFFIC_BYTES = None
 
 
+def folded_residual_flops(o, v):
+    """What the FP64 residual runs fewer flops than the library's algorithmic
+    count, which has six products of ring size: it folds them into four."""
+    return 4.0 * (o * v) ** 3
+
+
 def nominal_residual_flops(o, v, naux):
     """Nominal FP64 flops of one residual evaluation (fixed formula)."""
     return (2 * o * o * v ** 4 + 12 * o ** 3 * v ** 3 + 4 * o ** 4 * v * v + 8 * naux * o * o * v * v
@@ -320,12 +326,13 @@ def bench_headline(args):
     res_ms = ms_res / max(n_res, 1)
     roof = None
     if n_res:
-        tf = F_alg / (res_ms * 1e-3) / 1e12
+        F_run = F_alg - folded_residual_flops(o, v)
+        tf = F_run / (res_ms * 1e-3) / 1e12
         roof = {"bound": "mfma", "achieved": tf, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": tf / FP64_PEAK_TFLOPS, "traffic": RESIDUAL_TRAFFIC_BYTES,
                 "kernel": "FP64 residual evaluation (recorded graph of matrix-core products: ladder in the "
                           "symmetric/antisymmetric pair basis, ring, hole-hole, Fock and dressing terms)",
-                "launches_timed": n_res, "avg_ms": res_ms, "flops_per_launch": F_alg}
+                "launches_timed": n_res, "avg_ms": res_ms, "flops_per_launch": F_run}
     roof_jvp = None
     if n_jvp and prec == "bf16":
         jv_ms = ms_jvp / n_jvp

@@ -225,10 +225,10 @@ __global__ __launch_bounds__(256) void amp_layouts_kernel(int o, int v, int tile
   auto emit = [&](int a, int b, double x, double y) {
     const int64_t m = (((int64_t)i * v + a) * o + j) * v + b;
     const double u = 2.0 * x - y;
-    p.Tia[m] = x;
     p.Tsia[m] = y;
     p.Uia[m] = u;
     if (p.U) {
+      p.Tia[m] = x;
       const int64_t q = ij * vv + (int64_t)a * v + b;
       p.U[q] = u;
       p.Uklca[q] = 2.0 * y - x;
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256) void amp_layouts_kernel(int o, int v, int tile
 
 // The doubles residual from its parts,
 //   R_ij^ab += E[(i,a)][(j,b)] + P_ij^ab V_ij^ab + ladder_ij^ab,
-//   V_ij^ab = X[i][j][a][b] + T[(i,a)][(j,b)] + S[(j,a)][(i,b)],
+//   V_ij^ab = X[i][j][a][b] + T[(i,a)][(j,b)] + S[(j,a)][(i,b)] + w S[(i,a)][(j,b)],
 // the ladder unpacked from its symmetric and antisymmetric combinations (E
 // may be null). A workgroup takes the tiles (A, B), (B, A), A <= B, of (i, j)
 // and (j, i), i <= j: each part is read once, along rows, transposed
@@ -273,7 +273,11 @@ __global__ __launch_bounds__(256) void doubles_sum_kernel(int o, int v, int tile
   const bool offd = i < j;  // the antisymmetric part has rows i < j only
   auto ia = [&](int x, int a, int y, int b) { return (((int64_t)x * v + a) * o + y) * v + b; };
   auto ij = [&](int x, int y, int a, int b) { return ((int64_t)x * o + y) * vv + (int64_t)a * v + b; };
-  auto V = [&](int x, int y, int a, int b) { return p.X[ij(x, y, a, b)] + p.T[ia(x, a, y, b)] + p.S[ia(y, a, x, b)]; };
+  auto V = [&](int x, int y, int a, int b) {
+    double s = p.X[ij(x, y, a, b)] + p.T[ia(x, a, y, b)] + p.S[ia(y, a, x, b)];
+    if (p.w != 0.0) s += p.w * p.S[ia(x, a, y, b)];
+    return s;
+  };
   // tiles (P, Q) of (i, j) and (Q, P) of (j, i)
   auto half = [&](int P, int Q, bool first) {
     double d[kT / 8], r1[kT / 8], r2[kT / 8];

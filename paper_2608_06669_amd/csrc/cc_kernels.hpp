@@ -38,19 +38,21 @@ void ppl_pack_w(int v, int a0, int na, const double* Wblk, const int* pair_a, co
 // Layouts of doubles t[i][j][a][b] (u = 2 t_ij^ab - t_ij^ba):
 struct AmpLayouts {
   const double* t;
-  double *Tia, *Tsia, *Uia;  // [(i,a)][(j,b)]: t_ij^ab, t_ij^ba, u_ij^ab
+  double *Tsia, *Uia;  // [(i,a)][(j,b)]: t_ij^ba, u_ij^ab
   // Tp[ij][q] = (t_ij^cd + t_ij^dc)/2 (c < d) or t_ij^cc / 2 (c = d), i <= j;
   // Tm[ij][q'] = (t_ij^cd - t_ij^dc)/2, i < j
   double *Tp, *Tm;
-  double *U, *Uklca, *Uail;  // (null: not wanted) [i][j][a][b]: u_ij^ab, u_ij^ba; [a][i][j][b]: u_ij^ab
+  // (all null: not wanted) [(i,a)][(j,b)]: t_ij^ab; [i][j][a][b]: u_ij^ab, u_ij^ba; [a][i][j][b]: u_ij^ab
+  double *Tia, *U, *Uklca, *Uail;
 };
 void amp_layouts(int o, int v, const AmpLayouts& p, hipStream_t s);
 
 // R[i][j][a][b] += E[(i,a)][(j,b)] + V_ij^ab + V_ji^ba + sum_cd (ac|bd) t_ij^cd,
-// V_ij^ab = X[i][j][a][b] + T[(i,a)][(j,b)] + S[(j,a)][(i,b)], the ladder
-// rebuilt from Rp = Tp S, Rm = Tm A; E may be null.
+// V_ij^ab = X[i][j][a][b] + T[(i,a)][(j,b)] + S[(j,a)][(i,b)] + w S[(i,a)][(j,b)],
+// the ladder rebuilt from Rp = Tp S, Rm = Tm A; E may be null.
 struct DoublesParts {
   const double *X, *T, *S, *Rp, *Rm, *E;
+  double w;
   double* R;
 };
 void doubles_sum(int o, int v, const DoublesParts& p, hipStream_t s);

@@ -175,7 +175,7 @@ void for_each_buffer(const Sizes& z, const EngineOptions& opt, F f, G g) {
   f(np * o * o); f(np * ov); f(np * ov); f(np * v * v);
   const int64_t p2 = z.p2, p2m = z.p2m, o2 = z.o2;
   f(p2 * p2); f(p2m * p2m); f(z.wna * v * v * v); g(4 * (2 * p2 + 2 * p2m));
-  f(o * v * v * v); f(n2); f(n2); f(n2); f(n2);
+  f(o * v * v * v); for (int k = 0; k < 5; ++k) f(n2);
   if (opt.lowp_f32) {
     g(4 * p2 * pad_to(p2, 4)); g(4 * p2m * pad_to(p2m, 4));
     g(4 * o * v * v * v); g(4 * n2); g(4 * n2); g(4 * n2); g(4 * n2);
@@ -189,12 +189,15 @@ void for_each_buffer(const Sizes& z, const EngineOptions& opt, F f, G g) {
   for (int rep = 0; rep < 2; ++rep) {
     f(np * o * o); f(np * ov); f(np * v * v); f(naux); f(naux * o * o);
     f(o * o); f(ov); f(v * v);
-    for (int k = 0; k < 5; ++k) f(n2);  // Tia, Tsia, Uia, Tmp, X
+    for (int k = 0; k < 4; ++k) f(n2);  // Tsia, Uia, Tmp, X
     f(v * v); f(o * o); f(o * o * o * o); f(o * o * o * o); f(o * o * o * o); f(o * o * ov);
-    f(n2); f(n2);                       // J, K
+    f(n2); f(n2);                       // M, K
     f(naux * ov); f(naux * ov); f(o * o * ov);
     f(o2 * p2); f(o2 * p2m); f(o2 * p2); f(o2 * p2m);  // Tp, Tm, Rp, Rm
-    if (opt.lowp_f32 || opt.lowp_bf16) { f(n2); f(n2); f(n2); f(o * o * ov); }  // U, Uklca, Uail, KilcT
+    if (opt.lowp_f32 || opt.lowp_bf16) {  // Tia, U, Uklca, Uail, J, KilcT
+      for (int k = 0; k < 5; ++k) f(n2);
+      f(o * o * ov);
+    }
   }
   f(reduce_partials_size(64));
   f(ov + n2);  // zeros
@@ -229,7 +232,7 @@ Engine::Engine(int o, int v, int naux, const EngineOptions& opt)
   pair_a_ = arena_.take<int>(z.p2); pair_b_ = arena_.take<int>(z.p2);
   mpair_a_ = arena_.take<int>(z.p2m); mpair_b_ = arena_.take<int>(z.p2m);
   Wov.v = take(O * V * V * V);
-  Ioovv.v = take(N2); Iovov.v = take(N2); Ix.v = take(N2); Itil.v = take(N2);
+  Ioovv.v = take(N2); Iovov.v = take(N2); Ix.v = take(N2); Lh.v = take(N2); Itil.v = take(N2);
   // the low-precision ladder tensors keep rows of a 16-byte multiple (the
   // pair counts v(v+1)/2, v(v-1)/2 need not be), for vector loads
   ld32_ = pad_to(z.p2, 4); ld32m_ = pad_to(z.p2m, 4);
@@ -254,17 +257,17 @@ Engine::Engine(int o, int v, int naux, const EngineOptions& opt)
   cast_bytes_ = cast_bytes(z, opt);
   if (cast_bytes_) cast_ws_ = arena_.take<char>((size_t)cast_bytes_);
   Ten* inter[] = {&Loo, &Lvo, &Lvv, &this->D, &LooT, &Foo, &Fov, &Fvv,
-                  &Tia, &Tsia, &Uia, &Tmp, &X,
-                  &Gv, &Go, &Kilj, &Wkl, &Y, &Z, &J, &K, &Q, &QT, &Kilc,
+                  &Tsia, &Uia, &Tmp, &X,
+                  &Gv, &Go, &Kilj, &Wkl, &Y, &Z, &M, &K, &Q, &QT, &Kilc,
                   &Tp, &Tm, &Rp, &Rm,
-                  &U, &Uklca, &Uail, &KilcT};
+                  &Tia, &U, &Uklca, &Uail, &J, &KilcT};
   const int64_t isz[] = {NP * O * O, NP * OV, NP * V * V, NA, NA * O * O, O * O, OV, V * V,
-                         N2, N2, N2, N2, N2,
+                         N2, N2, N2, N2,
                          V * V, O * O, O * O * O * O, O * O * O * O, O * O * O * O, O * O * OV, N2, N2,
                          NA * OV, NA * OV, O * O * OV,
                          z.o2 * z.p2, z.o2 * z.p2m, z.o2 * z.p2, z.o2 * z.p2m,
-                         N2, N2, N2, O * O * OV};
-  const size_t nlow = opt.lowp_f32 || opt.lowp_bf16 ? 0 : 4;  // the last four: FP32 / BF16 only
+                         N2, N2, N2, N2, N2, O * O * OV};
+  const size_t nlow = opt.lowp_f32 || opt.lowp_bf16 ? 0 : 6;  // the last six: FP32 / BF16 only
   static_assert(sizeof(inter) / sizeof(inter[0]) == sizeof(isz) / sizeof(isz[0]), "buffer table");
   for (int rep = 0; rep < 2; ++rep)
     for (size_t k = 0; k + nlow < sizeof(isz) / sizeof(isz[0]); ++k) {
@@ -376,13 +379,14 @@ void Engine::operand(const Ten& t, bool tangent, const void** p, Prec* prec) con
 }
 
 // C = alpha A B + beta C, or its tangent dC = alpha (dA B + A dB) + beta dC;
-// with src, beta is 1 and takes src in place of C
-void Engine::mm(const GemmDesc& d, const Ten& A, const Ten& B, const Ten& C, const Ten* src, int64_t off) {
+// with src, alpha A B + beta src
+void Engine::mm(const GemmDesc& d, const Ten& A, const Ten& B, const Ten& C, const Ten* src, int64_t off,
+                double beta) {
   const double f = 2.0 * d.M * d.N * d.K * (double)d.nb0 * d.nb1;
   GemmDesc e = with_ws(d);
   if (src) {
     const bool there = mode_ == Mode::Value || src->var;  // (the tangent of a constant is zero)
-    e.beta = there ? 1.0 : 0.0;
+    e.beta = there ? beta : 0.0;
     e.Cin = there ? out(*src) + off : nullptr;
   }
   if (mode_ == Mode::Value) {
@@ -556,6 +560,7 @@ void Engine::prepare(const ProblemView& p, hipStream_t s, bool with_eigen) {
     const int dims[4] = {o, v, o, v};
     const int pm[4] = {2, 1, 0, 3};
     permute4(Iovov.v, Ix.v, dims, pm, 1.0, 0.0, s);
+    permute4(Iovov.v, Lh.v, dims, pm, -0.5, 1.0, s, Iovov.v);  // (kc|ld) - (kd|lc) / 2
     const int dims2[4] = {o, o, v, v};
     const int pm2[4] = {0, 1, 3, 2};
     permute4(Ioovv.v, Itil.v, dims2, pm2, -1.0, 2.0, s, Ioovv.v);
@@ -622,10 +627,12 @@ void Engine::run(Mode m) {
   {
     AmpLayouts p{};
     p.t = out(T2);
-    p.Tia = out(Tia); p.Tsia = out(Tsia); p.Uia = out(Uia);
+    p.Tsia = out(Tsia); p.Uia = out(Uia);
     p.Tp = out(Tp); p.Tm = out(Tm);
-    // (an FP64 tangent has no use for the last three)
-    if (lowp_engine && (lowp || mode_ == Mode::Value)) { p.U = out(U); p.Uklca = out(Uklca); p.Uail = out(Uail); }
+    // (an FP64 tangent has no use for the others)
+    if (lowp_engine && (lowp || mode_ == Mode::Value)) {
+      p.Tia = out(Tia); p.U = out(U); p.Uklca = out(Uklca); p.Uail = out(Uail);
+    }
     amp_layouts(o, v, p, s_);
   }
 
@@ -685,41 +692,60 @@ void Engine::run(Mode m) {
   mm(batch0(gd(v, v, o, 1, v, v, 1, v, 1, -1.0, 1.0), OO, 0, ov, vv), T1, Z, X);
 
   // ---- ring terms, rows and columns (i,a) ----
-  mm(gd(OV, OV, naux, 1, ov, ov, 1, ov, 1), Lvo, Lov0, J);         // (ai|kc)~
-  // (BF16 tangents read the ring integrals along k: Iovov is symmetric, and
-  // the BF16 copy of Ix holds its transpose)
-  const bool kc16 = mode_ == Mode::Tangent && jprec_ == Prec::BF16 && Iovov.lp16;
-  auto ring = [&](double alpha) {
-    GemmDesc g = gd(OV, OV, OV, ov, 1, kc16 ? 1 : ov, kc16 ? ldov16_ : 1, ov, 1, alpha, 1.0);
-    if (kc16) g.b_kzero = ldov16_;
-    return g;
-  };
-  mm(ring(0.5), Uia, Iovov, J);
-  mm(ring(-0.5), Tia, Ix, J);
   mm(gd(OO, VV, naux, 1, oo, vv, 1, vv, 1), Loo, Lvv, Tmp);        // (ki|ac)~ as [(k,i)][(c,a)]
   perm(Tmp, K, o, o, v, v, 1, 3, 0, 2, 1.0, 0.0);                  // [(i,a)][(k,c)]
-  mm(ring(-0.5), Tsia, Ix, K);
-  // (ai|bj)~: pair-symmetric, so half of it joins the sum that P_ij^ab
-  // doubles; in FP32 / BF16 (i,a),(j,b) and (j,b),(i,a) may differ by a
-  // rounding, and it stays apart, in the tangent of U, read above only
-  const Ten* E = lowp ? &U : nullptr;
-  mm(gd(OV, OV, naux, 1, ov, ov, 1, ov, 1, lowp ? 1.0 : 0.5), Lvo, Lvo, lowp ? U : Tmp);
-  GemmDesc gk = gd(OV, OV, OV, ov, 1, 1, ov, ov, 1, 1.0, lowp ? 0.0 : 1.0);
-  mm(gk, J, Uia, Tmp);                                             // J u_jk^bc
-  gk.alpha = -1.0;
-  gk.beta = 1.0;
-  mm(gk, K, Tia, Tmp);                                             // - K t_kj^cb
-  // - K_ki,bc t_kj^ac as [(i,b)][(j,a)], into J's tangent (free: a value
-  // pass has none yet, a tangent has just read it)
-  Ten KT = J;
+  const GemmDesc g0 = gd(OV, OV, naux, 1, ov, ov, 1, ov, 1), g1 = gd(OV, OV, OV, ov, 1, ov, 1, ov, 1),
+                 gT = gd(OV, OV, OV, ov, 1, 1, ov, ov, 1);
+  auto scaled = [](GemmDesc g, double alpha, double beta) {
+    g.alpha = alpha;
+    g.beta = beta;
+    return g;
+  };
+  Ten KT = M;  // - K t in a tangent array that is free: a value pass has none yet, a tangent has read it by then
   KT.v = KT.d;
-  gk.beta = 0.0;
-  mm(gk, K, Tsia, KT);
+  const Ten* E = nullptr;
+  double w = 0.0;
+  if (lowp) {
+    // (BF16 tangents read the ring integrals along k: Iovov is symmetric, and
+    // the BF16 copy of Ix holds its transpose)
+    const bool kc16 = jprec_ == Prec::BF16 && Iovov.lp16;
+    GemmDesc g = gd(OV, OV, OV, ov, 1, kc16 ? 1 : ov, kc16 ? ldov16_ : 1, ov, 1);
+    if (kc16) g.b_kzero = ldov16_;
+    mm(g0, Lvo, Lov0, J);                                          // (ai|kc)~
+    mm(scaled(g, 0.5, 1.0), Uia, Iovov, J);
+    mm(scaled(g, -0.5, 1.0), Tia, Ix, J);
+    mm(scaled(g, -0.5, 1.0), Tsia, Ix, K);
+    mm(gT, J, Uia, Tmp);                                           // J u_jk^bc
+    mm(scaled(gT, -1.0, 1.0), K, Tia, Tmp);                        // - K t_kj^cb
+    mm(scaled(gT, -1.0, 0.0), K, Tsia, KT);                        // - K_ki,bc t_kj^ac as [(i,b)][(j,a)]
+    // (ai|bj)~: its (i,a),(j,b) and (j,b),(i,a) elements may differ by a
+    // rounding, so it stays outside the pair sum, in the tangent of U, read
+    // above only
+    mm(g0, Lvo, Lvo, U);
+    E = &U;
+  } else {
+    // With t = (u + s) / 2, s_jk^bc = t_jk^cb, and M = J - K / 2,
+    //   J u - K t = M u - K s / 2,
+    //   M = (ai|kc)~ - (ki|ac)~ / 2 + u ((kc|ld) - (kd|lc) / 2) / 2:
+    // four products of ring size (six in a tangent) in place of six (nine)
+    mm(g0, Lvo, Lov0, M, &K, 0, -0.5);
+    mm(scaled(g1, 0.5, 1.0), Uia, Lh, M);
+    mm(scaled(g1, -0.5, 1.0), Tsia, Ix, K);
+    mm(scaled(g0, 0.5, 0.0), Lvo, Lvo, Tmp);                       // (ai|bj)~ / 2, doubled by the pair sum
+    mm(scaled(gT, 1.0, 1.0), M, Uia, Tmp);
+    mm_flops_ += (mode_ == Mode::Value ? 2 : 3) * 2.0 * ov * ov * ov;  // (counted in the six-product form)
+    if (lowp_engine && mode_ == Mode::Value) {
+      const int dims[4] = {o, v, o, v}, same[4] = {0, 1, 2, 3};
+      permute4(K.v, J.v, dims, same, 0.5, 1.0, s_, M.v);
+    }
+    mm(scaled(gT, -1.0, 0.0), K, Tsia, KT);
+    w = 0.5;
+  }
 
   // ---- r2 ----
   {
     DoublesParts p{};
-    p.X = out(X); p.T = out(Tmp); p.S = out(KT); p.Rp = out(Rp); p.Rm = out(Rm);
+    p.X = out(X); p.T = out(Tmp); p.S = out(KT); p.w = w; p.Rp = out(Rp); p.Rm = out(Rm);
     p.E = E ? out(*E) : nullptr;
     p.R = out(R2);
     doubles_sum(o, v, p, s_);

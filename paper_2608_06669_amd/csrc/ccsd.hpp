@@ -150,8 +150,9 @@ class Engine {
   // products in FP32 / BF16, which keep their order of accumulation
   bool lowp() const { return mode_ == Mode::Tangent && jprec_ != Prec::F64; }
   double* out(const Ten& t) const { return mode_ == Mode::Value ? t.v : t.d; }
-  // C = alpha A B + beta C, or (beta 1) alpha A B + src[off..]
-  void mm(const GemmDesc& d, const Ten& A, const Ten& B, const Ten& C, const Ten* src = nullptr, int64_t off = 0);
+  // C = alpha A B + beta C (d's), or alpha A B + beta src[off..]
+  void mm(const GemmDesc& d, const Ten& A, const Ten& B, const Ten& C, const Ten* src = nullptr, int64_t off = 0,
+          double beta = 1.0);
   void perm(const Ten& in, const Ten& out, int d0, int d1, int d2, int d3, int p0, int p1, int p2, int p3,
             double alpha, double beta, const Ten* src = nullptr);
   void dressed_fock_sums();
@@ -174,7 +175,7 @@ class Engine {
   void compute_eigen(const std::vector<double>& foo, const std::vector<double>& fvv, hipStream_t s);
   FockOp fop_;
   bool fop_ok_ = false;
-  Ten Loo0, Lov0, Lvo0, Lvv0, S, Am, Wov, Ioovv, Iovov, Ix, Ikldc, Itil;
+  Ten Loo0, Lov0, Lvo0, Lvv0, S, Am, Wov, Ioovv, Iovov, Ix, Lh, Ikldc, Itil;
   // symmetry-adapted ladder: pair tables and the (ac|bd) block staging area
   int *pair_a_, *pair_b_, *mpair_a_, *mpair_b_;
   double* wblk_;
@@ -189,9 +190,9 @@ class Engine {
   // (dressed vo blocks as [P][i][a], vv ones as [P][c][a] = (ac|, so Fvv and
   // Gv are transposed too)
   Ten Loo, Lvo, Lvv, D, LooT, Foo, Fov, Fvv;
-  Ten Tia, Tsia, Uia;
-  Ten U, Uklca, Uail, KilcT;  // for FP32 / BF16 products only
-  Ten Tmp, X, Gv, Go, Kilj, Wkl, Y, Z, J, K, Q, QT, Kilc;
+  Ten Tsia, Uia;
+  Ten Tia, U, Uklca, Uail, J, KilcT;  // for FP32 / BF16 products only
+  Ten Tmp, X, Gv, Go, Kilj, Wkl, Y, Z, M, K, Q, QT, Kilc;
   Ten Tp, Tm, Rp, Rm;
   double* partials_;
   double* zeros_;  // zero t-vector for the residual at t = 0
