@@ -50,8 +50,13 @@ INNER_STEP_TRAFFIC_BYTES = None
 
 def folded_residual_flops(o, v):
     """What the FP64 residual runs fewer flops than the library's algorithmic
-    count, which has six products of ring size: it folds them into four."""
-    return 4.0 * (o * v) ** 3
+    count: six products of ring size folded into four, and the T1 part of the
+    ladder, sum_cd (kc|ld) t_ij^cd and the hole-hole ladder over (anti)symmetric
+    pairs like the ladder."""
+    p2, p2m, o2, o2m = v * (v + 1) // 2, v * (v - 1) // 2, o * (o + 1) // 2, o * (o - 1) // 2
+    whole = 2.0 * o ** 3 * v ** 3 + 4.0 * o ** 4 * v ** 2
+    pairs = 2.0 * (o2 * p2 * (o * v + 2 * o2) + o2m * p2m * (o * v + 2 * o2m))
+    return 4.0 * (o * v) ** 3 + whole - pairs
 
 
 def nominal_residual_flops(o, v, naux):

@@ -159,7 +159,7 @@ __device__ inline int64_t opair(int i, int j, int n) {  // i <= j
 __global__ void ppl_pack_w_kernel(int v, int a0, int na, const double* __restrict__ Wblk,
                                   const int* __restrict__ pa, const int* __restrict__ pb,
                                   const int* __restrict__ ma, const int* __restrict__ mb, double* __restrict__ S,
-                                  double* __restrict__ A) {
+                                  int64_t lds, double* __restrict__ A, int64_t lda) {
   const int64_t P2 = (int64_t)v * (v + 1) / 2, P2m = (int64_t)v * (v - 1) / 2;
   const int64_t vv = (int64_t)v * v, v3 = vv * v;
   const int64_t p_lo = upair(a0, a0, v), p_hi = (a0 + na < v) ? upair(a0 + na, a0 + na, v) : P2;
@@ -171,13 +171,13 @@ __global__ void ppl_pack_w_kernel(int v, int a0, int na, const double* __restric
       const int64_t p = p_lo + e / P2, q = e % P2;
       const int a = pa[p], b = pb[p], c = pa[q], d = pb[q];
       const double* w = Wblk + (a - a0) * v3 + (int64_t)b * vv;
-      S[p * P2 + q] = w[(int64_t)c * v + d] + w[(int64_t)d * v + c];
+      S[p * lds + q] = (a == b ? 0.5 : 1.0) * (w[(int64_t)c * v + d] + w[(int64_t)d * v + c]);
     } else {
       const int64_t f = e - ns;
       const int64_t p = m_lo + f / P2m, q = f % P2m;
       const int a = ma[p], b = mb[p], c = ma[q], d = mb[q];
       const double* w = Wblk + (a - a0) * v3 + (int64_t)b * vv;
-      A[p * P2m + q] = w[(int64_t)c * v + d] - w[(int64_t)d * v + c];
+      A[p * lda + q] = w[(int64_t)c * v + d] - w[(int64_t)d * v + c];
     }
   }
 }
@@ -221,6 +221,10 @@ __global__ __launch_bounds__(256) void amp_layouts_kernel(int o, int v, int tile
   const double(*sx)[kT + 1] = same ? s1 : s2;
   const int64_t P2 = (int64_t)v * (v + 1) / 2, P2m = (int64_t)v * (v - 1) / 2;
   const int64_t pij = i <= j ? opair(i, j, o) : 0;
+  if (blockIdx.x == 0 && i <= j) {  // the rows' padding
+    if (P2 + threadIdx.x < p.ldp) p.Tp[pij * p.ldp + P2 + threadIdx.x] = 0.0;
+    if (i < j && P2m + threadIdx.x < p.ldm) p.Tm[pij * p.ldm + P2m + threadIdx.x] = 0.0;
+  }
   // x = t_ij^ab, y = t_ij^ba
   auto emit = [&](int a, int b, double x, double y) {
     const int64_t m = (((int64_t)i * v + a) * o + j) * v + b;
@@ -235,8 +239,8 @@ __global__ __launch_bounds__(256) void amp_layouts_kernel(int o, int v, int tile
       p.Uail[(((int64_t)a * o + i) * o + j) * v + b] = u;
     }
     if (i <= j && a <= b) {
-      p.Tp[pij * P2 + upair(a, b, v)] = a == b ? 0.5 * x : 0.5 * (x + y);
-      if (i < j && a < b) p.Tm[pij * P2m + spair(a, b, v)] = 0.5 * (x - y);
+      p.Tp[pij * p.ldp + upair(a, b, v)] = a == b ? p.diag * x : 0.5 * (x + y);
+      if (i < j && a < b) p.Tm[pij * p.ldm + spair(a, b, v)] = 0.5 * (x - y);
     }
   };
 #pragma unroll
@@ -253,7 +257,7 @@ __global__ __launch_bounds__(256) void amp_layouts_kernel(int o, int v, int tile
 }
 
 // The doubles residual from its parts,
-//   R_ij^ab += E[(i,a)][(j,b)] + P_ij^ab V_ij^ab + ladder_ij^ab,
+//   R_ij^ab (+)= E[(i,a)][(j,b)] + P_ij^ab V_ij^ab + ladder_ij^ab,
 //   V_ij^ab = X[i][j][a][b] + T[(i,a)][(j,b)] + S[(j,a)][(i,b)] + w S[(i,a)][(j,b)],
 // the ladder unpacked from its symmetric and antisymmetric combinations (E
 // may be null). A workgroup takes the tiles (A, B), (B, A), A <= B, of (i, j)
@@ -268,7 +272,6 @@ __global__ __launch_bounds__(256) void doubles_sum_kernel(int o, int v, int tile
   upair_inverse(blockIdx.y, o, &i, &j);
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int64_t vv = (int64_t)v * v;
-  const int64_t P2 = (int64_t)v * (v + 1) / 2, P2m = (int64_t)v * (v - 1) / 2;
   const int64_t pij = opair(i, j, o);
   const bool offd = i < j;  // the antisymmetric part has rows i < j only
   auto ia = [&](int x, int a, int y, int b) { return (((int64_t)x * v + a) * o + y) * v + b; };
@@ -287,14 +290,14 @@ __global__ __launch_bounds__(256) void doubles_sum_kernel(int o, int v, int tile
       d[q] = r1[q] = 0.0;
       if (a < v && b < v) {
         d[q] = V(i, j, a, b);
-        r1[q] = p.R[ij(i, j, a, b)];
+        if (p.add) r1[q] = p.R[ij(i, j, a, b)];
         if (p.E) r1[q] += p.E[ia(i, a, j, b)];
       }
       const int c = Q * kT + ty + 8 * q, e = P * kT + tx;
       r2[q] = 0.0;
       if (c < v && e < v) {
         st[ty + 8 * q][tx] = V(j, i, c, e);
-        r2[q] = p.R[ij(j, i, c, e)];
+        if (p.add) r2[q] = p.R[ij(j, i, c, e)];
         if (p.E) r2[q] += p.E[ia(j, c, i, e)];
       }
     }
@@ -306,8 +309,8 @@ __global__ __launch_bounds__(256) void doubles_sum_kernel(int o, int v, int tile
         double xs = 0.0, xa = 0.0;
         if (a < v && b < v) {
           const int lo = min(a, b), hi = max(a, b);
-          xs = p.Rp[pij * P2 + upair(lo, hi, v)];
-          if (offd && a != b) xa = p.Rm[pij * P2m + spair(lo, hi, v)];
+          xs = p.Rp[pij * p.ldp + upair(lo, hi, v)];
+          if (offd && a != b) xa = p.Rm[pij * p.ldm + spair(lo, hi, v)];
           if (a > b) xa = -xa;
         }
         x[q] = xs + xa;
@@ -340,6 +343,99 @@ __global__ __launch_bounds__(256) void doubles_sum_kernel(int o, int v, int tile
   if (i < j && A < B) {
     __syncthreads();
     half(B, A, false);
+  }
+}
+
+// The (k,b) and (k,l) columns of the ladder's matrices: 32 rows of W by 32
+// pairs (c, d) through LDS, read along d and written along the rows' index.
+template <bool ANTI>
+__global__ __launch_bounds__(256) void ladder_columns_kernel(int v, int64_t pairs, int cols, int o,
+                                                             const double* __restrict__ W, const int* __restrict__ pc,
+                                                             const int* __restrict__ pd, double* __restrict__ S,
+                                                             int64_t lds) {
+  __shared__ double st[kT][kT + 1];
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int64_t q0 = (int64_t)blockIdx.x * kT;
+  const int r0 = blockIdx.y * kT;
+  const int64_t q = q0 + tx, vv = (int64_t)v * v;
+  if (q < pairs) {
+    const int c = pc[q], d = pd[q];
+#pragma unroll
+    for (int e = 0; e < kT; e += 8) {
+      int r = r0 + ty + e;
+      if (r >= cols) break;
+      if (o > 0) {
+        int x, y;
+        if (ANTI) {
+          upair_inverse(r, o - 1, &x, &y);
+          ++y;
+        } else {
+          upair_inverse(r, o, &x, &y);
+        }
+        r = x * o + y;
+      }
+      const double* w = W + r * vv;
+      const double a = w[(int64_t)c * v + d], b = w[(int64_t)d * v + c];
+      st[ty + e][tx] = ANTI ? a - b : c == d ? a : a + b;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kT; e += 8) {
+    const int64_t p = q0 + ty + e;
+    if (p < pairs && r0 + tx < cols) S[p * lds + r0 + tx] = st[tx][ty + e];
+  }
+}
+
+__global__ void fill_columns_kernel(int64_t rows, double* x, int64_t ld, int cols) {
+  const int64_t n = rows * cols;
+  for (int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256)
+    x[e / cols * ld + e % cols] = 0.0;
+}
+
+// One thread per element of Z and of Y (with its W and combinations): a few
+// megabytes, launch-bound (in place of a permutation, and of the reductions
+// of two products split along their 32400-deep sums at v = 180).
+__global__ __launch_bounds__(256) void ladder_unpack_kernel(int o, int v, LadderParts p) {
+  const LadderLayout l = p.l;
+  const int ov = o * v, oo = o * o;
+  const int64_t nz = (int64_t)oo * ov, total = nz + (int64_t)oo * oo;
+  auto Y = [&](int k, int m, int i, int j) {
+    const int lo = min(i, j), hi = max(i, j), kl = min(k, m), kh = max(k, m);
+    double y = p.Rp[opair(lo, hi, o) * l.ldp + l.p2 + ov + upair(kl, kh, o)];
+    if (i != j && k != m && l.ldm > 0) {
+      const double a = p.Rm[opair(lo, hi, o) * l.ldm + l.p2m + ov + spair(kl, kh, o)];
+      y += (i < j) == (k < m) ? a : -a;
+    }
+    return y;
+  };
+  auto K = [&](int k, int i, int m, int j) { return p.Kilj[(((int64_t)k * o + i) * o + m) * o + j]; };
+  for (int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
+    if (e < nz) {
+      const int ij = (int)(e / ov), kb = (int)(e % ov), i = ij / o, j = ij % o;
+      const int64_t row = opair(min(i, j), max(i, j), o);
+      double z = p.Rp[row * l.ldp + l.p2 + kb];
+      if (i != j && l.ldm > 0) {
+        const double a = p.Rm[row * l.ldm + l.p2m + kb];
+        z += i < j ? a : -a;
+      }
+      p.Z[e] = z;
+    } else {
+      const int64_t f = e - nz;
+      const int kl = (int)(f / oo), ij = (int)(f % oo);
+      const int k = kl / o, m = kl % o, i = ij / o, j = ij % o;
+      const double y = Y(k, m, i, j), w = y + K(k, i, m, j);
+      p.Y[f] = y;
+      if (p.Wkl) p.Wkl[f] = w;
+      if (i <= j && k <= m) {
+        const double w2 = Y(m, k, i, j) + K(m, i, k, j);
+        const int64_t row = opair(i, j, o), c = opair(k, m, o);
+        p.Wp[row * l.o2k + c] = k == m ? w : w + w2;
+        if (k == 0 && m == 0 && l.o2k > l.o2) p.Wp[row * l.o2k + l.o2] = 0.0;
+        if (i < j && k < m) p.Wm[row * l.o2mk + c] = w - w2;
+        if (i < j && k == 0 && m == 0 && l.o2mk > l.o2m) p.Wm[row * l.o2mk + l.o2m] = 0.0;
+      }
+    }
   }
 }
 
@@ -400,10 +496,33 @@ __global__ __launch_bounds__(256) void fock_sum_kernel(int naux, int o, FockSum 
 }  // namespace
 
 void ppl_pack_w(int v, int a0, int na, const double* Wblk, const int* pair_a, const int* pair_b, const int* mpair_a,
-                const int* mpair_b, double* S, double* A, hipStream_t s) {
+                const int* mpair_b, double* S, int64_t lds, double* A, int64_t lda, hipStream_t s) {
   const int64_t P2 = (int64_t)v * (v + 1) / 2;
   ppl_pack_w_kernel<<<grid_for(na * (int64_t)v * P2, 32768), 256, 0, s>>>(v, a0, na, Wblk, pair_a, pair_b, mpair_a,
-                                                                          mpair_b, S, A);
+                                                                          mpair_b, S, lds, A, lda);
+  PNK_CHECK_LAUNCH();
+}
+void ladder_columns(int v, int64_t rows, int o, const double* W, const int* pair_a, const int* pair_b,
+                    const int* mpair_a, const int* mpair_b, double* S, int64_t lds, double* A, int64_t lda,
+                    hipStream_t s) {
+  const int64_t p2 = (int64_t)v * (v + 1) / 2, p2m = (int64_t)v * (v - 1) / 2;
+  const int64_t cs = o > 0 ? (int64_t)o * (o + 1) / 2 : rows, ca = o > 0 ? (int64_t)o * (o - 1) / 2 : rows;
+  ladder_columns_kernel<false><<<dim3((unsigned)ceil_div(p2, kT), (unsigned)ceil_div(cs, kT)), 256, 0, s>>>(
+      v, p2, (int)cs, o, W, pair_a, pair_b, S, lds);
+  PNK_CHECK_LAUNCH();
+  if (p2m == 0 || ca == 0) return;
+  ladder_columns_kernel<true><<<dim3((unsigned)ceil_div(p2m, kT), (unsigned)ceil_div(ca, kT)), 256, 0, s>>>(
+      v, p2m, (int)ca, o, W, mpair_a, mpair_b, A, lda);
+  PNK_CHECK_LAUNCH();
+}
+void fill_columns(int64_t rows, double* x, int64_t ld, int64_t cols, hipStream_t s) {
+  if (rows <= 0 || cols <= 0) return;
+  fill_columns_kernel<<<grid_for(rows * cols), 256, 0, s>>>(rows, x, ld, (int)cols);
+  PNK_CHECK_LAUNCH();
+}
+void ladder_unpack(int o, int v, const LadderParts& p, hipStream_t s) {
+  const int64_t oo = (int64_t)o * o;
+  ladder_unpack_kernel<<<grid_for(oo * o * v + oo * oo, 8192), 256, 0, s>>>(o, v, p);
   PNK_CHECK_LAUNCH();
 }
 void amp_layouts(int o, int v, const AmpLayouts& p, hipStream_t s) {

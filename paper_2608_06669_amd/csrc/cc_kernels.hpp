@@ -30,29 +30,60 @@ void jacobi_update(int o, int v, const double* f_oo, const double* f_vv, double 
 // Symmetry-adapted particle-particle ladder. Pairs a <= b are numbered
 // row-major over the upper triangle (p), pairs a < b likewise (p'), and
 // occupied pairs i <= j likewise; pair_a/pair_b map a packed index back.
-// S[p][q] = W_ab,cd + W_ab,dc and A[p'][q'] = W_ab,cd - W_ab,dc for the
-// rows whose a lies in [a0, a0 + na); Wblk[a - a0][b][c][d] = (ac|bd).
+// S[p][q] = W_ab,cd + W_ab,dc (halved for a = b) and A[p'][q'] = W_ab,cd -
+// W_ab,dc (row lengths lds, lda) for the rows whose a lies in [a0, a0 + na);
+// Wblk[a - a0][b][c][d] = (ac|bd).
 void ppl_pack_w(int v, int a0, int na, const double* Wblk, const int* pair_a, const int* pair_b,
-                const int* mpair_a, const int* mpair_b, double* S, double* A, hipStream_t s);
+                const int* mpair_a, const int* mpair_b, double* S, int64_t lds, double* A, int64_t lda, hipStream_t s);
+// S[q][r] = W_r,cd + W_r,dc (half of it for c = d), A[q'][r] = W_r,cd - W_r,dc
+// from W[r][c][d], r < rows. With o > 0 the rows of W are pairs (k, l) of o
+// and the columns run over k <= l (S, row-major) and k < l (A).
+void ladder_columns(int v, int64_t rows, int o, const double* W, const int* pair_a, const int* pair_b,
+                    const int* mpair_a, const int* mpair_b, double* S, int64_t lds, double* A, int64_t lda,
+                    hipStream_t s);
+// x[r][c] = 0, r < rows, c < cols, row length ld
+void fill_columns(int64_t rows, double* x, int64_t ld, int64_t cols, hipStream_t s);
+
+// Lengths of the packed ladder: pairs of virtuals c <= d (p2) and c < d (p2m),
+// of occupied i <= j (o2) and i < j (o2m). T+ and T- have rows of p2k and p2mk
+// and o2k, o2mk of them (zero past the pairs); S, R+ (ldp) and A, R- (ldm) have
+// columns for the pairs, for (k,b) and for k <= l (k < l), then padding.
+struct LadderLayout {
+  int64_t p2, p2m, o2, o2m, p2k, p2mk, ldp, ldm, o2k, o2mk;
+};
+// From the (k,b) and (k,l) columns of R+, R-: Z[(i,j)][(k,b)] = sum_cd (kc|bd)
+// t_ij^cd, Y[(k,l)][(i,j)] = sum_cd (kc|ld) t_ij^cd, W_klij = Kilj[(k,i)][(l,j)] +
+// Y and its combinations Wp[ij][kl] = W_klij + W_lkij (W_kkij once), rows i <= j
+// and o2k columns, Wm = W_klij - W_lkij, i < j, k < l. Wkl (all W) may be null.
+struct LadderParts {
+  LadderLayout l;
+  const double *Rp, *Rm, *Kilj;
+  double *Z, *Y, *Wp, *Wm, *Wkl;
+};
+void ladder_unpack(int o, int v, const LadderParts& p, hipStream_t s);
 
 // Layouts of doubles t[i][j][a][b] (u = 2 t_ij^ab - t_ij^ba):
 struct AmpLayouts {
   const double* t;
   double *Tsia, *Uia;  // [(i,a)][(j,b)]: t_ij^ba, u_ij^ab
-  // Tp[ij][q] = (t_ij^cd + t_ij^dc)/2 (c < d) or t_ij^cc / 2 (c = d), i <= j;
-  // Tm[ij][q'] = (t_ij^cd - t_ij^dc)/2, i < j
+  // Tp[ij][q] = (t_ij^cd + t_ij^dc)/2 (c < d) or diag t_ij^cc (c = d), i <= j;
+  // Tm[ij][q'] = (t_ij^cd - t_ij^dc)/2, i < j; rows zero past the pairs
   double *Tp, *Tm;
+  int64_t ldp, ldm;
+  double diag;
   // (all null: not wanted) [(i,a)][(j,b)]: t_ij^ab; [i][j][a][b]: u_ij^ab, u_ij^ba; [a][i][j][b]: u_ij^ab
   double *Tia, *U, *Uklca, *Uail;
 };
 void amp_layouts(int o, int v, const AmpLayouts& p, hipStream_t s);
 
-// R[i][j][a][b] += E[(i,a)][(j,b)] + V_ij^ab + V_ji^ba + sum_cd (ac|bd) t_ij^cd,
+// R[i][j][a][b] (+)= E[(i,a)][(j,b)] + V_ij^ab + V_ji^ba + sum_cd (ac|bd) t_ij^cd,
 // V_ij^ab = X[i][j][a][b] + T[(i,a)][(j,b)] + S[(j,a)][(i,b)] + w S[(i,a)][(j,b)],
 // the ladder rebuilt from Rp = Tp S, Rm = Tm A; E may be null.
 struct DoublesParts {
   const double *X, *T, *S, *Rp, *Rm, *E;
+  int64_t ldp, ldm;  // row lengths of Rp, Rm
   double w;
+  bool add;  // to what R holds (else R is written)
   double* R;
 };
 void doubles_sum(int o, int v, const DoublesParts& p, hipStream_t s);

@@ -134,10 +134,13 @@ namespace {
 int64_t pad_to(int64_t n, int64_t m) { return (n + m - 1) / m * m; }
 
 struct Sizes {
-  int64_t o, v, naux, np, n, ov, n2, p2, p2m, o2, wna;
+  int64_t o, v, naux, np, n, ov, n2, p2, p2m, o2, o2m, wna;
+  int64_t p2k, p2mk, ldp, ldm, o2k, o2mk;  // padded lengths (LadderLayout)
   explicit Sizes(int o_, int v_, int naux_)
       : o(o_), v(v_), naux(naux_), np(naux_ + 1), n(o_ + v_), ov((int64_t)o_ * v_), n2(ov * ov),
-        p2((int64_t)v_ * (v_ + 1) / 2), p2m((int64_t)v_ * (v_ - 1) / 2), o2((int64_t)o_ * (o_ + 1) / 2) {
+        p2((int64_t)v_ * (v_ + 1) / 2), p2m((int64_t)v_ * (v_ - 1) / 2), o2((int64_t)o_ * (o_ + 1) / 2),
+        o2m((int64_t)o_ * (o_ - 1) / 2), p2k(pad_to(p2, 8)), p2mk(pad_to(p2m, 8)), ldp(pad_to(p2 + ov + o2, 8)),
+        ldm(p2m ? pad_to(p2m + ov + o2m, 8) : 0), o2k(pad_to(o2, 2)), o2mk(pad_to(o2m, 2)) {
     // (ac|bd) is built for blocks of `wna` values of a at a time
     const int64_t v3 = v * v * v;
     wna = std::max<int64_t>(1, std::min<int64_t>(v, (32ll << 20) / v3));
@@ -173,9 +176,9 @@ void for_each_buffer(const Sizes& z, const EngineOptions& opt, F f, G g) {
   // constants
   f(o * o); f(ov); f(v * v); f(n * n); f(n * n); f(naux); f(naux * o * n);
   f(np * o * o); f(np * ov); f(np * ov); f(np * v * v);
-  const int64_t p2 = z.p2, p2m = z.p2m, o2 = z.o2;
-  f(p2 * p2); f(p2m * p2m); f(z.wna * v * v * v); g(4 * (2 * p2 + 2 * p2m));
-  f(o * v * v * v); for (int k = 0; k < 5; ++k) f(n2);
+  const int64_t p2 = z.p2, p2m = z.p2m;
+  f(z.p2k * z.ldp); f(z.p2mk * z.ldm); f(z.wna * v * v * v); g(4 * (2 * p2 + 2 * p2m));
+  for (int k = 0; k < 5; ++k) f(n2);
   if (opt.lowp_f32) {
     g(4 * p2 * pad_to(p2, 4)); g(4 * p2m * pad_to(p2m, 4));
     g(4 * o * v * v * v); g(4 * n2); g(4 * n2); g(4 * n2); g(4 * n2);
@@ -190,13 +193,14 @@ void for_each_buffer(const Sizes& z, const EngineOptions& opt, F f, G g) {
     f(np * o * o); f(np * ov); f(np * v * v); f(naux); f(naux * o * o);
     f(o * o); f(ov); f(v * v);
     for (int k = 0; k < 4; ++k) f(n2);  // Tsia, Uia, Tmp, X
-    f(v * v); f(o * o); f(o * o * o * o); f(o * o * o * o); f(o * o * o * o); f(o * o * ov);
+    f(v * v); f(o * o); f(o * o * o * o); f(o * o * o * o); f(o * o * ov);
     f(n2); f(n2);                       // M, K
     f(naux * ov); f(naux * ov); f(o * o * ov);
-    f(o2 * p2); f(o2 * p2m); f(o2 * p2); f(o2 * p2m);  // Tp, Tm, Rp, Rm
-    if (opt.lowp_f32 || opt.lowp_bf16) {  // Tia, U, Uklca, Uail, J, KilcT
+    f(z.o2k * z.p2k); f(z.o2mk * z.p2mk); f(z.o2 * z.ldp); f(z.o2m * z.ldm);  // Tp, Tm, Rp, Rm
+    f(z.o2 * z.o2k); f(z.o2m * z.o2mk);  // Wp, Wm
+    if (opt.lowp_f32 || opt.lowp_bf16) {  // Tia, U, Uklca, Uail, J, KilcT, Wkl
       for (int k = 0; k < 5; ++k) f(n2);
-      f(o * o * ov);
+      f(o * o * ov); f(o * o * o * o);
     }
   }
   f(reduce_partials_size(64));
@@ -227,11 +231,11 @@ Engine::Engine(int o, int v, int naux, const EngineOptions& opt)
   f_oo_ = take(O * O); f_ov_ = take(OV); f_vv_ = take(V * V); fock_ = take(N * N); h_ = take(N * N); dtr_ = take(NA);
   Lo_ = take(NA * O * N);
   Loo0.v = take(NP * O * O); Lov0.v = take(NP * OV); Lvo0.v = take(NP * OV); Lvv0.v = take(NP * V * V);
-  p2_ = z.p2; p2m_ = z.p2m; o2_ = z.o2; wblk_na_ = (int)z.wna;
-  S.v = take(z.p2 * z.p2); Am.v = take(z.p2m * z.p2m); wblk_ = take(z.wna * V * V * V);
+  lad_ = {z.p2, z.p2m, z.o2, z.o2m, z.p2k, z.p2mk, z.ldp, z.ldm, z.o2k, z.o2mk};
+  wblk_na_ = (int)z.wna;
+  S.v = take(z.p2k * z.ldp); Am.v = take(z.p2mk * z.ldm); wblk_ = take(z.wna * V * V * V);
   pair_a_ = arena_.take<int>(z.p2); pair_b_ = arena_.take<int>(z.p2);
   mpair_a_ = arena_.take<int>(z.p2m); mpair_b_ = arena_.take<int>(z.p2m);
-  Wov.v = take(O * V * V * V);
   Ioovv.v = take(N2); Iovov.v = take(N2); Ix.v = take(N2); Lh.v = take(N2); Itil.v = take(N2);
   // the low-precision ladder tensors keep rows of a 16-byte multiple (the
   // pair counts v(v+1)/2, v(v-1)/2 need not be), for vector loads
@@ -258,16 +262,16 @@ Engine::Engine(int o, int v, int naux, const EngineOptions& opt)
   if (cast_bytes_) cast_ws_ = arena_.take<char>((size_t)cast_bytes_);
   Ten* inter[] = {&Loo, &Lvo, &Lvv, &this->D, &LooT, &Foo, &Fov, &Fvv,
                   &Tsia, &Uia, &Tmp, &X,
-                  &Gv, &Go, &Kilj, &Wkl, &Y, &Z, &M, &K, &Q, &QT, &Kilc,
-                  &Tp, &Tm, &Rp, &Rm,
-                  &Tia, &U, &Uklca, &Uail, &J, &KilcT};
+                  &Gv, &Go, &Kilj, &Y, &Z, &M, &K, &Q, &QT, &Kilc,
+                  &Tp, &Tm, &Rp, &Rm, &Wp, &Wm,
+                  &Tia, &U, &Uklca, &Uail, &J, &KilcT, &Wkl};
   const int64_t isz[] = {NP * O * O, NP * OV, NP * V * V, NA, NA * O * O, O * O, OV, V * V,
                          N2, N2, N2, N2,
-                         V * V, O * O, O * O * O * O, O * O * O * O, O * O * O * O, O * O * OV, N2, N2,
+                         V * V, O * O, O * O * O * O, O * O * O * O, O * O * OV, N2, N2,
                          NA * OV, NA * OV, O * O * OV,
-                         z.o2 * z.p2, z.o2 * z.p2m, z.o2 * z.p2, z.o2 * z.p2m,
-                         N2, N2, N2, N2, N2, O * O * OV};
-  const size_t nlow = opt.lowp_f32 || opt.lowp_bf16 ? 0 : 6;  // the last six: FP32 / BF16 only
+                         z.o2k * z.p2k, z.o2mk * z.p2mk, z.o2 * z.ldp, z.o2m * z.ldm, z.o2 * z.o2k, z.o2m * z.o2mk,
+                         N2, N2, N2, N2, N2, O * O * OV, O * O * O * O};
+  const size_t nlow = opt.lowp_f32 || opt.lowp_bf16 ? 0 : 7;  // the last seven: FP32 / BF16 only
   static_assert(sizeof(inter) / sizeof(inter[0]) == sizeof(isz) / sizeof(isz[0]), "buffer table");
   for (int rep = 0; rep < 2; ++rep)
     for (size_t k = 0; k + nlow < sizeof(isz) / sizeof(isz[0]); ++k) {
@@ -507,22 +511,32 @@ void Engine::prepare(const ProblemView& p, hipStream_t s, bool with_eigen) {
   extract_occ_rows(naux, o, n, p.L, Lo_, s);
   gemm64(with_ws(gd(n, n, naux * o, 1, n, n, 1, n, 1, 1.0, 1.0)), Lo_, Lo_, h_, s);
   extract_blocks(naux, o, v, p.L, h_, Loo0.v, Lov0.v, Lvo0.v, Lvv0.v, s);
+  const int64_t p2 = lad_.p2, p2m = lad_.p2m, ldp = lad_.ldp, ldm = lad_.ldm;
+  // zero padding the products run over
+  fill(lad_.p2k * ldp - p2 * ldp, 0.0, S.v + p2 * ldp, s);
+  fill(lad_.p2mk * ldm - p2m * ldm, 0.0, Am.v + p2m * ldm, s);
+  for (Ten* t : {&Tp, &Tm}) {
+    const bool sym = t == &Tp;
+    const int64_t row = sym ? lad_.p2k : lad_.p2mk, r0 = sym ? lad_.o2 : lad_.o2m, r1 = sym ? lad_.o2k : lad_.o2mk;
+    fill((r1 - r0) * row, 0.0, t->v + r0 * row, s);
+    fill((r1 - r0) * row, 0.0, t->d + r0 * row, s);
+  }
   // symmetry-adapted (ac|bd): pair tables, then blocks of a at a time:
   // Wblk[a - a0][b][c][d] = sum_P L_ac L_bd (batch b0 = b, b1 = a - a0),
-  // packed into S (a <= b, c <= d) and A (a < b, c < d)
+  // packed into S (a <= b, c <= d; rows a = b halved) and A (a < b, c < d)
   {
-    std::vector<int> pa(p2_), pb(p2_), ma(std::max<int64_t>(p2m_, 1)), mb(std::max<int64_t>(p2m_, 1));
+    std::vector<int> pa(p2), pb(p2), ma(std::max<int64_t>(p2m, 1)), mb(std::max<int64_t>(p2m, 1));
     int64_t k = 0, km = 0;
     for (int a = 0; a < v; ++a)
       for (int b = a; b < v; ++b) {
         pa[k] = a; pb[k] = b; ++k;
         if (b > a) { ma[km] = a; mb[km] = b; ++km; }
       }
-    PNK_HIP(hipMemcpyAsync(pair_a_, pa.data(), p2_ * sizeof(int), hipMemcpyHostToDevice, s));
-    PNK_HIP(hipMemcpyAsync(pair_b_, pb.data(), p2_ * sizeof(int), hipMemcpyHostToDevice, s));
-    if (p2m_ > 0) {
-      PNK_HIP(hipMemcpyAsync(mpair_a_, ma.data(), p2m_ * sizeof(int), hipMemcpyHostToDevice, s));
-      PNK_HIP(hipMemcpyAsync(mpair_b_, mb.data(), p2m_ * sizeof(int), hipMemcpyHostToDevice, s));
+    PNK_HIP(hipMemcpyAsync(pair_a_, pa.data(), p2 * sizeof(int), hipMemcpyHostToDevice, s));
+    PNK_HIP(hipMemcpyAsync(pair_b_, pb.data(), p2 * sizeof(int), hipMemcpyHostToDevice, s));
+    if (p2m > 0) {
+      PNK_HIP(hipMemcpyAsync(mpair_a_, ma.data(), p2m * sizeof(int), hipMemcpyHostToDevice, s));
+      PNK_HIP(hipMemcpyAsync(mpair_b_, mb.data(), p2m * sizeof(int), hipMemcpyHostToDevice, s));
     }
     PNK_HIP(hipStreamSynchronize(s));  // host tables go out of scope
     for (int a0 = 0; a0 < v; a0 += wblk_na_) {
@@ -533,17 +547,23 @@ void Engine::prepare(const ProblemView& p, hipStream_t s, bool with_eigen) {
       d.b_b0 = v; d.b_b1 = 0;
       d.c_b0 = vv; d.c_b1 = vv * v;
       gemm64(with_ws(d), Lvv0.v + (int64_t)a0 * v, Lvv0.v, wblk_, s);
-      ppl_pack_w(v, a0, na, wblk_, pair_a_, pair_b_, mpair_a_, mpair_b_, S.v, Am.v, s);
+      ppl_pack_w(v, a0, na, wblk_, pair_a_, pair_b_, mpair_a_, mpair_b_, S.v, ldp, Am.v, ldm, s);
     }
   }
-  // Wov[k][b][c][d] = (kc|bd)
-  {
+  // further columns: (kc|bd) +- (kd|bc), blocks of k at a time through
+  // Wblk[k - k0][b][c][d] = (kc|bd)
+  for (int k0 = 0; k0 < o; k0 += wblk_na_) {
+    const int nk = std::min(wblk_na_, o - k0);
     GemmDesc d = gd(v, v, naux, 1, ov, vv, 1, v, 1);
-    d.nb0 = v; d.nb1 = o;
+    d.nb0 = v; d.nb1 = nk;
     d.a_b0 = 0; d.a_b1 = v;
     d.b_b0 = v; d.b_b1 = 0;
     d.c_b0 = vv; d.c_b1 = vv * v;
-    gemm64(with_ws(d), Lov0.v, Lvv0.v, Wov.v, s);
+    gemm64(with_ws(d), Lov0.v + (int64_t)k0 * v, Lvv0.v, wblk_, s);
+    const int64_t r0 = (int64_t)k0 * v, nr = (int64_t)nk * v;
+    ladder_columns(v, nr, 0, wblk_, pair_a_, pair_b_, mpair_a_, mpair_b_, S.v + p2 + r0, ldp, Am.v + p2m + r0, ldm, s);
+    if (Wov.lp32) cast_f64_to_f32(nr * vv, wblk_, (float*)Wov.lp32 + r0 * vv, s);
+    if (Wov.lp16) cast_f64_to_bf16_rows(nr, vv, ldw16_, wblk_, vv, (uint16_t*)Wov.lp16 + r0 * ldw16_, s);
   }
   // Ioovv[k][l][c][d] = (kc|ld)
   {
@@ -554,6 +574,11 @@ void Engine::prepare(const ProblemView& p, hipStream_t s, bool with_eigen) {
     d.c_b0 = vv; d.c_b1 = vv * o;
     gemm64(with_ws(d), Lov0.v, Lov0.v, Ioovv.v, s);
   }
+  // the last columns: (kc|ld) +- (kd|lc), k <= l
+  ladder_columns(v, (int64_t)o * o, o, Ioovv.v, pair_a_, pair_b_, mpair_a_, mpair_b_, S.v + p2 + ov, ldp,
+                 Am.v + p2m + ov, ldm, s);
+  fill_columns(p2, S.v + p2 + ov + lad_.o2, ldp, ldp - (p2 + ov + lad_.o2), s);
+  if (p2m > 0) fill_columns(p2m, Am.v + p2m + ov + lad_.o2m, ldm, ldm - (p2m + ov + lad_.o2m), s);
   // Iovov[(k,c)][(l,d)] = (kc|ld); Ix[l][d][k][c] = (kd|lc)
   gemm64(with_ws(gd((int)ov, (int)ov, naux, 1, ov, ov, 1, ov, 1)), Lov0.v, Lov0.v, Iovov.v, s);
   {
@@ -571,22 +596,20 @@ void Engine::prepare(const ProblemView& p, hipStream_t s, bool with_eigen) {
     }
   }
   // the ladder tensors with padded rows, the others flat
-  if (S.lp32) cast_f64_to_f32_rows(p2_, p2_, ld32_, S.v, (float*)S.lp32, s);
-  if (S.lp16) cast_f64_to_bf16_rows(p2_, p2_, ld16_, S.v, (uint16_t*)S.lp16, s);
-  if (Am.lp32) cast_f64_to_f32_rows(p2m_, p2m_, ld32m_, Am.v, (float*)Am.lp32, s);
-  if (Am.lp16) cast_f64_to_bf16_rows(p2m_, p2m_, ld16m_, Am.v, (uint16_t*)Am.lp16, s);
-  if (Wov.lp32) cast_f64_to_f32((int64_t)o * v * vv, Wov.v, (float*)Wov.lp32, s);
+  if (S.lp32) cast_f64_to_f32_rows(p2, p2, ld32_, S.v, ldp, (float*)S.lp32, s, pair_a_, pair_b_);
+  if (S.lp16) cast_f64_to_bf16_rows(p2, p2, ld16_, S.v, ldp, (uint16_t*)S.lp16, s, pair_a_, pair_b_);
+  if (Am.lp32) cast_f64_to_f32_rows(p2m, p2m, ld32m_, Am.v, ldm, (float*)Am.lp32, s);
+  if (Am.lp16) cast_f64_to_bf16_rows(p2m, p2m, ld16m_, Am.v, ldm, (uint16_t*)Am.lp16, s);
   for (Ten* t : {&Ioovv, &Iovov, &Ix})
     if (t->lp32) cast_f64_to_f32(n2_, t->v, (float*)t->lp32, s);
   if (Ioovv.lp16) cast_f64_to_bf16(n2_, Ioovv.v, (uint16_t*)Ioovv.lp16, s);
-  if (Wov.lp16) cast_f64_to_bf16_rows(ov, (int64_t)v * v, ldw16_, Wov.v, (uint16_t*)Wov.lp16, s);
   if (Iovov.lp16) {
-    cast_f64_to_bf16_rows(ov, ov, ldov16_, Iovov.v, (uint16_t*)Iovov.lp16, s);
+    cast_f64_to_bf16_rows(ov, ov, ldov16_, Iovov.v, ov, (uint16_t*)Iovov.lp16, s);
     // Ix^T[(k,c)][(l,d)] = Ix[(l,d)][(k,c)] = (kd|lc), staged in Tmp
     const int dims[4] = {o, v, o, v};
     const int pm[4] = {0, 3, 2, 1};
     permute4(Iovov.v, Tmp.v, dims, pm, 1.0, 0.0, s);
-    cast_f64_to_bf16_rows(ov, ov, ldov16_, Tmp.v, (uint16_t*)Ix.lp16, s);
+    cast_f64_to_bf16_rows(ov, ov, ldov16_, Tmp.v, ov, (uint16_t*)Ix.lp16, s);
   }
   fill(ov_ + n2_, 0.0, zeros_, s);
   // f_ov == 0 lets A_F skip its singles-doubles coupling
@@ -628,7 +651,8 @@ void Engine::run(Mode m) {
     AmpLayouts p{};
     p.t = out(T2);
     p.Tsia = out(Tsia); p.Uia = out(Uia);
-    p.Tp = out(Tp); p.Tm = out(Tm);
+    p.Tp = out(Tp); p.Tm = out(Tm); p.ldp = lad_.p2k; p.ldm = lad_.p2mk;
+    p.diag = lowp ? 0.5 : 1.0;  // (FP64 has the half in S)
     // (an FP64 tangent has no use for the others)
     if (lowp_engine && (lowp || mode_ == Mode::Value)) {
       p.Tia = out(Tia); p.U = out(U); p.Uklca = out(Uklca); p.Uail = out(Uail);
@@ -636,36 +660,60 @@ void Engine::run(Mode m) {
     amp_layouts(o, v, p, s_);
   }
 
-  // ---- particle-particle ladder, symmetry-adapted: for i <= j and the
-  // (anti)symmetric combinations of c,d, R+ = T+ S, R- = T- A ----
-  {
+  // ---- ladders, symmetry-adapted: for i <= j and the (anti)symmetric
+  // combinations of c,d, R+ = T+ S, R- = T- A (the antisymmetric pairs over
+  // i < j only: t_ii^cd = t_ii^dc) ----
+  const int64_t P2 = lad_.p2, P2m = lad_.p2m, p2k = lad_.p2k, p2mk = lad_.p2mk, ldp = lad_.ldp, ldm = lad_.ldm;
+  const int O2 = (int)lad_.o2, O2m = (int)lad_.o2m;
+  const bool anti = P2m > 0 && O2m > 0;
+  mm(gd(OO, OO, naux, 1, oo, oo, 1, oo, 1), Loo, Loo, Kilj);       // (ki|lj)~ as [(k,i)][(l,j)]
+  if (lowp) {
     // S and A are symmetric matrices: read them along the contiguous index
-    // the compute type stages best (n for FP64/FP32, k for BF16)
-    const bool kc = mode_ == Mode::Tangent && jprec_ == Prec::BF16;
-    const int P2 = (int)p2_, P2m = (int)p2m_, O2 = (int)o2_, O2m = o_ * (o_ - 1) / 2;
-    // row length of the copy the product reads (padded in FP32 / BF16)
-    const bool t32 = mode_ == Mode::Tangent && jprec_ == Prec::F32;
-    const int64_t ls = kc && S.lp16 ? ld16_ : (t32 && S.lp32 ? ld32_ : p2_);
-    const int64_t lm = kc && Am.lp16 ? ld16m_ : (t32 && Am.lp32 ? ld32m_ : p2m_);
+    // the compute type stages best (n for FP32, k for BF16, whose copies'
+    // rows are zero to their length, so that the packed amplitudes may run
+    // the contraction over whole panels)
+    const bool kc = jprec_ == Prec::BF16;
+    const int64_t ls = kc ? ld16_ : ld32_, lm = kc ? ld16m_ : ld32m_;
     if (timers_) timers_->begin(kTimerPPL, s_);
-    // (the BF16 copies' rows are zero from P2 to their length: the packed
-    // amplitudes may run the contraction over whole panels)
-    GemmDesc gs = gd(O2, P2, P2, p2_, 1, kc ? 1 : ls, kc ? ls : 1, p2_, 1);
-    if (kc && S.lp16) gs.b_kzero = ld16_;
+    GemmDesc gs = gd(O2, (int)P2, (int)P2, p2k, 1, kc ? 1 : ls, kc ? ls : 1, ldp, 1);
+    if (kc) gs.b_kzero = ld16_;
     mm(gs, Tp, S, Rp);
-    // the antisymmetric pairs over i < j only (t_ii^cd = t_ii^dc)
-    if (P2m > 0 && O2m > 0) {
-      GemmDesc ga = gd(O2m, P2m, P2m, p2m_, 1, kc ? 1 : lm, kc ? lm : 1, p2m_, 1);
-      if (kc && Am.lp16) ga.b_kzero = ld16m_;
+    if (anti) {
+      GemmDesc ga = gd(O2m, (int)P2m, (int)P2m, p2mk, 1, kc ? 1 : lm, kc ? lm : 1, ldm, 1);
+      if (kc) ga.b_kzero = ld16m_;
       mm(ga, Tm, Am, Rm);
     }
     if (timers_) timers_->end(kTimerPPL, s_);
+    // hole-hole ladder
+    mm(gd(OO, OO, VV, vv, 1, 1, vv, oo, 1), Ioovv, T2, Y);         // Y[(k,l)][(i,j)]
+    perm(Kilj, Wkl, o, o, o, o, 0, 2, 1, 3, 1.0, 1.0, &Y);         // [(k,l)][(i,j)]
+    mm(gd(OO, VV, OO, 1, oo, vv, 1, vv, 1), Wkl, T2, R2);
+    // T1 part of the dressed ladder, Z[(i,j)][(k,b)]; BF16 reads the padded
+    // copy of Wov
+    GemmDesc gz = gd(OO, OV, VV, vv, 1, 1, kc ? ldw16_ : vv, ov, 1);
+    if (kc) gz.b_kzero = ldw16_;
+    mm(gz, T2, Wov, Z);
+  } else {
+    // further columns of S and A give Z and Y at half and a quarter of their
+    // flops, and W_klij t_kl^ab acts on the pair combinations as well
+    const double count = mm_flops_;
+    if (timers_) timers_->begin(kTimerPPL, s_);
+    mm(gd(O2, (int)ldp, (int)p2k, p2k, 1, ldp, 1, ldp, 1), Tp, S, Rp);
+    if (anti) mm(gd(O2m, (int)ldm, (int)p2mk, p2mk, 1, ldm, 1, ldm, 1), Tm, Am, Rm);
+    if (timers_) timers_->end(kTimerPPL, s_);
+    LadderParts p{};
+    p.l = lad_;
+    p.Rp = out(Rp); p.Rm = out(Rm); p.Kilj = out(Kilj);
+    p.Z = out(Z); p.Y = out(Y); p.Wp = out(Wp); p.Wm = out(Wm);
+    p.Wkl = lowp_engine && mode_ == Mode::Value ? Wkl.v : nullptr;
+    ladder_unpack(o, v, p, s_);
+    // (columns past the pairs, whose Z and Y have been read, run along)
+    mm(gd(O2, (int)p2k, (int)lad_.o2k, lad_.o2k, 1, p2k, 1, ldp, 1, 1.0, 1.0), Wp, Tp, Rp);
+    if (anti) mm(gd(O2m, (int)p2mk, (int)lad_.o2mk, lad_.o2mk, 1, p2mk, 1, ldm, 1, 1.0, 1.0), Wm, Tm, Rm);
+    // (counted in the form with whole Z, Y and W)
+    mm_flops_ = count + 2.0 * O2 * P2 * P2 + 2.0 * O2m * P2m * P2m + 2.0 * oo * oo * vv + 2.0 * oo * vv * ov +
+                2.0 * oo * oo * vv * (mode_ == Mode::Value ? 1.0 : 2.0);
   }
-  // ---- hole-hole ladder ----
-  mm(gd(OO, OO, VV, vv, 1, 1, vv, oo, 1), Ioovv, T2, Y);           // Y[(k,l)][(i,j)]
-  mm(gd(OO, OO, naux, 1, oo, oo, 1, oo, 1), Loo, Loo, Kilj);       // [(k,i)][(l,j)]
-  perm(Kilj, Wkl, o, o, o, o, 0, 2, 1, 3, 1.0, 1.0, &Y);           // [(k,l)][(i,j)]
-  mm(gd(OO, VV, OO, 1, oo, vv, 1, vv, 1), Wkl, T2, R2);
 
   // ---- Fock-type intermediates, Gv as [c][b] ----
   if (lowp) {
@@ -681,13 +729,6 @@ void Engine::run(Mode m) {
   mm(batch0(gd(o, VV, o, 1, o, vv, 1, vv, 1, -1.0, 1.0), o, 0, O * vv, O * vv), Go, T2, X);
 
   // ---- T1 part of the dressed ladder ----
-  {
-    // Z[(i,j)][(k,b)]; BF16 tangents read the padded BF16 copy of Wov
-    const bool kcw = mode_ == Mode::Tangent && jprec_ == Prec::BF16 && Wov.lp16;
-    GemmDesc gz = gd(OO, OV, VV, vv, 1, 1, kcw ? ldw16_ : vv, ov, 1);
-    if (kcw) gz.b_kzero = ldw16_;
-    mm(gz, T2, Wov, Z);
-  }
   mm(batch0(gd(OO, v, o, 1, oo, v, 1, ov, 1, -0.5, 1.0), o, O * oo, 0, v), Y, T1, Z);
   mm(batch0(gd(v, v, o, 1, v, v, 1, v, 1, -1.0, 1.0), OO, 0, ov, vv), T1, Z, X);
 
@@ -731,13 +772,13 @@ void Engine::run(Mode m) {
     mm(g0, Lvo, Lov0, M, &K, 0, -0.5);
     mm(scaled(g1, 0.5, 1.0), Uia, Lh, M);
     mm(scaled(g1, -0.5, 1.0), Tsia, Ix, K);
-    mm(scaled(g0, 0.5, 0.0), Lvo, Lvo, Tmp);                       // (ai|bj)~ / 2, doubled by the pair sum
-    mm(scaled(gT, 1.0, 1.0), M, Uia, Tmp);
-    mm_flops_ += (mode_ == Mode::Value ? 2 : 3) * 2.0 * ov * ov * ov;  // (counted in the six-product form)
     if (lowp_engine && mode_ == Mode::Value) {
       const int dims[4] = {o, v, o, v}, same[4] = {0, 1, 2, 3};
       permute4(K.v, J.v, dims, same, 0.5, 1.0, s_, M.v);
     }
+    mm(scaled(g0, 0.5, 0.0), Lvo, Lvo, Tmp);                       // (ai|bj)~ / 2, doubled by the pair sum
+    mm(scaled(gT, 1.0, 1.0), M, Uia, Tmp);
+    mm_flops_ += (mode_ == Mode::Value ? 2 : 3) * 2.0 * ov * ov * ov;  // (counted in the six-product form)
     mm(scaled(gT, -1.0, 0.0), K, Tsia, KT);
     w = 0.5;
   }
@@ -745,7 +786,8 @@ void Engine::run(Mode m) {
   // ---- r2 ----
   {
     DoublesParts p{};
-    p.X = out(X); p.T = out(Tmp); p.S = out(KT); p.w = w; p.Rp = out(Rp); p.Rm = out(Rm);
+    p.X = out(X); p.T = out(Tmp); p.S = out(KT); p.w = w; p.Rp = out(Rp); p.Rm = out(Rm); p.ldp = ldp; p.ldm = ldm;
+    p.add = lowp;
     p.E = E ? out(*E) : nullptr;
     p.R = out(R2);
     doubles_sum(o, v, p, s_);

@@ -20,6 +20,7 @@
 #include <memory>
 #include <vector>
 
+#include "cc_kernels.hpp"
 #include "common.hpp"
 #include "fock_op.hpp"
 #include "gemm.hpp"
@@ -180,7 +181,7 @@ class Engine {
   int *pair_a_, *pair_b_, *mpair_a_, *mpair_b_;
   double* wblk_;
   int wblk_na_;
-  int64_t p2_, p2m_, o2_;
+  LadderLayout lad_;
   int64_t ld32_ = 0, ld32m_ = 0, ld16_ = 0, ld16m_ = 0;  // row lengths of the low-precision ladder copies
   int64_t ldov16_ = 0;  // row length of the BF16 ring integrals (read along k)
   int64_t ldw16_ = 0;   // row length of the BF16 copy of Wov
@@ -191,9 +192,9 @@ class Engine {
   // Gv are transposed too)
   Ten Loo, Lvo, Lvv, D, LooT, Foo, Fov, Fvv;
   Ten Tsia, Uia;
-  Ten Tia, U, Uklca, Uail, J, KilcT;  // for FP32 / BF16 products only
-  Ten Tmp, X, Gv, Go, Kilj, Wkl, Y, Z, M, K, Q, QT, Kilc;
-  Ten Tp, Tm, Rp, Rm;
+  Ten Tia, U, Uklca, Uail, J, KilcT, Wkl;  // for FP32 / BF16 products only
+  Ten Tmp, X, Gv, Go, Kilj, Y, Z, M, K, Q, QT, Kilc;
+  Ten Tp, Tm, Rp, Rm, Wp, Wm;
   double* partials_;
   double* zeros_;  // zero t-vector for the residual at t = 0
   Timers* timers_ = nullptr;

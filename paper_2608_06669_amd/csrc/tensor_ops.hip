@@ -120,14 +120,17 @@ __global__ void cast_bf16_kernel(int64_t n, const double* __restrict__ x, uint16
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = f32_to_bf16_rne((float)x[i]);
 }
-// rows x cols row-major (row length cols) to rows of length ld >= cols; the
-// ld - cols padding elements of each row are zero
+// rows x cols (row length ldx) to rows of length ld >= cols; the ld - cols
+// padding elements of each row are zero. Rows r with pa[r] = pb[r] (where
+// given) are doubled.
 template <typename T>
-__global__ void cast_rows_kernel(int64_t rows, int64_t cols, int64_t ld, const double* __restrict__ x, T* __restrict__ y) {
+__global__ void cast_rows_kernel(int64_t rows, int64_t cols, int64_t ld, const double* __restrict__ x, int64_t ldx,
+                                 T* __restrict__ y, const int* __restrict__ pa, const int* __restrict__ pb) {
   const int64_t n = rows * ld;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t r = i / ld, c = i - r * ld;
-    const double v = c < cols ? x[r * cols + c] : 0.0;
+    double v = c < cols ? x[r * ldx + c] : 0.0;
+    if (pa && pa[r] == pb[r]) v *= 2.0;
     if constexpr (sizeof(T) == 2) y[i] = f32_to_bf16_rne((float)v);
     else y[i] = (float)v;
   }
@@ -408,14 +411,16 @@ void cast_f64_to_bf16(int64_t n, const double* x, uint16_t* y, hipStream_t s) {
   cast_bf16_kernel<<<grid_for(n, 16384), 256, 0, s>>>(n, x, y);
   PNK_CHECK_LAUNCH();
 }
-void cast_f64_to_f32_rows(int64_t rows, int64_t cols, int64_t ld, const double* x, float* y, hipStream_t s) {
+void cast_f64_to_f32_rows(int64_t rows, int64_t cols, int64_t ld, const double* x, int64_t ldx, float* y, hipStream_t s,
+                           const int* pa, const int* pb) {
   if (rows <= 0 || cols <= 0) return;
-  cast_rows_kernel<float><<<grid_for(rows * ld, 16384), 256, 0, s>>>(rows, cols, ld, x, y);
+  cast_rows_kernel<float><<<grid_for(rows * ld, 16384), 256, 0, s>>>(rows, cols, ld, x, ldx, y, pa, pb);
   PNK_CHECK_LAUNCH();
 }
-void cast_f64_to_bf16_rows(int64_t rows, int64_t cols, int64_t ld, const double* x, uint16_t* y, hipStream_t s) {
+void cast_f64_to_bf16_rows(int64_t rows, int64_t cols, int64_t ld, const double* x, int64_t ldx, uint16_t* y, hipStream_t s,
+                           const int* pa, const int* pb) {
   if (rows <= 0 || cols <= 0) return;
-  cast_rows_kernel<uint16_t><<<grid_for(rows * ld, 16384), 256, 0, s>>>(rows, cols, ld, x, y);
+  cast_rows_kernel<uint16_t><<<grid_for(rows * ld, 16384), 256, 0, s>>>(rows, cols, ld, x, ldx, y, pa, pb);
   PNK_CHECK_LAUNCH();
 }
 
