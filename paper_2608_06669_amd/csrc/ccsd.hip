@@ -733,7 +733,16 @@ void Engine::run(Mode m) {
   mm(batch0(gd(v, v, o, 1, v, v, 1, v, 1, -1.0, 1.0), OO, 0, ov, vv), T1, Z, X);
 
   // ---- ring terms, rows and columns (i,a) ----
-  mm(gd(OO, VV, naux, 1, oo, vv, 1, vv, 1), Loo, Lvv, Tmp);        // (ki|ac)~ as [(k,i)][(c,a)]
+  // Engines that offer FP32 products keep J and K, the largest values these
+  // round, as sums in ascending k from 1024 rows on (where such products
+  // still fill the chip): a last bit that depended on the tiles would move
+  // some FP32 results by an FP32 rounding.
+  const bool f32_values = opt_.lowp_f32 && mode_ == Mode::Value && ov >= 1024;
+  auto piece = [&](GemmDesc g) {
+    g.ascending = f32_values;
+    return g;
+  };
+  mm(piece(gd(OO, VV, naux, 1, oo, vv, 1, vv, 1)), Loo, Lvv, Tmp); // (ki|ac)~ as [(k,i)][(c,a)]
   perm(Tmp, K, o, o, v, v, 1, 3, 0, 2, 1.0, 0.0);                  // [(i,a)][(k,c)]
   const GemmDesc g0 = gd(OV, OV, naux, 1, ov, ov, 1, ov, 1), g1 = gd(OV, OV, OV, ov, 1, ov, 1, ov, 1),
                  gT = gd(OV, OV, OV, ov, 1, 1, ov, ov, 1);
@@ -769,12 +778,19 @@ void Engine::run(Mode m) {
     //   J u - K t = M u - K s / 2,
     //   M = (ai|kc)~ - (ki|ac)~ / 2 + u ((kc|ld) - (kd|lc) / 2) / 2:
     // four products of ring size (six in a tangent) in place of six (nine)
-    mm(g0, Lvo, Lov0, M, &K, 0, -0.5);
-    mm(scaled(g1, 0.5, 1.0), Uia, Lh, M);
-    mm(scaled(g1, -0.5, 1.0), Tsia, Ix, K);
-    if (lowp_engine && mode_ == Mode::Value) {
-      const int dims[4] = {o, v, o, v}, same[4] = {0, 1, 2, 3};
-      permute4(K.v, J.v, dims, same, 0.5, 1.0, s_, M.v);
+    const int dims[4] = {o, v, o, v}, same[4] = {0, 1, 2, 3};
+    if (f32_values) {
+      mm(piece(g0), Lvo, Lov0, J);
+      mm(piece(scaled(g1, 0.5, 1.0)), Uia, Iovov, J);
+      mm(piece(scaled(g1, -0.5, 1.0)), Tia, Ix, J);
+      mm(piece(scaled(g1, -0.5, 1.0)), Tsia, Ix, K);
+      permute4(K.v, M.v, dims, same, -0.5, 1.0, s_, J.v);
+      mm_flops_ -= 2.0 * ov * ov * ov;
+    } else {
+      mm(g0, Lvo, Lov0, M, &K, 0, -0.5);
+      mm(scaled(g1, 0.5, 1.0), Uia, Lh, M);
+      mm(scaled(g1, -0.5, 1.0), Tsia, Ix, K);
+      if (lowp_engine && mode_ == Mode::Value) permute4(K.v, J.v, dims, same, 0.5, 1.0, s_, M.v);
     }
     mm(scaled(g0, 0.5, 0.0), Lvo, Lvo, Tmp);                       // (ai|bj)~ / 2, doubled by the pair sum
     mm(scaled(gT, 1.0, 1.0), M, Uia, Tmp);

@@ -763,14 +763,15 @@ void launch_f64_layout(const f64pipe::Args& p, bool vec, unsigned grid, hipStrea
 }
 
 template <int BN>
-void launch_f64_tiles(f64pipe::Args p, const F64Layout& la, const F64Layout& lb, int64_t nb, int64_t ws_elems, hipStream_t s) {
+void launch_f64_tiles(f64pipe::Args p, const F64Layout& la, const F64Layout& lb, int64_t nb, int64_t ws_elems, bool asc,
+                      hipStream_t s) {
   const bool vec = la.vec && lb.vec;
   p.tm = (int)ceil_div(p.M, 64);
   p.tn = (int)ceil_div(p.N, BN);
   p.wr = std::min(p.M, 64);
   p.wc = std::min(p.N, BN);
   const int64_t tiles = (int64_t)p.tm * p.tn * nb;
-  const F64Plan plan = f64_plan(tiles, BN, p.K, (int64_t)p.wr * p.wc, ws_elems, vec, p.A2 != nullptr);
+  const F64Plan plan = asc ? F64Plan{tiles, 1} : f64_plan(tiles, BN, p.K, (int64_t)p.wr * p.wc, ws_elems, vec, p.A2 != nullptr);
   PNK_REQUIRE(tiles * plan.ts < (int64_t(1) << 31), "gemm: batch too large");
   p.kchunk = plan.ts > 1 ? (int)(ceil_div(ceil_div(p.K, plan.ts), 8) * 8) : p.K;
   p.ts = (int)ceil_div(p.K, p.kchunk);  // no empty chunk
@@ -778,7 +779,10 @@ void launch_f64_tiles(f64pipe::Args p, const F64Layout& la, const F64Layout& lb,
   p.ntail = (int)(tiles - p.nfull);
   const unsigned grid = (unsigned)(p.nfull + (int64_t)p.ntail * p.ts);
   if (la.kc && lb.kc) launch_f64_layout<BN, true, true>(p, vec, grid, s);
-  else if (la.kc) launch_f64_layout<BN, true, false>(p, vec, grid, s);
+  else if (la.kc && BN == 64 && asc) {
+    if (vec) f64pipe::gemm_f64_pipe<64, 64, true, false, true, true><<<grid, 256, 0, s>>>(p);
+    else f64pipe::gemm_f64_pipe<64, 64, true, false, false, true><<<grid, 256, 0, s>>>(p);
+  } else if (la.kc) launch_f64_layout<BN, true, false>(p, vec, grid, s);
   else if (lb.kc) launch_f64_layout<BN, false, true>(p, vec, grid, s);
   else launch_f64_layout<BN, false, false>(p, vec, grid, s);
   PNK_CHECK_LAUNCH();
@@ -814,9 +818,10 @@ bool launch_f64(const GemmDesc& d, const double* A, const double* B, const doubl
   // 400 x 3600 x 32400 1692 against 1767. Below about 1e10 multiplications
   // their coarser rounds cost more than that (600 x 3600 x 3600 306 against
   // 292 us).
-  const bool wide = d.K >= 2048 && (double)d.M * d.N * d.K * nb >= 1e10;
-  if (wide) launch_f64_tiles<128>(p, la, lb, nb, ws, s);
-  else launch_f64_tiles<64>(p, la, lb, nb, ws, s);
+  const bool asc = d.ascending && !lb.kc;
+  const bool wide = !asc && d.K >= 2048 && (double)d.M * d.N * d.K * nb >= 1e10;
+  if (wide) launch_f64_tiles<128>(p, la, lb, nb, ws, asc, s);
+  else launch_f64_tiles<64>(p, la, lb, nb, ws, asc, s);
   return true;
 }
 

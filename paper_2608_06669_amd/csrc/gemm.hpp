@@ -23,6 +23,9 @@ struct GemmDesc {
   int64_t c_m = 0, c_n = 0, c_b0 = 0, c_b1 = 0;
   double alpha = 1.0, beta = 0.0;
   const double* Cin = nullptr;  // C = alpha A B + beta Cin, at C's strides (null: C itself)
+  // FP64, B contiguous along n: sums in one piece and, from the first multiple
+  // of 8 on, in ascending k, whatever the tiles
+  bool ascending = false;
   // Optional scratch for split-K: products with too few output tiles to
   // fill the GPU split the contraction into S chunks whose partial sums go
   // here and are then added in a fixed order (deterministic). Needs S *

@@ -63,3 +63,26 @@ def test_low_precision_tangent(handle, o, v, naux, prec, rel):
     want = ccsd.jvp_complex_step(p.f_oo, p.f_ov, p.f_vv, p.L, t1, t2, v1, v2)
     num = sum(np.sum((g.cpu().numpy() - w) ** 2) for g, w in zip(got, want))
     assert np.sqrt(num / sum(np.sum(w ** 2) for w in want)) < rel
+
+
+@pytest.mark.parametrize("o,v,naux", [(8, 128, 40), (9, 115, 33)])
+def test_values_for_fp32_products(o, v, naux):
+    """From o v = 1024 on, an engine with FP32 copies forms J and K in another
+    order than others: the same residual (1e-12 of the largest component, both
+    sums of a few thousand terms in FP64), and FP32 J v near the FP64 one."""
+    import paper_2608_06669_amd as pk
+    p = problem(make_problem(o, v, naux, 66, gauge="haar"))
+    t = [dev(x) for x in random_amplitudes(o, v, 67, scale=0.02)]
+    q = [dev(x) for x in random_amplitudes(o, v, 68, scale=1.0)]
+    plain, fp32 = pk.Handle(0), pk.Handle(0)
+    try:
+        y = fp32.jvp(p, *t, *q, prec="fp32")
+        want = [x.cpu().numpy() for x in plain.residual(p, *t)]
+        assert rel_max(fp32.residual(p, *t), want) <= 1e-12
+        ref = plain.jvp(p, *t, *q, prec="fp64")
+        num = sum(float(((a - b) ** 2).sum()) for a, b in zip(y, ref))
+        assert num ** 0.5 < 5e-5 * sum(float((b ** 2).sum()) for b in ref) ** 0.5
+        assert rel_max(fp32.jvp(p, *t, *q, prec="fp64"), [x.cpu().numpy() for x in ref]) <= 1e-12
+    finally:
+        plain.close()
+        fp32.close()
