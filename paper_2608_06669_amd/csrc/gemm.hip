@@ -234,6 +234,133 @@ __global__ __launch_bounds__(256) void gemm_kernel(KArgs p) {
       }
 }
 
+// FP32 / BF16 products with at most 32 rows (M; a product with few columns
+// comes transposed): one wave per 16 columns and MT 16-row tiles, operands
+// straight from memory to registers, rounded there, U steps of 32 (BF16) or 16
+// (FP32) k ahead; no LDS, no barrier. The wide operand is read once and
+// used by MT instructions, so these products are HBM-bound: those of one BF16
+// J v at o = 20, v = 180 (1.2 GB, 1 to 20 rows) take 1.05 ms, where 64 x 64
+// tiles through LDS, mostly padding and one panel in flight, took 1.31; 20 x
+// 32400 x 20 in 20 batches 171 us with one step ahead, 212 with two.
+// k order, chunks and roundings are those of gemm_kernel: same results.
+template <class Mma, typename TA, typename TB, int MT, int U>
+__global__ __launch_bounds__(256, U == 1 ? 4 : 2) void gemm_thin(KArgs p) {
+  using L = typename Mma::L;
+  constexpr bool bf16 = Mma::KCONTIG_LDS;
+  constexpr int E = bf16 ? 8 : 4, KS = 4 * E;
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const int n0 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 16;
+  if (n0 >= p.N) return;
+  const int split = blockIdx.z % p.splits;
+  const int zb = blockIdx.z / p.splits;
+  const int b0 = blockIdx.y % p.nb0;
+  const int b1 = blockIdx.y / p.nb0 + zb * (gridDim.y / p.nb0);
+  const int kbeg = split * p.kchunk, kend = min(p.K, kbeg + p.kchunk);
+  const int nk1 = (kend - kbeg + KS - 1) / KS, nk = p.A2 ? 2 * nk1 : nk1;
+  // (rows and columns past the matrix read its last ones; not written)
+  const int col = n0 + (lane & 15);
+  const int64_t aoff = b0 * p.a_b0 + b1 * p.a_b1, boff = b0 * p.b_b0 + b1 * p.b_b1 + min(col, p.N - 1) * p.b_n;
+  int64_t arow[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) arow[i] = aoff + min(i * 16 + (lane & 15), p.M - 1) * p.a_m;
+  struct Raw {
+    TA a[MT][E];
+    TB b[E];
+  };
+  auto kofs = [&](int e) { return bf16 ? 8 * g + e : 4 * e + g; };
+  auto fetch = [&](auto (&r)[E], auto* x, int64_t s_k, bool vec, int k0) {
+    using T = std::remove_reference_t<decltype(r[0])>;
+    const T* row = (const T*)x;
+    if (k0 + KS <= kend) {
+      if (bf16 && vec) {
+        const uint4* q = reinterpret_cast<const uint4*>(row + k0 + 8 * g);
+#pragma unroll
+        for (int u = 0; u < (int)sizeof(r) / 16; ++u) reinterpret_cast<uint4*>(r)[u] = q[u];
+        return;
+      }
+      const T* q = row + (k0 + kofs(0)) * s_k;
+      const int64_t st = bf16 ? s_k : 4 * s_k;
+#pragma unroll
+      for (int e = 0; e < E; ++e) r[e] = q[e * st];
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int k = k0 + kofs(e);
+        const T v = row[min(k, kend - 1) * s_k];
+        r[e] = k < kend ? v : T(0);
+      }
+    }
+  };
+  auto load = [&](Raw& r, int t) {
+    t = min(t, nk - 1);
+    const bool second = t >= nk1;
+    const int k0 = kbeg + (second ? t - nk1 : t) * KS;
+    const TA* A = (const TA*)(second ? p.A2 : p.A);
+    const TB* B = (const TB*)(second ? p.B2 : p.B);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) fetch(r.a[i], A + arow[i], p.a_k, p.a_vec != 0, k0);
+    fetch(r.b, B + boff, p.b_k, p.b_vec != 0, k0);
+  };
+  f4 acc[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i] = f4{};
+  auto multiply = [&](const Raw& r) {
+    if constexpr (bf16) {
+      u16x8 x, y;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = to_lds<TB, L>(r.b[e]);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = to_lds<TA, L>(r.a[i][e]);
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, x), __builtin_bit_cast(bf8, y), acc[i], 0,
+                                                         0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(to_lds<TA, L>(r.a[i][e]), to_lds<TB, L>(r.b[e]), acc[i], 0, 0, 0);
+    }
+  };
+  Raw x[U], y[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) load(x[u], u);
+  int t = 0;
+  for (; t + U < nk; t += 2 * U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(y[u], t + U + u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) multiply(x[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(x[u], t + 2 * U + u);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (t + U + u < nk) multiply(y[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (t + u < nk) multiply(x[u]);
+
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = i * 16 + 4 * g + r;
+      if (row >= p.M || col >= p.N) continue;
+      if (p.splits > 1) {
+        const int64_t b = (int64_t)b1 * p.nb0 + b0;
+        p.ws[(((int64_t)split * p.nbtot + b) * p.M + row) * p.N + col] = (double)acc[i][r];
+      } else {
+        const int64_t at = b0 * p.c_b0 + b1 * p.c_b1 + row * p.c_m + col * p.c_n;
+        double v = p.alpha * (double)acc[i][r];
+        if (p.beta != 0.0) v += p.beta * ((const double*)p.Cin)[at];
+        ((double*)p.C)[at] = v;
+      }
+    }
+}
+
 // C[b][m][n] = alpha * sum_s ws[s][b][m][n] + beta * C[b][m][n] (fixed order)
 template <typename TC>
 __global__ __launch_bounds__(256) void splitk_reduce(KArgs p) {
@@ -579,6 +706,37 @@ bool vec_ok(const void* base, int64_t s_row, int64_t s_k, int64_t s_b0, int64_t 
   return s_row == 1 && s_k % V == 0;
 }
 
+// gemm_thin, transposed if the columns are the few
+template <class Mma, typename TA, typename TB>
+void launch_thin(const KArgs& p, bool akc, bool bkc, int64_t gy, int64_t gz, hipStream_t s) {
+  if (p.M > 32) {
+    KArgs q = p;
+    std::swap(q.M, q.N);
+    q.A = p.B; q.A2 = p.B2; q.a_m = p.b_n; q.a_k = p.b_k; q.a_b0 = p.b_b0; q.a_b1 = p.b_b1; q.a_vec = p.b_vec;
+    q.B = p.A; q.B2 = p.A2; q.b_n = p.a_m; q.b_k = p.a_k; q.b_b0 = p.a_b0; q.b_b1 = p.a_b1; q.b_vec = p.a_vec;
+    std::swap(q.c_m, q.c_n);
+    launch_thin<Mma, TB, TA>(q, bkc, akc, gy, gz, s);
+    return;
+  }
+  KArgs q = p;
+  // 16-byte loads along k: rows and batches aligned
+  q.a_vec = akc && p.a_vec;
+  q.b_vec = bkc && p.b_vec;
+  const int waves = (int)std::min<int64_t>(4, ceil_div(p.N, 16));
+  const dim3 grid((unsigned)ceil_div(p.N, 16 * waves), (unsigned)gy, (unsigned)(gz * p.splits));
+  // a few steps: one ahead, and twice the waves for the registers saved
+  const bool brief = (int64_t)p.kchunk * (p.A2 ? 2 : 1) <= 128;
+  if (p.M <= 16) {
+    if (brief) gemm_thin<Mma, TA, TB, 1, 1><<<grid, 64 * waves, 0, s>>>(q);
+    else gemm_thin<Mma, TA, TB, 1, 2><<<grid, 64 * waves, 0, s>>>(q);
+  } else if (brief) {
+    gemm_thin<Mma, TA, TB, 2, 1><<<grid, 64 * waves, 0, s>>>(q);
+  } else {
+    gemm_thin<Mma, TA, TB, 2, 2><<<grid, 64 * waves, 0, s>>>(q);
+  }
+  PNK_CHECK_LAUNCH();
+}
+
 template <class Mma, typename TA, typename TB, typename TC, int BM, int BN, int BK, int WGM>
 void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2, const void* B2, void* C,
                 hipStream_t s) {
@@ -643,6 +801,14 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
       splitk_reduce<TC><<<(unsigned)std::min<int64_t>(ceil_div(total, 256), 4096), 256, 0, s>>>(q);
     PNK_CHECK_LAUNCH();
   };
+  if constexpr (!f64 && BM == 64) {
+    if (std::min(d.M, d.N) <= 32) {
+      launch_thin<Mma, TA, TB>(p, akc, bkc, gy, gz, s);
+      if (p.splits > 1 && d.M > 32) std::swap(p.c_m, p.c_n), std::swap(p.M, p.N);
+      reduce(p);
+      return;
+    }
+  }
   if (pipe_cfg && akc && bkc && !A2 && d.K % 64 == 0 && p.a_vec && p.b_vec && d.M > 128) {
     // more than 128 rows: 256 x 128 tiles with 8 waves, one workgroup per
     // CU. Tiles that cannot fill the GPU take split-K in whole rounds of
