@@ -534,6 +534,225 @@ __global__ __launch_bounds__(256) void inner_begin_kernel(const double* __restri
   fin[kInnerFinBHat] = bhat;
 }
 
+// A whole segment of the solve in one workgroup, for vectors of at most
+// kRunThreads E elements: the recurrence stays in registers (E elements per
+// thread), the three sums of a step go through one barrier and every thread
+// forms the scalars for itself; x follows from one more run over them, as in
+// inner_finish_kernel. FIRST: b's shares give the norms (as
+// inner_begin_kernel); else the state after the segment before it is in
+// memory. Bound by the chain of sums and scalars: 1.9 us a step at 2624 elements
+// (o = 4, v = 16), 2.6 at 7952 (o = 4, v = 28), where a launch for each step took
+// 6.1; 22 steps with the start and x 43 us in place of 157.
+constexpr int kRunThreads = 512;
+
+template <bool PACKED, int E>
+__global__ __launch_bounds__(kRunThreads) void inner_run_kernel(Args p, int n, bool first, const double* __restrict__ shares,
+                                                                int nshares, double rtol, double limit, double* v0,
+                                                                double* v1, double* w1o, double* w2o, double* xo) {
+  constexpr int NW = kRunThreads / 64;
+  __shared__ double sm[2][3][NW];
+  __shared__ double cf[kInnerSegment][8];  // A, B, s, delta, eps, 1 / rho, phi; s y
+  __shared__ double g[2];
+  enum { A = 0, B, S, DELTA, EPS, IR, PHI, Y };
+  const int tid = threadIdx.x;
+  double* st = p.state;
+  double* fin = p.state + 2 * kInnerState;
+  int par = 0;
+  auto sums = [&](double (&r)[3]) {
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) r[c] += __shfl_xor(r[c], m, 64);
+    if ((tid & 63) == 0)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sm[par][c][tid >> 6] = r[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      double t = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) t += sm[par][c][w];
+      r[c] = t;
+    }
+    par ^= 1;  // (the other half until every thread is past the next barrier)
+  };
+  // element tid + 512 e: its diagonal, and whether its block counts twice
+  double v[E], u[E], d[E];
+  uint32_t twice = 0;
+  const int ov = p.o * p.v, vv = p.v * p.v;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int q = tid + kRunThreads * e;
+    v[e] = u[e] = d[e] = 0.0;
+    if (q >= n) continue;
+    v[e] = v0[q];
+    if (!first) u[e] = v1[q];
+    if (q < ov) {
+      d[e] = p.sscale * (p.eps_v[q % p.v] - p.eps_o[q / p.v]);
+    } else {
+      const int f = q - ov, a = f % vv;
+      int i, j;
+      decode_pair(f / vv, p.o, PACKED, i, j);
+      d[e] = p.eps_v[a / p.v] + p.eps_v[a % p.v] - (p.eps_o[i] + p.eps_o[j]);
+      if (PACKED && i != j) twice |= 1u << e;
+    }
+  }
+  double beta = 0.0, gc2 = 1.0, gs2 = 0.0, gc1 = 1.0, gs1 = 0.0, phibar, total = 0.0, scale = 1.0, tol;
+  if (first) {
+    double r[3] = {0.0, 0.0, 0.0};
+    for (int k = tid; k < nshares; k += kRunThreads) {
+      r[0] += shares[k];
+      r[1] += shares[nshares + k];
+    }
+    sums(r);
+    const double bn = sqrt(r[0]), bhat = sqrt(r[1]);
+    phibar = bhat;
+    scale = bhat != 0.0 ? 1.0 / bhat : 0.0;
+    tol = rtol * bn;
+    if (tid == 0) fin[kInnerFinBNorm] = bn;
+  } else {
+    beta = st[kSBeta];
+    gc2 = st[kSC2];
+    gs2 = st[kSS2];
+    gc1 = st[kSC1];
+    gs1 = st[kSS1];
+    phibar = st[kSPhiBar];
+    total = st[kSTotal];
+    tol = fin[kInnerFinTol];
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) v[e] *= scale;
+  double sk = 1.0, sp = 1.0, res = phibar, betan = 1.0;
+  bool done = false;
+  int k = 0;
+  for (; k < kInnerSegment && !done; ++k) {
+    double r[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const double w = twice >> e & 1 ? 2.0 : 1.0;
+      const double vk = sk * v[e], y = d[e] * vk - beta * (sp * u[e]);
+      r[0] += w * vk * y;
+      r[1] += w * y * y;
+      r[2] += w * vk * vk;
+    }
+    sums(r);
+    // (as in inner_step_kernel)
+    const double vp = r[0], pp = r[1], nv = r[2];
+    const double alpha = nv > 0.0 ? vp / nv : 0.0;
+    betan = sqrt(fmax(pp - alpha * vp, 0.0));
+    const double eps = gs2 * beta, dbar = gc2 * beta;
+    const double delta = gc1 * dbar + gs1 * alpha, gbar = -gs1 * dbar + gc1 * alpha;
+    const double rho = hypot(gbar, betan);
+    const double c = rho != 0.0 ? gbar / rho : 1.0, sn = rho != 0.0 ? betan / rho : 0.0;
+    const double ib = betan != 0.0 ? 1.0 / betan : 0.0;
+    const double sn1 = beta * ib != 0.0 ? beta * ib * sp : sk;
+    const double ca = ib * (sk / sn1), cb = -alpha * ca;
+    if (tid == 0) {
+      cf[k][A] = ca;
+      cf[k][B] = cb;
+      cf[k][S] = sk;
+      cf[k][DELTA] = delta;
+      cf[k][EPS] = eps;
+      cf[k][IR] = rho != 0.0 ? 1.0 / rho : 0.0;
+      cf[k][PHI] = c * phibar;
+    }
+    phibar = -sn * phibar;
+    res = fabs(phibar);
+    total += 1.0;
+    done = res <= tol || betan == 0.0 || total >= limit;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const double t = (d[e] * ca + cb) * v[e] - u[e];
+      u[e] = v[e];
+      v[e] = t;
+    }
+    beta = betan;
+    sp = sk;
+    sk = sn1;
+    gc2 = gc1;
+    gs2 = gs1;
+    gc1 = c;
+    gs1 = sn;
+  }
+  if (tid == 0) {
+    st[kSBeta] = beta;
+    st[kSC2] = gc2;
+    st[kSS2] = gs2;
+    st[kSC1] = gc1;
+    st[kSS1] = gs1;
+    st[kSPhiBar] = phibar;
+    st[kSTotal] = total;
+    fin[kInnerFinTol] = tol;
+    fin[kInnerFinSteps] = total;
+    fin[kInnerFinRes] = res;
+    fin[kInnerFinBeta] = betan;
+    // R y = phi, as in inner_finish_kernel
+    double y1 = 0.0, y2 = 0.0, d1 = 0.0, e1 = 0.0, e2 = 0.0;
+    for (int j = k - 1; j >= 0; --j) {
+      const double y = (cf[j][PHI] - d1 * y1 - e2 * y2) * cf[j][IR];
+      cf[j][Y] = cf[j][S] * y;
+      y2 = y1;
+      y1 = y;
+      e2 = e1;
+      e1 = cf[j][EPS];
+      d1 = cf[j][DELTA];
+    }
+    g[0] = -d1 * y1 - e2 * y2;
+    g[1] = -e1 * y1;
+  }
+  __syncthreads();
+  constexpr int G = E < 8 ? E : 8;
+#pragma unroll
+  for (int e0 = 0; e0 < E; e0 += G) {
+    double a[G], b[G], x[G];
+#pragma unroll
+    for (int e = 0; e < G; ++e) {
+      const int q = min(tid + kRunThreads * (e0 + e), n - 1);
+      a[e] = scale * v0[q];
+      b[e] = first ? 0.0 : v1[q];
+      x[e] = first ? 0.0 : xo[q] + g[0] * w1o[q] + g[1] * w2o[q];
+    }
+    for (int j = 0; j < k; ++j) {
+      const double ca = cf[j][A], cb = cf[j][B], y = cf[j][Y];
+#pragma unroll
+      for (int e = 0; e < G; ++e) {
+        x[e] += y * a[e];
+        const double t = (d[e0 + e] * ca + cb) * a[e] - b[e];
+        b[e] = a[e];
+        a[e] = t;
+      }
+    }
+    if (!done) {
+      // another segment follows: the w recurrence itself, before v0 and v1 go
+#pragma unroll 1
+      for (int e = 0; e < G; ++e) {
+        const int q = tid + kRunThreads * (e0 + e);
+        if (q >= n) break;
+        double dq = 0.0;
+#pragma unroll
+        for (int f = 0; f < G; ++f) dq = f == e ? d[e0 + f] : dq;
+        double z = scale * v0[q], zp = first ? 0.0 : v1[q];
+        double w1 = first ? 0.0 : w1o[q], w2 = first ? 0.0 : w2o[q];
+        for (int j = 0; j < k; ++j) {
+          const double w = (cf[j][S] * z - cf[j][DELTA] * w1 - cf[j][EPS] * w2) * cf[j][IR];
+          w2 = w1;
+          w1 = w;
+          const double t = (dq * cf[j][A] + cf[j][B]) * z - zp;
+          zp = z;
+          z = t;
+        }
+        v0[q] = sk * z;
+        v1[q] = sp * zp;
+        w1o[q] = w1;
+        w2o[q] = w2;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < G; ++e)
+      if (tid + kRunThreads * (e0 + e) < n) xo[tid + kRunThreads * (e0 + e)] = x[e];
+  }
+}
+
 // x_ij = x_ji^T for i > j of a full-layout vector's doubles, in place (through LDS).
 __global__ __launch_bounds__(256) void inner_mirror_kernel(int o, int v, double* __restrict__ x2) {
   __shared__ double tile[kPackTile][kPackTile + 1];
@@ -918,6 +1137,30 @@ void launch_step(const InnerSolve& q, const Args& p, hipStream_t s) {
   else inner_step_kernel<PACKED, 4><<<grid, 256, lds, s>>>(p);
 }
 }  // namespace
+
+// Up to 16 elements a thread: with 24 the registers spill (4.4 us a step in
+// place of 2.6 at 16; a launch for each step takes 6.1 at any such length).
+bool inner_runs_whole(const InnerSolve& q) { return q.n <= 16 * kRunThreads; }
+
+namespace {
+template <bool PACKED>
+void launch_run(const InnerSolve& q, const Args& p, bool first, int nshares, double rtol, double limit, hipStream_t s) {
+  const int n = (int)q.n;
+  auto go = [&](auto kernel) {
+    kernel<<<1, kRunThreads, 0, s>>>(p, n, first, q.norm_parts, nshares, rtol, limit, q.v0, q.v1, q.w1, q.w2, q.x);
+  };
+  if (n <= 2 * kRunThreads) go(inner_run_kernel<PACKED, 2>);
+  else if (n <= 8 * kRunThreads) go(inner_run_kernel<PACKED, 8>);
+  else go(inner_run_kernel<PACKED, 16>);
+}
+}  // namespace
+
+void inner_run(const InnerSolve& q, bool first, int nshares, double rtol, int limit, double singles_scale, hipStream_t s) {
+  const Args p = args_of(q, 0, singles_scale);
+  if (q.packed) launch_run<true>(q, p, first, nshares, rtol, limit, s);
+  else launch_run<false>(q, p, first, nshares, rtol, limit, s);
+  PNK_CHECK_LAUNCH();
+}
 
 void inner_step(const InnerSolve& q, int parity, double singles_scale, hipStream_t s) {
   const Args p = args_of(q, parity, singles_scale);

@@ -78,6 +78,11 @@ void inner_begin(const InnerSolve& q, int nshares, double rtol, int limit, hipSt
 // meets the tolerance or the limit, later launches write nothing.
 void inner_step(const InnerSolve& q, int parity, double singles_scale, hipStream_t s);
 bool inner_is_step_kernel(const void* func);
+// Vectors that fit one workgroup: a segment of kInnerSegment steps, or up to the
+// one that meets the tolerance or the limit, in one launch that also stands
+// for inner_begin (first segment), inner_finish and its rebase.
+bool inner_runs_whole(const InnerSolve& q);
+void inner_run(const InnerSolve& q, bool first, int nshares, double rtol, int limit, double singles_scale, hipStream_t s);
 // x from the first `steps` of the current segment (of step_base + steps in
 // all). With `rebase`, v0, v1, w1, w2 and x are left as the state after them,
 // for another kInnerSegment steps, and the launch of `parity` comes next.

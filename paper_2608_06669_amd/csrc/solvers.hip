@@ -330,7 +330,8 @@ int Solver::precond_solve_sym(const FockEigen& eig, VecIn b, VecOut x, double rt
   const FockOp* op = eng_.fock_op();
   const int64_t cap = packed && op && op->bm == 32 ? 4 * ceil_div(maxit, 4) - 1 : 6 * ceil_div(maxit, 6);
   const int limit = (int)std::min<int64_t>(cap, 0x7fffffff);
-  inner_begin(q, nshares, rtol, limit, s);
+  const bool whole = inner_runs_whole(q);
+  if (!whole) inner_begin(q, nshares, rtol, limit, s);
   const double* fin = q.state + 2 * kInnerState;
   Timers* tm = eng_.timers();
   // the event pairs are read for a sample of the solves: each bracketed
@@ -344,7 +345,21 @@ int Solver::precond_solve_sym(const FockEigen& eig, VecIn b, VecOut x, double rt
   int batch = std::max(1, (int)ceil_div(inner_steps_hint_ + 1, kInnerBlock));
   int launched = 0, seg_launched = 0, seg_base = 0, steps = 0;
   bool conv = false;
-  while (true) {
+  auto outcome = [&]() {
+    read_scalars(host_, fin, kInnerFinRead, s);  // synchronises the stream
+    steps = (int)host_[kInnerFinSteps];
+    // ||b - A_F x|| <= ||D^1/2 (b - A_F x)|| = the scaled residual (D >= I)
+    const double res = host_[kInnerFinRes], bn = host_[kInnerFinBNorm];
+    conv = std::isfinite(res) && steps > 0 && (res <= rtol * bn || host_[kInnerFinBeta] == 0.0);
+    return conv || !std::isfinite(res) || steps >= limit;
+  };
+  for (bool first = true, ended = false; whole && !ended; first = false) {
+    if (tm) tm->begin(kTimerFock, s);
+    inner_run(q, first, nshares, rtol, limit, kInnerSinglesScale, s);
+    if (tm) tm->end(kTimerFock, s);
+    ended = outcome();
+  }
+  while (!whole) {
     const int nb = std::min(batch, kSegBlocks - seg_launched / kInnerBlock);
     bool timed = false, graph = false;
     if (use_graphs_) {
@@ -358,11 +373,7 @@ int Solver::precond_solve_sym(const FockEigen& eig, VecIn b, VecOut x, double rt
     launched += nb * kInnerBlock;
     seg_launched += nb * kInnerBlock;
     batch = 1;
-    read_scalars(host_, fin, kInnerFinRead, s);  // synchronises the stream
-    steps = (int)host_[kInnerFinSteps];
-    // ||b - A_F x|| <= ||D^1/2 (b - A_F x)|| = the scaled residual (D >= I)
-    const double res = host_[kInnerFinRes], bn = host_[kInnerFinBNorm];
-    conv = std::isfinite(res) && steps > 0 && (res <= rtol * bn || host_[kInnerFinBeta] == 0.0);
+    const bool ended = outcome();
     if (timed) {
       const int ran = std::min(nb * kInnerBlock, std::min(launched, steps + 1) - before);
       for (int k = 0; k < ran; ++k) {
@@ -371,15 +382,17 @@ int Solver::precond_solve_sym(const FockEigen& eig, VecIn b, VecOut x, double rt
         else (void)hipGetLastError();
       }
     }
-    if (conv || !std::isfinite(res) || steps >= limit) break;
+    if (ended) break;
     if (seg_launched == kInnerSegment) {
       inner_finish(q, steps - seg_base, seg_base == 0, true, 0, kInnerSinglesScale, s);
       seg_base = steps;
       seg_launched = 0;
     }
   }
-  inner_steps_hint_ = steps;
-  inner_finish(q, steps - seg_base, seg_base == 0, false, 0, kInnerSinglesScale, s);
+  if (!whole) {
+    inner_steps_hint_ = steps;
+    inner_finish(q, steps - seg_base, seg_base == 0, false, 0, kInnerSinglesScale, s);
+  }
   if (eig.ut_v) inner_rotate_vir(eig, false, rows, q.x, Qi_ + 5 * n, s);
   inner_unload(q, Qi_, Qi_ + n, kInnerSinglesScale, x, s);
   if (converged) *converged = conv;

@@ -89,3 +89,27 @@ def test_inner_solve_stops_at_its_cap(handle):
         # (whole blocks of four launches, the first of which completes no step)
         assert not ok and iters == 4 * -(-maxit // 4) - 1
         assert np.isfinite(host(x2)).all()
+
+
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("o,v,lowest,at_least", [(2, 5, 1e-3, 20), (4, 20, 1e-2, 65), (3, 36, 1e-3, 129), (4, 28, 1e-3, 129)])
+def test_inner_solve_in_one_workgroup(handle, o, v, lowest, at_least, packed):
+    """Vectors short enough for one workgroup, over one and several segments,
+    and a step limit that ends the solve before the tolerance."""
+    p = make_near_degenerate(o, v, 12, 78)
+    rng = np.random.default_rng(7)
+    uo, uv = haar_orthogonal(rng, o), haar_orthogonal(rng, v)
+    p.f_oo[:] = -(uo * np.geomspace(lowest, 1.5, o)) @ uo.T
+    p.f_vv[:] = (uv * np.geomspace(lowest, 2.5, v)) @ uv.T
+    p.f_oo[:] = 0.5 * (p.f_oo + p.f_oo.T)
+    p.f_vv[:] = 0.5 * (p.f_vv + p.f_vv.T)
+    P = pk.DeviceProblem.from_problem(p)
+    b1, b2 = (dev(b) for b in random_amplitudes(o, v, 6, scale=1.0))
+    x1, x2, iters, ok = handle.precond_solve(P, b1, b2, rtol=1e-11, maxit=2000, pair_symmetric=packed)
+    assert ok and iters >= at_least
+    y1, y2 = handle.fock_apply(P, x1, x2)
+    r = torch.sqrt(((b1 - y1) ** 2).sum() + ((b2 - y2) ** 2).sum())
+    # (the product itself rounds at 1e-15 of ||A_F|| ||x||, 1e-12 here)
+    assert float(r / torch.sqrt((b1 ** 2).sum() + (b2 ** 2).sum())) <= 2e-11
+    _, _, short, ok = handle.precond_solve(P, b1, b2, rtol=1e-11, maxit=6, pair_symmetric=packed)
+    assert not ok and 6 <= short <= 8
