@@ -889,8 +889,8 @@ struct F64Plan {
   int64_t nfull;
   int ts;
 };
-F64Plan f64_plan(int64_t tiles, int bn, int K, int64_t sum_elems, int64_t ws_elems, bool vec, bool dual) {
-  const double unit = (double)ceil_div(K, 8) * (dual ? 2 : 1) * (bn == 128 ? 0.456 : vec ? 0.235 : 0.27);
+F64Plan f64_plan(int64_t tiles, int bm, int bn, int K, int64_t sum_elems, int64_t ws_elems, bool vec, bool dual) {
+  const double unit = (double)ceil_div(K, 8) * (dual ? 2 : 1) * (bn == 128 ? 0.456 : vec ? 0.235 : 0.27) * bm / 64;
   auto rate = [&](int64_t c, bool together) {
     static const double e[2][2][4] = {{{0.50, 0.72, 0.85, 0.90}, {0.50, 0.65, 0.78, 0.82}},
                                       {{0.76, 0.85, 0.90, 0.92}, {0.76, 0.74, 0.85, 0.85}}};
@@ -928,23 +928,48 @@ void launch_f64_layout(const f64pipe::Args& p, bool vec, unsigned grid, hipStrea
   else f64pipe::gemm_f64_pipe<64, BN, A_KC, B_KC, false><<<grid, 256, 0, s>>>(p);
 }
 
+// Rows of a tile for M rows: the count that pads least, 64 if another saves less
+// than 5 %. Only for A contiguous along k and B along n in 16-byte loads (the
+// products of a few pair rows or occupied rows with a wide operand), and 64
+// columns: of 72 x 128 tiles only two fit a CU. (96 x 64 tiles, three to a CU,
+// took 72 us where two of 48 rows take 64, 91 x 5464 x 4192.)
+int f64_rows(int M, const F64Layout& la, const F64Layout& lb) {
+  int best = 64;
+  if (!la.kc || lb.kc || !la.vec || !lb.vec) return best;
+  static const int kRows[] = {72, 80, 48};
+  int64_t pad = ceil_div(M, 64) * 64 * 95 / 100;
+  for (int r : kRows) {
+    const int64_t q = ceil_div(M, r) * r;
+    if (q < pad) {
+      pad = q;
+      best = r;
+    }
+  }
+  return best;
+}
+
 template <int BN>
 void launch_f64_tiles(f64pipe::Args p, const F64Layout& la, const F64Layout& lb, int64_t nb, int64_t ws_elems, bool asc,
                       hipStream_t s) {
   const bool vec = la.vec && lb.vec;
-  p.tm = (int)ceil_div(p.M, 64);
+  p.bm = BN == 128 || asc ? 64 : f64_rows(p.M, la, lb);
+  p.bn = BN;
+  p.tm = (int)ceil_div(p.M, p.bm);
   p.tn = (int)ceil_div(p.N, BN);
-  p.wr = std::min(p.M, 64);
+  p.wr = std::min(p.M, p.bm);
   p.wc = std::min(p.N, BN);
   const int64_t tiles = (int64_t)p.tm * p.tn * nb;
-  const F64Plan plan = asc ? F64Plan{tiles, 1} : f64_plan(tiles, BN, p.K, (int64_t)p.wr * p.wc, ws_elems, vec, p.A2 != nullptr);
+  const F64Plan plan = asc ? F64Plan{tiles, 1} : f64_plan(tiles, p.bm, BN, p.K, (int64_t)p.wr * p.wc, ws_elems, vec, p.A2 != nullptr);
   PNK_REQUIRE(tiles * plan.ts < (int64_t(1) << 31), "gemm: batch too large");
   p.kchunk = plan.ts > 1 ? (int)(ceil_div(ceil_div(p.K, plan.ts), 8) * 8) : p.K;
   p.ts = (int)ceil_div(p.K, p.kchunk);  // no empty chunk
   p.nfull = (int)(p.ts > 1 ? plan.nfull : tiles);
   p.ntail = (int)(tiles - p.nfull);
   const unsigned grid = (unsigned)(p.nfull + (int64_t)p.ntail * p.ts);
-  if (la.kc && lb.kc) launch_f64_layout<BN, true, true>(p, vec, grid, s);
+  if (p.bm == 72) f64pipe::gemm_f64_pipe<72, 64, true, false, true><<<grid, 256, 0, s>>>(p);
+  else if (p.bm == 80) f64pipe::gemm_f64_pipe<80, 64, true, false, true><<<grid, 256, 0, s>>>(p);
+  else if (p.bm == 48) f64pipe::gemm_f64_pipe<48, 64, true, false, true><<<grid, 256, 0, s>>>(p);
+  else if (la.kc && lb.kc) launch_f64_layout<BN, true, true>(p, vec, grid, s);
   else if (la.kc && BN == 64 && asc) {
     if (vec) f64pipe::gemm_f64_pipe<64, 64, true, false, true, true><<<grid, 256, 0, s>>>(p);
     else f64pipe::gemm_f64_pipe<64, 64, true, false, false, true><<<grid, 256, 0, s>>>(p);
@@ -955,9 +980,9 @@ void launch_f64_tiles(f64pipe::Args p, const F64Layout& la, const F64Layout& lb,
   if (p.ntail) {
     const int n = p.wr * p.wc;
     if (p.ts >= 32)
-      f64pipe::gemm_f64_reduce_wide<64, BN><<<dim3((unsigned)p.ntail, (unsigned)ceil_div(n, 16)), 256, 0, s>>>(p);
+      f64pipe::gemm_f64_reduce_wide<<<dim3((unsigned)p.ntail, (unsigned)ceil_div(n, 16)), 256, 0, s>>>(p);
     else
-      f64pipe::gemm_f64_reduce<64, BN><<<dim3((unsigned)p.ntail, (unsigned)ceil_div(n, 256)), 256, 0, s>>>(p);
+      f64pipe::gemm_f64_reduce<<<dim3((unsigned)p.ntail, (unsigned)ceil_div(n, 256)), 256, 0, s>>>(p);
     PNK_CHECK_LAUNCH();
   }
 }
@@ -985,7 +1010,7 @@ bool launch_f64(const GemmDesc& d, const double* A, const double* B, const doubl
   // their coarser rounds cost more than that (600 x 3600 x 3600 306 against
   // 292 us).
   const bool asc = d.ascending && !lb.kc;
-  const bool wide = !asc && d.K >= 2048 && (double)d.M * d.N * d.K * nb >= 1e10;
+  const bool wide = !asc && f64_rows(d.M, la, lb) == 64 && d.K >= 2048 && (double)d.M * d.N * d.K * nb >= 1e10;
   if (wide) launch_f64_tiles<128>(p, la, lb, nb, ws, asc, s);
   else launch_f64_tiles<64>(p, la, lb, nb, ws, asc, s);
   return true;

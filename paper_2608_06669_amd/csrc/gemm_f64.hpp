@@ -11,6 +11,7 @@ typedef double d2 __attribute__((ext_vector_type(2)));
 
 struct Args {
   int M, N, K, nb0;
+  int bm, bn;      // tile
   int tm, tn;      // tiles along M and N
   int nfull;       // tiles computed in one piece: C written directly
   int ntail, ts;   // the other tiles, each cut into ts chunks of kchunk along K
@@ -74,7 +75,7 @@ static __device__ __align__(16) double zero_src[2];
 // rows of any alignment and length take the same path.
 // Operands are read from LDS 16 bytes at a time: two consecutive k of a row
 // (k-contiguous panels, stored [row][8] with the four 16-byte chunks of a row
-// at slot chunk ^ ((row / 4) % 4)) or two consecutive rows at one k (stored
+// at slot chunk ^ ((row / 4) % 4), rows counted within the wave's half) or two consecutive rows at one k (stored
 // [k][rows]). Lanes 16 g .. 16 g + 15 take k = 2 g and 2 g + 1 of a panel, one
 // for each of its two instruction steps. The fragments of a panel are read
 // while the panel before it is multiplied, so neither the LDS latency nor the
@@ -84,6 +85,10 @@ static __device__ __align__(16) double zero_src[2];
 // 62-65 (the former kernel, 16-deep panels in three stages with the fragments
 // read after the barrier, 1640-1710 us in place of 1441-1492), 1183^3 with
 // rows of odd length, which it could not take, at 37-41 (4-byte loads).
+// Tiles of 48, 72 or 80 rows serve row counts that multiples of 64 fit badly
+// (the pair rows of the ladders): 136 x 12880 x 10440 takes 990 us with 72 rows
+// where 64 took 1430, 78 x 5360 x 4096 118 with 80 (142), 20 x 180 x 108000 126
+// with 48 (165); 210 x 20104 x 16296 2740 with 72 (2860 with 64 x 128).
 // A contraction that is not whole panels starts with its remainder, zeros in
 // place of the missing k, in the prologue: the loop sees whole panels only.
 //
@@ -97,8 +102,10 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
   constexpr int BK = 8, NT = 256, AE = BM * BK, BE = BN * BK, SE = AE + BE;
   constexpr int WTM = BM / 2, WTN = BN / 2, TMI = WTM / 4, TNI = WTN / 16;
   constexpr int EPL = VEC ? 4 : 1;                                // dwords per lane and load
-  constexpr int CA = AE * 2 / (EPL * NT), CB = BE * 2 / (EPL * NT);  // loads per thread and panel
-  static_assert(CA >= 1 && CB >= 1 && CA * EPL * NT == AE * 2 && CB * EPL * NT == BE * 2, "whole loads per thread");
+  // loads per thread and panel; where A's are not whole ones, every wave takes
+  // the last with its first RA lanes (all waves count the same loads)
+  constexpr int FA = AE * 2 / (EPL * NT), RA = (AE * 2 / EPL - FA * NT) / 4, CA = FA + (RA > 0), CB = BE * 2 / (EPL * NT);
+  static_assert((FA * NT + 4 * RA) * EPL == AE * 2 && CB >= 1 && CB * EPL * NT == BE * 2, "whole loads");
   static_assert((A_KC || TMI % 2 == 0) && (B_KC || TNI % 2 == 0), "row pairs");
   __shared__ __attribute__((aligned(1024))) double st0[SE], st1[SE], st2[SE], st3[SE];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -128,13 +135,13 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
   // (rows past the matrix read its last ones, whose outputs are not written)
   // and the k they hold
   uint32_t oa[CA], ob[CB];
-  auto place = [&](int j, bool kc, int rows, int left, int64_t ld, uint32_t* off, int* k) {
-    const int w = (j * NT + tid) * EPL;         // dword of the panel
+  auto place = [&](int j, bool part, bool kc, int rows, int left, int64_t ld, uint32_t* off, int* k) {
+    const int w = (j * NT + (part ? wave * RA + min(lane, RA - 1) : tid)) * EPL;  // dword of the panel
     const int c = w >> 2, half = (w >> 1) & 1;  // 16-byte chunk, element of it
     int r, kk;
     if (kc) {
       r = c >> 2;
-      kk = 2 * ((c & 3) ^ ((r >> 2) & 3)) + half;
+      kk = 2 * ((c & 3) ^ ((r % (rows / 2) >> 2) & 3)) + half;
       r = min(r, left - 1);
       *off = (uint32_t)(((int64_t)r * ld + kk) * 8 + (w & 1) * 4);
     } else {
@@ -151,10 +158,14 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
   const int64_t sa = A_KC ? 8 : 8 * p.lda, sb = B_KC ? 8 : 8 * p.ldb;  // bytes from one k to the next
   int kq;
 #pragma unroll
-  for (int j = 0; j < CA; ++j) place(j, A_KC, BM, p.M - m0, p.lda, &oa[j], &kq);
+  for (int j = 0; j < CA; ++j) place(j, j == FA, A_KC, BM, p.M - m0, p.lda, &oa[j], &kq);
 #pragma unroll
-  for (int j = 0; j < CB; ++j) place(j, B_KC, BN, p.N - n0, p.ldb, &ob[j], &kq);
+  for (int j = 0; j < CB; ++j) place(j, false, B_KC, BN, p.N - n0, p.ldb, &ob[j], &kq);
 
+  auto load_a = [&](int j, const char* src, double* st) {
+    if (j < FA) to_lds<VEC>(src, (uint32_t*)st + (j * NT + wave * 64) * EPL);
+    else if (lane < RA) to_lds<VEC>(src, (uint32_t*)st + (j * NT + wave * RA) * EPL);
+  };
   // whole panel f of the first (f < nf) or second product; past the last
   // one, the last again (never read)
   auto issue = [&](double* st, int t) {
@@ -167,7 +178,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
     // would add 64-bit vectors for every load)
     asm volatile("" : "+s"(a), "+s"(bq));
 #pragma unroll
-    for (int j = 0; j < CA; ++j) to_lds<VEC>(a + oa[j], (uint32_t*)st + (j * NT + wave * 64) * EPL);
+    for (int j = 0; j < CA; ++j) load_a(j, a + oa[j], st);
 #pragma unroll
     for (int j = 0; j < CB; ++j) to_lds<VEC>(bq + ob[j], (uint32_t*)(st + AE) + (j * NT + wave * 64) * EPL);
   };
@@ -178,14 +189,14 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
     for (int j = 0; j < CA; ++j) {
       uint32_t o;
       int k;
-      place(j, A_KC, BM, p.M - m0, p.lda, &o, &k);
-      to_lds<VEC>(k < rem ? a + o : z, (uint32_t*)st + (j * NT + wave * 64) * EPL);
+      place(j, j == FA, A_KC, BM, p.M - m0, p.lda, &o, &k);
+      load_a(j, k < rem ? a + o : z, st);
     }
 #pragma unroll
     for (int j = 0; j < CB; ++j) {
       uint32_t o;
       int k;
-      place(j, B_KC, BN, p.N - n0, p.ldb, &o, &k);
+      place(j, false, B_KC, BN, p.N - n0, p.ldb, &o, &k);
       to_lds<VEC>(k < rem ? bq + o : z, (uint32_t*)(st + AE) + (j * NT + wave * 64) * EPL);
     }
   };
@@ -212,9 +223,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
         const int m = wm * WTM + i * 4 + (lane & 3);
         if constexpr (ASC) {
 #pragma unroll
-          for (int e = 0; e < 2; ++e) f.a[e][i] = st[m * BK + 2 * ((2 * e + (g >> 1)) ^ ((m >> 2) & 3)) + (g & 1)];
+          for (int e = 0; e < 2; ++e) f.a[e][i] = st[m * BK + 2 * ((2 * e + (g >> 1)) ^ (i & 3)) + (g & 1)];
         } else {
-          const d2 x = *reinterpret_cast<const d2*>(st + m * BK + 2 * (g ^ ((m >> 2) & 3)));
+          const d2 x = *reinterpret_cast<const d2*>(st + m * BK + 2 * (g ^ (i & 3)));
           f.a[0][i] = x[0];
           f.a[1][i] = x[1];
         }
@@ -349,7 +360,6 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
 
 // C of the tail tiles from their chunk sums, added in chunk order. blockIdx.x:
 // tail tile; blockIdx.y and the threads walk its wr x wc elements.
-template <int BM, int BN>
 __global__ __launch_bounds__(256) void gemm_f64_reduce(Args p) {
   int b, im, in;
   tile_coords(p, p.nfull + blockIdx.x, &b, &im, &in);
@@ -358,7 +368,7 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce(Args p) {
   const double* __restrict__ W = p.ws + (int64_t)blockIdx.x * n;
   const int64_t coff = (b % p.nb0) * p.c_b0 + (b / p.nb0) * p.c_b1;
   for (int e = blockIdx.y * 256 + threadIdx.x; e < n; e += gridDim.y * 256) {
-    const int m = im * BM + e / p.wc, c = in * BN + e % p.wc;
+    const int m = im * p.bm + e / p.wc, c = in * p.bn + e % p.wc;
     if (m >= p.M || c >= p.N) continue;
     const int64_t at = coff + m * p.c_m + c * p.c_n;
     const double old = p.beta != 0.0 ? p.Cin[at] : 0.0;
@@ -380,7 +390,6 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce(Args p) {
 
 // The same for many chunks and few outputs: 16 lanes per output, each adding
 // every 16th chunk in increasing order, then the 16 lane sums in order.
-template <int BM, int BN>
 __global__ __launch_bounds__(256) void gemm_f64_reduce_wide(Args p) {
   __shared__ double sm[16][17];
   int b, im, in;
@@ -407,7 +416,7 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce_wide(Args p) {
     }
     sm[sg][eo] = acc;
     __syncthreads();
-    const int m = im * BM + e / p.wc, c = in * BN + e % p.wc;
+    const int m = im * p.bm + e / p.wc, c = in * p.bn + e % p.wc;
     if (sg == 0 && e < n && m < p.M && c < p.N) {
       double sum = 0.0;
       for (int q = 0; q < 16; ++q) sum += sm[q][eo];

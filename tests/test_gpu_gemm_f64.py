@@ -30,7 +30,9 @@ def _operand(x, kc, ld, base):
 SIZES = [(1, 1, 1, 1, False), (3, 70, 8, 1, False), (64, 64, 16, 2, False), (65, 66, 24, 1, False),
          (66, 64, 32, 3, False), (63, 65, 33, 1, False), (130, 62, 39, 1, False), (128, 192, 72, 1, False),
          (1100, 1090, 96, 1, True), (70, 66, 1001, 1, True), (2, 2, 5000, 2, True), (20, 18, 40000, 1, True),
-         (130, 8190, 9802, 1, True)]
+         (130, 8190, 9802, 1, True),
+         # rows that tiles of 48, 72 and 80 fit
+         (48, 130, 40, 2, False), (143, 66, 100, 1, True), (79, 129, 1001, 1, True), (150, 200, 64, 1, False)]
 
 
 @pytest.mark.parametrize("M,N,K,nb,splitk", SIZES)
