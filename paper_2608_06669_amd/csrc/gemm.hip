@@ -894,11 +894,15 @@ F64Plan f64_plan(int64_t tiles, int bm, int bn, int K, int64_t sum_elems, int64_
   auto rate = [&](int64_t c, bool together) {
     static const double e[2][2][4] = {{{0.50, 0.72, 0.85, 0.90}, {0.50, 0.65, 0.78, 0.82}},
                                       {{0.76, 0.85, 0.90, 0.92}, {0.76, 0.74, 0.85, 0.85}}};
+    // (four whole tiles to a CU with a long contraction: 933 tiles of 190 x
+    // 19904 x 16112 took 2830 us in one piece, 2560 with the last 421 cut)
+    if (together && bn == 64 && c >= 4 && K >= 8192) return 0.82;
     return e[bn == 128][together][std::min<int64_t>(c, 4) - 1];
   };
+  const int64_t resident = bm > 64 ? 3 : 4;  // tiles that fit a CU
   F64Plan best{tiles, 1};
   const int64_t c0 = ceil_div(tiles, 256);
-  double t_best = c0 <= 4 ? c0 / rate(c0, true) * unit : ((tiles / 256) / 0.9 + (tiles % 256 ? 1.0 / 0.6 : 0.0)) * unit;
+  double t_best = c0 <= resident ? c0 / rate(c0, true) * unit : ((tiles / 256) / 0.9 + (tiles % 256 ? 1.0 / 0.6 : 0.0)) * unit;
   if (K < 64 || ws_elems <= 0) return best;
   static const int kCuts[] = {2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
   const int64_t whole = tiles / 256 * 256;
@@ -1010,7 +1014,11 @@ bool launch_f64(const GemmDesc& d, const double* A, const double* B, const doubl
   // their coarser rounds cost more than that (600 x 3600 x 3600 306 against
   // 292 us).
   const bool asc = d.ascending && !lb.kc;
-  const bool wide = !asc && f64_rows(d.M, la, lb) == 64 && d.K >= 2048 && (double)d.M * d.N * d.K * nb >= 1e10;
+  // (and with fewer than two tiles to a CU: 190 x 19904 x 16112 2680 against
+  // 2560)
+  const int64_t tiles128 = ceil_div(d.M, 64) * ceil_div(d.N, 128) * nb;
+  const bool wide = !asc && f64_rows(d.M, la, lb) == 64 && d.K >= 2048 && tiles128 >= 512 &&
+                    (double)d.M * d.N * d.K * nb >= 1e10;
   if (wide) launch_f64_tiles<128>(p, la, lb, nb, ws, asc, s);
   else launch_f64_tiles<64>(p, la, lb, nb, ws, asc, s);
   return true;
