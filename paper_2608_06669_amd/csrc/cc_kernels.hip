@@ -197,8 +197,8 @@ __device__ inline void upair_inverse(int k, int n, int* x, int* y) {
 // t: a workgroup takes the 32 x 32 tiles (A, B) and (B, A), A <= B, of one
 // pair (i, j), so each element meets its exchange partner t_ij^ba in LDS and
 // all writes run along rows. HBM-bound: at o = 20, v = 180 (104 MB per
-// array; one read, four written without U, Uklca, Uail) 97 us, in place of a
-// pass per layout and the ladder's packing (ten launches, 0.46 ms).
+// array) 72 us with one read and three written, 200 us with seven, in place of
+// a pass per layout and the ladder's packing (ten launches, 0.46 ms).
 constexpr int kT = 32;
 
 __global__ __launch_bounds__(256) void amp_layouts_kernel(int o, int v, int tiles, AmpLayouts p) {
@@ -262,9 +262,10 @@ __global__ __launch_bounds__(256) void amp_layouts_kernel(int o, int v, int tile
 // the ladder unpacked from its symmetric and antisymmetric combinations (E
 // may be null). A workgroup takes the tiles (A, B), (B, A), A <= B, of (i, j)
 // and (j, i), i <= j: each part is read once, along rows, transposed
-// partners meet in LDS. HBM-bound: at o = 20, v = 180 126 us for five arrays
-// of 104 MB read and one written, in place of two permutations into X, one
-// into R, the unpacking and the pair sum (five launches, 0.40 ms).
+// partners meet in LDS. HBM-bound: at o = 20, v = 180 119 us for four arrays
+// of 104 MB read (S from cache where it is read again) and one written, in place
+// of two permutations into X, one into R, the unpacking and the pair sum (five
+// launches, 0.40 ms).
 __global__ __launch_bounds__(256) void doubles_sum_kernel(int o, int v, int tiles, DoublesParts p) {
   __shared__ double st[kT][kT + 1], sx[kT][kT + 1];
   int A, B, i, j;

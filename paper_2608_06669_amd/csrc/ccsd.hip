@@ -147,13 +147,11 @@ struct Sizes {
   }
 };
 
-// Split-K scratch. Products with few output tiles, or with a long
-// contraction, split it; the chunk count is also capped by this size
-// (splits * M * N * batch must fit). 16 times the largest o^2 v^2-class
-// tensor, at most 16 M elements (128 MB): room for the four chunks of the
-// o v x o v products at o = 10, v = 90, the twelve of their 300 x 900 x 900
-// ones, and the three to seven chunks of the ladder products at o = 20,
-// v = 180.
+// Split-K scratch. Products with few output tiles, or whose last tiles would
+// leave the chip idle, cut them along k; the chunk count is also capped by
+// this size. 16 times the largest o^2 v^2-class tensor, at most 16 M elements
+// (128 MB): room for eight chunks of the last 177 tiles of the ladder at o =
+// 20, v = 180.
 int64_t splitk_elems(const Sizes& z) {
   const int64_t big = std::max<int64_t>({z.o * z.o * z.v * z.v, z.ov * z.ov, (int64_t)z.o * z.o * z.o * z.o});
   return std::min<int64_t>(std::max<int64_t>(16 * big, 1 << 16), 16 * 1024 * 1024);
@@ -177,8 +175,8 @@ void for_each_buffer(const Sizes& z, const EngineOptions& opt, F f, G g) {
   f(o * o); f(ov); f(v * v); f(n * n); f(n * n); f(naux); f(naux * o * n);
   f(np * o * o); f(np * ov); f(np * ov); f(np * v * v);
   const int64_t p2 = z.p2, p2m = z.p2m;
-  f(z.p2k * z.ldp); f(z.p2mk * z.ldm); f(z.wna * v * v * v); g(4 * (2 * p2 + 2 * p2m));
-  for (int k = 0; k < 5; ++k) f(n2);
+  f(z.p2k * z.ldp); f(z.p2mk * z.ldm); f(z.wna * v * v * v); g(4 * p2); g(4 * p2); g(4 * p2m); g(4 * p2m);
+  for (int k = 0; k < 4; ++k) f(n2);
   if (opt.lowp_f32) {
     g(4 * p2 * pad_to(p2, 4)); g(4 * p2m * pad_to(p2m, 4));
     g(4 * o * v * v * v); g(4 * n2); g(4 * n2); g(4 * n2); g(4 * n2);
@@ -192,14 +190,17 @@ void for_each_buffer(const Sizes& z, const EngineOptions& opt, F f, G g) {
   for (int rep = 0; rep < 2; ++rep) {
     f(np * o * o); f(np * ov); f(np * v * v); f(naux); f(naux * o * o);
     f(o * o); f(ov); f(v * v);
-    for (int k = 0; k < 4; ++k) f(n2);  // Tsia, Uia, Tmp, X
-    f(v * v); f(o * o); f(o * o * o * o); f(o * o * o * o); f(o * o * ov);
+    f(n2); f(n2);  // Tsia, Uia
+    f(v * v); f(o * o); f(o * o * o * o); f(o * o * ov);
     f(n2); f(n2);                       // M, K
-    f(naux * ov); f(naux * ov); f(o * o * ov);
-    f(z.o2k * z.p2k); f(z.o2mk * z.p2mk); f(z.o2 * z.ldp); f(z.o2m * z.ldm);  // Tp, Tm, Rp, Rm
-    f(z.o2 * z.o2k); f(z.o2m * z.o2mk);  // Wp, Wm
+    f(naux * ov); f(o * o * ov);  // QT, Kilc
+    f(z.o2k * z.p2k); f(z.o2mk * z.p2mk);  // Tp, Tm
+    if (rep == 0) {  // Tmp, X, Kilj, Q, Rp, Rm
+      f(n2); f(n2); f(o * o * o * o); f(naux * ov); f(z.o2 * z.ldp); f(z.o2m * z.ldm);
+    }
+    if (rep == 0 || o == 1 || !(opt.lowp_f32 || opt.lowp_bf16)) { f(z.o2 * z.o2k); f(z.o2m * z.o2mk); }  // Wp, Wm
     if (opt.lowp_f32 || opt.lowp_bf16) {  // Tia, U, Uklca, Uail, J, KilcT, Wkl
-      for (int k = 0; k < 5; ++k) f(n2);
+      for (int k = 0; k < 5 - 2 * rep; ++k) f(n2);
       f(o * o * ov); f(o * o * o * o);
     }
   }
@@ -216,7 +217,7 @@ size_t engine_bytes(int o, int v, int naux, const EngineOptions& opt) {
   size_t total = 0;
   auto add = [&](int64_t bytes) { total += ((size_t)bytes + 255) & ~size_t(255); };
   for_each_buffer(z, opt, [&](int64_t nd) { add(nd * 8); }, [&](int64_t nb) { add(nb); });
-  return total + 4096;
+  return total + 256;
 }
 
 // ----------------------------------------------------------- engine -----
@@ -236,7 +237,7 @@ Engine::Engine(int o, int v, int naux, const EngineOptions& opt)
   S.v = take(z.p2k * z.ldp); Am.v = take(z.p2mk * z.ldm); wblk_ = take(z.wna * V * V * V);
   pair_a_ = arena_.take<int>(z.p2); pair_b_ = arena_.take<int>(z.p2);
   mpair_a_ = arena_.take<int>(z.p2m); mpair_b_ = arena_.take<int>(z.p2m);
-  Ioovv.v = take(N2); Iovov.v = take(N2); Ix.v = take(N2); Lh.v = take(N2); Itil.v = take(N2);
+  Iovov.v = take(N2); Ix.v = take(N2); Lh.v = take(N2); Itil.v = take(N2);
   // the low-precision ladder tensors keep rows of a 16-byte multiple (the
   // pair counts v(v+1)/2, v(v-1)/2 need not be), for vector loads
   ld32_ = pad_to(z.p2, 4); ld32m_ = pad_to(z.p2m, 4);
@@ -273,12 +274,25 @@ Engine::Engine(int o, int v, int naux, const EngineOptions& opt)
                          N2, N2, N2, N2, N2, O * O * OV, O * O * O * O};
   const size_t nlow = opt.lowp_f32 || opt.lowp_bf16 ? 0 : 7;  // the last seven: FP32 / BF16 only
   static_assert(sizeof(inter) / sizeof(inter[0]) == sizeof(isz) / sizeof(isz[0]), "buffer table");
+  // read only in the pass that writes them: one array for value and tangent
+  Ten* scratch[] = {&Tmp, &X, &Kilj, &Q, &Rp, &Rm};
   for (int rep = 0; rep < 2; ++rep)
     for (size_t k = 0; k + nlow < sizeof(isz) / sizeof(isz[0]); ++k) {
-      if (rep == 0) inter[k]->v = take(isz[k]);
-      else inter[k]->d = take(isz[k]);
-      inter[k]->var = true;
+      Ten* t = inter[k];
+      t->var = true;
+      if (rep == 0) t->v = take(isz[k]);
+      else if (std::find(std::begin(scratch), std::end(scratch), t) != std::end(scratch)) t->d = t->v;
+      else if (t != &J && t != &Uail && (nlow != 0 || o == 1 || (t != &Wp && t != &Wm))) t->d = take(isz[k]);
     }
+  // An FP64 tangent has M, Wp and Wm, one in FP32 or BF16 J and Wkl (o^4 >=
+  // o2 o2k + o2m o2mk from two occupied orbitals on)
+  J.d = M.d;
+  Uail.d = Tmp.d;  // (read before Tmp is first written)
+  if (!nlow && o > 1) {
+    Wp.d = Wkl.d;
+    Wm.d = Wkl.d + z.o2 * z.o2k;
+  }
+  Ioovv.v = X.v;  // (prepare only: products read its copies)
   partials_ = take(reduce_partials_size(64));
   zeros_ = take(OV + N2);
   ws_elems_ = splitk_elems(z);
@@ -751,7 +765,7 @@ void Engine::run(Mode m) {
     g.beta = beta;
     return g;
   };
-  Ten KT = M;  // - K t in a tangent array that is free: a value pass has none yet, a tangent has read it by then
+  Ten KT = M;  // - K t in the tangent of M (J), free: a value pass has none yet, a tangent has read it by then
   KT.v = KT.d;
   const Ten* E = nullptr;
   double w = 0.0;

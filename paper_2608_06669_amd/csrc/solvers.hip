@@ -311,8 +311,8 @@ bool Solver::ensure_inner_graph(const InnerSolve& q, bool timed, int nb) {
 // Fock blocks (inner_solve.hpp): b is rotated into them and x back. Everything
 // stays on the device, including the stopping test; the host reads the
 // outcome once per batch of queued steps. At o = 20, v = 180 and rtol 1e-12
-// this takes 1440 us, a third of them the rotations; on the given orbitals,
-// with the Fock products in every step, it took 7900 (o = 10, v = 90: 400
+// this takes 1285 us, a third of them the rotations; on the given orbitals,
+// with the Fock products in every step, it took 7900 (o = 10, v = 90: 350
 // and 960).
 int Solver::precond_solve_sym(const FockEigen& eig, VecIn b, VecOut x, double rtol, int maxit, hipStream_t s,
                               bool* converged, bool pair_symmetric) {
