@@ -614,8 +614,13 @@ void Engine::prepare(const ProblemView& p, hipStream_t s, bool with_eigen) {
   if (S.lp16) cast_f64_to_bf16_rows(p2, p2, ld16_, S.v, ldp, (uint16_t*)S.lp16, s, pair_a_, pair_b_);
   if (Am.lp32) cast_f64_to_f32_rows(p2m, p2m, ld32m_, Am.v, ldm, (float*)Am.lp32, s);
   if (Am.lp16) cast_f64_to_bf16_rows(p2m, p2m, ld16m_, Am.v, ldm, (uint16_t*)Am.lp16, s);
-  for (Ten* t : {&Ioovv, &Iovov, &Ix})
-    if (t->lp32) cast_f64_to_f32(n2_, t->v, (float*)t->lp32, s);
+  if (Ioovv.lp32) cast_f64_to_f32(n2_, Ioovv.v, (float*)Ioovv.lp32, s);
+  for (Ten* t : {&Iovov, &Ix})  // FP32 ring integrals transposed, read along k (staged in Tmp)
+    if (t->lp32) {
+      const int dims[4] = {o, v, o, v}, pm[4] = {2, 3, 0, 1};
+      permute4(t->v, Tmp.v, dims, pm, 1.0, 0.0, s);
+      cast_f64_to_f32(n2_, Tmp.v, (float*)t->lp32, s);
+    }
   if (Ioovv.lp16) cast_f64_to_bf16(n2_, Ioovv.v, (uint16_t*)Ioovv.lp16, s);
   if (Iovov.lp16) {
     cast_f64_to_bf16_rows(ov, ov, ldov16_, Iovov.v, ov, (uint16_t*)Iovov.lp16, s);
@@ -770,10 +775,10 @@ void Engine::run(Mode m) {
   const Ten* E = nullptr;
   double w = 0.0;
   if (lowp) {
-    // (BF16 tangents read the ring integrals along k: Iovov is symmetric, and
-    // the BF16 copy of Ix holds its transpose)
-    const bool kc16 = jprec_ == Prec::BF16 && Iovov.lp16;
-    GemmDesc g = gd(OV, OV, OV, ov, 1, kc16 ? 1 : ov, kc16 ? ldov16_ : 1, ov, 1);
+    // (the copies of the ring integrals are read along k: transposed, but
+    // for Iovov in BF16, which is symmetric)
+    const bool kc16 = jprec_ == Prec::BF16;
+    GemmDesc g = gd(OV, OV, OV, ov, 1, 1, kc16 ? ldov16_ : ov, ov, 1);
     if (kc16) g.b_kzero = ldov16_;
     mm(g0, Lvo, Lov0, J);                                          // (ai|kc)~
     mm(scaled(g, 0.5, 1.0), Uia, Iovov, J);

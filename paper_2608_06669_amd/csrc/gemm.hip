@@ -1,7 +1,7 @@
 // Matrix-core GEMM for gfx950 (CDNA4), FP64 / FP32 / BF16 compute.
 //
 // FP64 products run in gemm_f64_pipe (gemm_f64.hpp), BF16 ones of packed
-// operands in gemm_bf16_pipe; the others in gemm_kernel:
+// operands in gemm_pipe; the others in gemm_kernel:
 //
 // One workgroup = 4 wavefronts of 64 lanes computes a BM x BN tile of C.
 // The waves form a WGM x WGN grid; each wave owns (BM/WGM) x (BN/WGN)
@@ -425,12 +425,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_wide(KArgs p) {
   }
 }
 
-// BF16 product of two k-contiguous BF16 operands (rows 16-byte aligned, the
-// contraction a multiple of 64, zero-padded), BM x 128 tiles, 64-deep
-// panels in a ring of three LDS stages filled straight from global memory
+// Product of two k-contiguous operands in the compute type (rows 16-byte
+// aligned; BF16: the contraction a multiple of 64, zero-padded), BM x BN tiles,
+// panels of 128 bytes of k (64 BF16, 32 FP32) in a ring of three LDS stages filled straight from global memory
 // (16 bytes per lane, no register staging), so two panels' loads are in
 // flight while the matrix cores work on the third. A stage holds A then B,
-// [row][64] each; the eight 16-byte chunks of a row are stored at slot
+// [row][128 bytes] each; the eight 16-byte chunks of a row are stored at slot
 // chunk ^ ((row / 2) % 8), which spreads the fragment reads of 16
 // consecutive rows over all 64 banks (each wave's load writes 1 KB
 // contiguously: its lanes fetch the chunks in slot order). Each wave forms
@@ -439,18 +439,24 @@ __global__ __launch_bounds__(256) void splitk_reduce_wide(KArgs p) {
 // MI355X 1.1-1.4x faster than 128 x 128 on the 3600 x 3600 x 7232, 210 x
 // 16290 x 16290 and 400 x 3600 x 32400 products and 1.4x at 8192^3). Same
 // tile order, split-K and epilogue as gemm_kernel.
+// FP32: 128 x 64 tiles with 4 waves of 64 x 32 (72 KB: two workgroups per CU; 128
+// x 128 would leave 2304^2 outputs 1.3 tiles per CU), 16-byte chunks of k past
+// the end read as zeros; k in ascending order like gemm_kernel, the same
+// results: 2304^3 230 us where the register-staged 128 x 128 tiles took 405.
 template <int N>
 __device__ inline void wait_vm_lgkm0() {  // vmcnt(N), lgkmcnt(0)
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
 }
 
-template <int BM, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_bf16_pipe(KArgs p) {
-  constexpr int BN = 128, BK = 64, STAGES = 3, NT = 64 * NW;
-  static_assert(BM == 64 * (NW / 2), "one 64 x 64 block per wave, two waves across the tile");
-  constexpr int SE = (BM + BN) * BK;                             // elements per stage
-  constexpr int CA = BM * BK / 8 / NT, CB = BN * BK / 8 / NT;  // 16-byte chunks per thread and stage
-  __shared__ __attribute__((aligned(1024))) uint16_t st0[SE], st1[SE], st2[SE];
+template <typename T, int BM, int BN, int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_pipe(KArgs p) {
+  constexpr bool f32 = sizeof(T) == 4;
+  constexpr int BK = 128 / (int)sizeof(T), CE = 16 / (int)sizeof(T), STAGES = 3, NT = 64 * NW;
+  static_assert(BM == 64 * (NW / 2), "64 rows per wave, two waves across the tile");
+  constexpr int WTN = BN / 2, TNJ = WTN / 16;
+  constexpr int SE = (BM + BN) * BK;                 // elements per stage
+  constexpr int CA = BM * 8 / NT, CB = BN * 8 / NT;  // 16-byte chunks per thread and stage
+  __shared__ __attribute__((aligned(1024))) T st0[SE], st1[SE], st2[SE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
 
@@ -474,68 +480,92 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_pipe(KArgs p) {
   const int b0 = blockIdx.y % p.nb0;
   const int b1 = blockIdx.y / p.nb0 + zb * (gridDim.y / p.nb0);
   const int kbeg = split * p.kchunk;
-  const int nk = (min(p.K, kbeg + p.kchunk) - kbeg) / BK;  // >= 1
-  const uint16_t* __restrict__ Ag = (const uint16_t*)p.A + b0 * p.a_b0 + b1 * p.a_b1 + kbeg;
-  const uint16_t* __restrict__ Bg = (const uint16_t*)p.B + b0 * p.b_b0 + b1 * p.b_b1 + kbeg;
+  const int klen = min(p.K, kbeg + p.kchunk) - kbeg;
+  const int nk = f32 ? (klen + BK - 1) / BK : klen / BK;  // >= 1
+  const T* __restrict__ Ag = (const T*)p.A + b0 * p.a_b0 + b1 * p.a_b1 + kbeg;
+  const T* __restrict__ Bg = (const T*)p.B + b0 * p.b_b0 + b1 * p.b_b1 + kbeg;
   double* Cg = (double*)p.C + b0 * p.c_b0 + b1 * p.c_b1;
   const double* Ci = (const double*)p.Cin + b0 * p.c_b0 + b1 * p.c_b1;
 
   // this thread's chunks c = j NT + tid (row c / 8, slot c % 8) of A (j <
   // CA) and of B (j < CB) (rows past the matrix read its last row; those
   // outputs are not written)
-  const uint16_t* ga[CA];
-  const uint16_t* gb[CB];
+  const T* ga[CA];
+  const T* gb[CB];
+  int ka[CA], kb[CB];  // their k within a panel
 #pragma unroll
   for (int j = 0; j < CA; ++j) {
     const int c = j * NT + tid, r = c >> 3, slot = c & 7, g = slot ^ ((r >> 1) & 7);
-    ga[j] = Ag + (int64_t)min(m0 + r, p.M - 1) * p.a_m + 8 * g;
+    ka[j] = CE * g;
+    ga[j] = Ag + (int64_t)min(m0 + r, p.M - 1) * p.a_m + CE * g;
   }
 #pragma unroll
   for (int j = 0; j < CB; ++j) {
     const int c = j * NT + tid, r = c >> 3, slot = c & 7, g = slot ^ ((r >> 1) & 7);
-    gb[j] = Bg + (int64_t)min(n0 + r, p.N - 1) * p.b_n + 8 * g;
+    kb[j] = CE * g;
+    gb[j] = Bg + (int64_t)min(n0 + r, p.N - 1) * p.b_n + CE * g;
   }
   // panel t into stage st (past the last panel: the last one again, never
-  // read). (The global address goes in as void*: converted implicitly, the
-  // host pass drops the template's launch stub.)
-  auto issue = [&](uint16_t* st, int t) {
+  // read)
+  auto issue = [&](T* st, int t) {
     const int k0 = min(t, nk - 1) * BK;
+    auto at = [&](const T* g, int k) -> const void* {
+      return !f32 || k0 + k < klen ? (const void*)(g + k0) : (const void*)f64pipe::zero_src;
+    };
 #pragma unroll
     for (int j = 0; j < CA; ++j)
-      __builtin_amdgcn_global_load_lds((const void*)(ga[j] + k0),
-                                       (__attribute__((address_space(3))) void*)(st + (j * NT + wave * 64) * 8), 16, 0, 0);
+      f64pipe::to_lds<true>(at(ga[j], ka[j]), (uint32_t*)st + (j * NT + wave * 64) * 4);
 #pragma unroll
     for (int j = 0; j < CB; ++j)
-      __builtin_amdgcn_global_load_lds((const void*)(gb[j] + k0),
-                                       (__attribute__((address_space(3))) void*)(st + BM * BK + (j * NT + wave * 64) * 8),
-                                       16, 0, 0);
+      f64pipe::to_lds<true>(at(gb[j], kb[j]), (uint32_t*)(st + BM * BK) + (j * NT + wave * 64) * 4);
   };
-  f4 acc[4][4];
+  f4 acc[4][TNJ];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](const uint16_t* st) {
+    for (int j = 0; j < TNJ; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](const T* st) {
+   if constexpr (f32) {
+#pragma unroll
+    for (int ks = 0; ks < BK / 4; ++ks) {  // k = 4 ks + lane / 16
+      float af[4], bfr[TNJ];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = wm * 64 + i * 16 + (lane & 15);
+        af[i] = st[row * BK + 4 * (ks ^ ((row >> 1) & 7)) + (lane >> 4)];
+      }
+#pragma unroll
+      for (int j = 0; j < TNJ; ++j) {
+        const int row = wn * WTN + j * 16 + (lane & 15);
+        bfr[j] = st[BM * BK + row * BK + 4 * (ks ^ ((row >> 1) & 7)) + (lane >> 4)];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < TNJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i], bfr[j], acc[i][j], 0, 0, 0);
+    }
+   } else {
 #pragma unroll
     for (int ks = 0; ks < BK / 32; ++ks) {
       const int q = 4 * ks + (lane >> 4);  // this lane's 8-element chunk of the 32-deep step
-      bf8 af[4], bfr[4];
+      bf8 af[4], bfr[TNJ];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = wm * 64 + i * 16 + (lane & 15);
         af[i] = __builtin_bit_cast(bf8, *reinterpret_cast<const u16x8*>(st + row * BK + 8 * (q ^ ((row >> 1) & 7))));
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = wn * 64 + j * 16 + (lane & 15);
+      for (int j = 0; j < TNJ; ++j) {
+        const int row = wn * WTN + j * 16 + (lane & 15);
         bfr[j] = __builtin_bit_cast(
             bf8, *reinterpret_cast<const u16x8*>(st + BM * BK + row * BK + 8 * (q ^ ((row >> 1) & 7))));
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < TNJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
     }
+   }
   };
   issue(st0, 0);
   issue(st1, 1);
@@ -545,7 +575,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_pipe(KArgs p) {
   // is done with the stage about to be refilled), refill that stage with
   // panel t + 2, and compute panel t. (A plain barrier: the workgroup fence
   // of __syncthreads would wait for all loads in flight.)
-  auto step = [&](int t, const uint16_t* cur, uint16_t* nxt) {
+  auto step = [&](int t, const T* cur, T* nxt) {
     wait_vm_lgkm0<(CA + CB) * (STAGES - 2)>();
     __builtin_amdgcn_s_barrier();
     issue(nxt, t + STAGES - 1);
@@ -571,13 +601,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_pipe(KArgs p) {
   // together before its writes
   const double alpha = p.alpha, beta = p.beta;
   auto row_of = [&](int i, int r) { return m0 + wm * 64 + i * 16 + 4 * (lane >> 4) + r; };
-  auto col_of = [&](int j) { return n0 + wn * 64 + j * 16 + (lane & 15); };
+  auto col_of = [&](int j) { return n0 + wn * WTN + j * 16 + (lane & 15); };
   if (p.splits > 1) {
     double* __restrict__ W = p.ws + ((int64_t)split * p.nbtot + (int64_t)b1 * p.nb0 + b0) * p.M * p.N;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < TNJ; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           if (row_of(i, r) < p.M && col_of(j) < p.N) W[(int64_t)row_of(i, r) * p.N + col_of(j)] = (double)acc[i][j][r];
@@ -585,7 +615,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_pipe(KArgs p) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < TNJ; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           if (row_of(i, r) < p.M && col_of(j) < p.N)
@@ -593,14 +623,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_pipe(KArgs p) {
   } else {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      double cv[4][4];
+      double cv[TNJ][4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < TNJ; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           cv[j][r] = Ci[min(row_of(i, r), p.M - 1) * p.c_m + min(col_of(j), p.N - 1) * p.c_n];
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < TNJ; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           if (row_of(i, r) < p.M && col_of(j) < p.N)
@@ -809,6 +839,18 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
       return;
     }
   }
+  // FP32 operands both k-contiguous, in one piece
+  constexpr bool pipe32 = std::is_same<Mma, MmaF32>::value && std::is_same<TA, float>::value &&
+                          std::is_same<TB, float>::value && BM == 128;
+  if constexpr (pipe32) {
+    if (akc && bkc && !A2 && p.a_vec && p.b_vec && splits == 1 && d.K % 4 == 0) {
+      KArgs q = p;
+      q.tiles_n = (int)ceil_div(d.N, 64);
+      gemm_pipe<float, 128, 64, 4><<<dim3((unsigned)(q.tiles_m * q.tiles_n), grid.y, grid.z), 256, 0, s>>>(q);
+      PNK_CHECK_LAUNCH();
+      return;
+    }
+  }
   if (pipe_cfg && akc && bkc && !A2 && d.K % 64 == 0 && p.a_vec && p.b_vec && d.M > 128) {
     // more than 128 rows: 256 x 128 tiles with 8 waves, one workgroup per
     // CU. Tiles that cannot fill the GPU take split-K in whole rounds of
@@ -835,13 +877,13 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
     q.splits = sp;
     PNK_REQUIRE(gz * sp <= 65535, "gemm: batch too large");
     dim3 g2((unsigned)(q.tiles_m * q.tiles_n), (unsigned)gy, (unsigned)(gz * sp));
-    gemm_bf16_pipe<256, 8><<<g2, 512, 0, s>>>(q);
+    gemm_pipe<uint16_t, 256, 128, 8><<<g2, 512, 0, s>>>(q);
     PNK_CHECK_LAUNCH();
     reduce(q);
     return;
   }
   if (pipe_cfg && akc && bkc && !A2 && d.K % 64 == 0 && p.a_vec && p.b_vec) {
-    gemm_bf16_pipe<128, 4><<<grid, 256, 0, s>>>(p);
+    gemm_pipe<uint16_t, 128, 128, 4><<<grid, 256, 0, s>>>(p);
   } else if constexpr (f64) gemm_kernel<Mma, TA, TB, TC, BM, BN, BK, WGM, false, false><<<grid, 256, 0, s>>>(p);
   else if (akc && bkc) gemm_kernel<Mma, TA, TB, TC, BM, BN, BK, WGM, true, true><<<grid, 256, 0, s>>>(p);
   else if (akc) gemm_kernel<Mma, TA, TB, TC, BM, BN, BK, WGM, true, false><<<grid, 256, 0, s>>>(p);

@@ -34,3 +34,22 @@ def test_thin_product(M, N, K, nb, ta, tb, prec):
                              prec=prec, precast=precast, splitk=splitk)
         torch.cuda.synchronize()
         assert bool(((Cd.cpu() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(2049, 2047, 4), (2048, 2048, 32), (2049, 2047, 36), (2050, 2113, 100), (2049, 2047, 1028)])
+def test_wide_fp32_product(M, N, K):
+    """FP32 products in one piece with both operands rounded beforehand: ragged
+    128 x 64 tiles, one to 33 panels of 32 with and without a remainder."""
+    import paper_2608_06669_amd as pk
+    g = torch.Generator(device="cpu").manual_seed(K)
+    A = torch.randn(M, K, generator=g, dtype=torch.float64)
+    B = torch.randn(K, N, generator=g, dtype=torch.float64)
+    C = torch.randn(M, N, generator=g, dtype=torch.float64)
+    a, b = A.float().double(), B.float().double()
+    want = 0.5 * a @ b - 2.0 * C
+    bound = (K + 2) * 2.0 ** -23 * (0.5 * a.abs() @ b.abs()) + 1e-14 * C.abs() + 1e-14
+    Cd = C.cuda()
+    pk.diag_gemm_batched(A.cuda(), B.cuda(), Cd, (K, 1, 0), (N, 1, 0), (N, 1, 0), M, N, K, 1, alpha=0.5, beta=-2.0,
+                         prec="fp32", precast=True, splitk=True)
+    torch.cuda.synchronize()
+    assert bool(((Cd.cpu() - want).abs() <= bound).all())
