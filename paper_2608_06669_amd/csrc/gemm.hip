@@ -897,9 +897,12 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
 // ---- FP64: gemm_f64_pipe ----
 
 // An operand's layout for gemm_f64_pipe: contiguous along k (kc) or along its
-// row index, the stride of the other index, and whether 16-byte loads apply.
+// row index, the stride of the other index, whether 16-byte loads apply, and
+// whether a tile's offsets need 64 bits (rows from 2^22 elements on, or stored
+// backwards): 20 x 20 x 4232000 (o = 20, v = 460) takes 3.48 ms, rows of 4176980
+// elements with 32-bit offsets 3.29, gemm_kernel's element-wise loads 8.55.
 struct F64Layout {
-  bool ok, kc, vec;
+  bool ok, kc, vec, far;
   int64_t ld;
 };
 F64Layout f64_layout(const void* x, const void* x2, int rows, int K, int64_t s_r, int64_t s_k, int64_t s_b0, int64_t s_b1) {
@@ -908,8 +911,7 @@ F64Layout f64_layout(const void* x, const void* x2, int rows, int K, int64_t s_r
   l.ok = l.kc || s_r == 1 || rows == 1;
   const int64_t ld = l.kc ? s_r : s_k;
   l.ld = (l.kc ? rows : K) == 1 ? 0 : ld;
-  // the kernel keeps a tile's offsets in 32 bits
-  l.ok = l.ok && l.ld >= 0 && l.ld < (int64_t(1) << 22);
+  l.far = l.ld < 0 || l.ld >= (int64_t(1) << 22);
   l.vec = aligned16(x) && (!x2 || aligned16(x2)) && l.ld % 2 == 0 && s_b0 % 2 == 0 && s_b1 % 2 == 0 &&
           (l.kc ? K : rows) % 2 == 0;
   return l;
@@ -968,10 +970,20 @@ F64Plan f64_plan(int64_t tiles, int bm, int bn, int K, int64_t sum_elems, int64_
   return best;
 }
 
-template <int BN, bool A_KC, bool B_KC>
+template <int BN, bool A_KC, bool B_KC, bool LONG = false, bool ASC = !A_KC && !B_KC>
 void launch_f64_layout(const f64pipe::Args& p, bool vec, unsigned grid, hipStream_t s) {
-  if (vec) f64pipe::gemm_f64_pipe<64, BN, A_KC, B_KC, true><<<grid, 256, 0, s>>>(p);
-  else f64pipe::gemm_f64_pipe<64, BN, A_KC, B_KC, false><<<grid, 256, 0, s>>>(p);
+  if (vec) f64pipe::gemm_f64_pipe<64, BN, A_KC, B_KC, true, LONG, ASC><<<grid, 256, 0, s>>>(p);
+  else f64pipe::gemm_f64_pipe<64, BN, A_KC, B_KC, false, LONG, ASC><<<grid, 256, 0, s>>>(p);
+}
+
+// LONG: the tile kept to 64 x 64
+template <int BN, bool LONG>
+void launch_f64_kernel(const f64pipe::Args& p, bool akc, bool bkc, bool vec, bool asc, unsigned grid, hipStream_t s) {
+  if (akc && bkc) launch_f64_layout<BN, true, true, LONG>(p, vec, grid, s);
+  else if (akc && BN == 64 && asc) launch_f64_layout<64, true, false, LONG, true>(p, vec, grid, s);
+  else if (akc) launch_f64_layout<BN, true, false, LONG>(p, vec, grid, s);
+  else if (bkc) launch_f64_layout<BN, false, true, LONG>(p, vec, grid, s);
+  else launch_f64_layout<BN, false, false, LONG>(p, vec, grid, s);
 }
 
 // Rows of a tile for M rows: the count that pads least, 64 if another saves less
@@ -981,7 +993,7 @@ void launch_f64_layout(const f64pipe::Args& p, bool vec, unsigned grid, hipStrea
 // took 72 us where two of 48 rows take 64, 91 x 5464 x 4192.)
 int f64_rows(int M, const F64Layout& la, const F64Layout& lb) {
   int best = 64;
-  if (!la.kc || lb.kc || !la.vec || !lb.vec) return best;
+  if (!la.kc || lb.kc || !la.vec || !lb.vec || la.far || lb.far) return best;
   static const int kRows[] = {72, 80, 48};
   int64_t pad = ceil_div(M, 64) * 64 * 95 / 100;
   for (int r : kRows) {
@@ -1015,13 +1027,8 @@ void launch_f64_tiles(f64pipe::Args p, const F64Layout& la, const F64Layout& lb,
   if (p.bm == 72) f64pipe::gemm_f64_pipe<72, 64, true, false, true><<<grid, 256, 0, s>>>(p);
   else if (p.bm == 80) f64pipe::gemm_f64_pipe<80, 64, true, false, true><<<grid, 256, 0, s>>>(p);
   else if (p.bm == 48) f64pipe::gemm_f64_pipe<48, 64, true, false, true><<<grid, 256, 0, s>>>(p);
-  else if (la.kc && lb.kc) launch_f64_layout<BN, true, true>(p, vec, grid, s);
-  else if (la.kc && BN == 64 && asc) {
-    if (vec) f64pipe::gemm_f64_pipe<64, 64, true, false, true, true><<<grid, 256, 0, s>>>(p);
-    else f64pipe::gemm_f64_pipe<64, 64, true, false, false, true><<<grid, 256, 0, s>>>(p);
-  } else if (la.kc) launch_f64_layout<BN, true, false>(p, vec, grid, s);
-  else if (lb.kc) launch_f64_layout<BN, false, true>(p, vec, grid, s);
-  else launch_f64_layout<BN, false, false>(p, vec, grid, s);
+  else if (BN == 64 && (la.far || lb.far)) launch_f64_kernel<64, true>(p, la.kc, lb.kc, vec, asc, grid, s);
+  else launch_f64_kernel<BN, false>(p, la.kc, lb.kc, vec, asc, grid, s);
   PNK_CHECK_LAUNCH();
   if (p.ntail) {
     const int n = p.wr * p.wc;
@@ -1059,7 +1066,7 @@ bool launch_f64(const GemmDesc& d, const double* A, const double* B, const doubl
   // (and with fewer than two tiles to a CU: 190 x 19904 x 16112 2680 against
   // 2560)
   const int64_t tiles128 = ceil_div(d.M, 64) * ceil_div(d.N, 128) * nb;
-  const bool wide = !asc && f64_rows(d.M, la, lb) == 64 && d.K >= 2048 && tiles128 >= 512 &&
+  const bool wide = !asc && !la.far && !lb.far && f64_rows(d.M, la, lb) == 64 && d.K >= 2048 && tiles128 >= 512 &&
                     (double)d.M * d.N * d.K * nb >= 1e10;
   if (wide) launch_f64_tiles<128>(p, la, lb, nb, ws, asc, s);
   else launch_f64_tiles<64>(p, la, lb, nb, ws, asc, s);

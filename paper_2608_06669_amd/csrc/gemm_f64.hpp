@@ -2,6 +2,8 @@
 // operand addressing). Included by gemm.hip only.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace pnk {
@@ -97,7 +99,10 @@ static __device__ __align__(16) double zero_src[2];
 // rows; along k, one 16-byte read per fragment becomes two of 8 bytes (all
 // products of a residual that way: 14.5 in place of 13.6 ms at o = 20, v =
 // 180), so those kernels otherwise take k = 0, 2, 4, 6 and 1, 3, 5, 7.
-template <int BM, int BN, bool A_KC, bool B_KC, bool VEC, bool ASC = !A_KC && !B_KC>
+//
+// LONG: rows of any length and direction, the lanes' offsets in 64 bits. In 32
+// bits, half the registers, they reach 128 rows of up to 2^22 elements.
+template <int BM, int BN, bool A_KC, bool B_KC, bool VEC, bool LONG = false, bool ASC = !A_KC && !B_KC>
 __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
   constexpr int BK = 8, NT = 256, AE = BM * BK, BE = BN * BK, SE = AE + BE;
   constexpr int WTM = BM / 2, WTN = BN / 2, TMI = WTM / 4, TNI = WTN / 16;
@@ -134,8 +139,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
   // this thread's loads j NT + tid: byte offsets from the tile's corner
   // (rows past the matrix read its last ones, whose outputs are not written)
   // and the k they hold
-  uint32_t oa[CA], ob[CB];
-  auto place = [&](int j, bool part, bool kc, int rows, int left, int64_t ld, uint32_t* off, int* k) {
+  using Offset = std::conditional_t<LONG, int64_t, uint32_t>;
+  Offset oa[CA], ob[CB];
+  auto place = [&](int j, bool part, bool kc, int rows, int left, int64_t ld, Offset* off, int* k) {
     const int w = (j * NT + (part ? wave * RA + min(lane, RA - 1) : tid)) * EPL;  // dword of the panel
     const int c = w >> 2, half = (w >> 1) & 1;  // 16-byte chunk, element of it
     int r, kk;
@@ -143,11 +149,11 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
       r = c >> 2;
       kk = 2 * ((c & 3) ^ ((r % (rows / 2) >> 2) & 3)) + half;
       r = min(r, left - 1);
-      *off = (uint32_t)(((int64_t)r * ld + kk) * 8 + (w & 1) * 4);
+      *off = (Offset)(((int64_t)r * ld + kk) * 8 + (w & 1) * 4);
     } else {
       kk = c / (rows / 2);
       r = min(2 * (c % (rows / 2)) + half, VEC ? left - 2 : left - 1);
-      *off = (uint32_t)(((int64_t)kk * ld + r) * 8 + (w & 1) * 4);
+      *off = (Offset)(((int64_t)kk * ld + r) * 8 + (w & 1) * 4);
     }
     *k = kk;
   };
@@ -187,14 +193,14 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
     const char *a = t ? A2 : A1, *bq = t ? B2 : B1, *z = (const char*)zero_src;
 #pragma unroll
     for (int j = 0; j < CA; ++j) {
-      uint32_t o;
+      Offset o;
       int k;
       place(j, j == FA, A_KC, BM, p.M - m0, p.lda, &o, &k);
       load_a(j, k < rem ? a + o : z, st);
     }
 #pragma unroll
     for (int j = 0; j < CB; ++j) {
-      uint32_t o;
+      Offset o;
       int k;
       place(j, false, B_KC, BN, p.N - n0, p.ldb, &o, &k);
       to_lds<VEC>(k < rem ? bq + o : z, (uint32_t*)(st + AE) + (j * NT + wave * 64) * EPL);
