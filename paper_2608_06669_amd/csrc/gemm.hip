@@ -698,6 +698,16 @@ __global__ __launch_bounds__(256) void gemm_smallk(KArgs p) {
   }
 }
 
+// The batch as gridDim.y gridDim.z, y a multiple of nb0, within the limit of
+// both (which a batch has to keep in every kernel, also one that counts its
+// workgroups otherwise).
+void batch_grid(const GemmDesc& d, int64_t* gy, int64_t* gz) {
+  *gy = d.nb0;
+  *gz = d.nb1;
+  while (*gy * 2 <= 65535 && *gz % 2 == 0) { *gy *= 2; *gz /= 2; }
+  PNK_REQUIRE(*gy <= 65535 && *gz <= 65535, "gemm: batch too large");
+}
+
 void launch_smallk(const GemmDesc& d, const void* A, const void* B, void* C, hipStream_t s) {
   KArgs p{};
   p.M = d.M; p.N = d.N; p.K = d.K; p.nb0 = d.nb0; p.splits = 1;
@@ -711,9 +721,8 @@ void launch_smallk(const GemmDesc& d, const void* A, const void* B, void* C, hip
   const bool long_n = d.N >= d.M;
   const int L = long_n ? d.N : d.M;
   const int S = long_n ? d.M : d.N;
-  int64_t gy = d.nb0, gz = d.nb1;
-  while (gy * 2 <= 65535 && gz % 2 == 0) { gy *= 2; gz /= 2; }
-  PNK_REQUIRE(gy <= 65535 && gz <= 65535, "gemm: batch too large");
+  int64_t gy, gz;
+  batch_grid(d, &gy, &gz);
   // one lane per index of the long side leaves a few waves per SIMD when
   // the long side is short of a million: split the short side into groups
   // (at most four) until about 4096 waves run
@@ -797,10 +806,9 @@ void launch_cfg(const GemmDesc& d, const void* A, const void* B, const void* A2,
   // CU); thin products with a long contraction stay near 512. Long
   // contractions with fewer than 512 tiles (one or two workgroups per CU,
   // each walking thousands of k steps) are split too.
-  // gridDim.y * gridDim.z covers the batch; y is a multiple of nb0, and z
-  // also carries the chunks
-  int64_t gy = d.nb0, gz = d.nb1;
-  while (gy * 2 <= 65535 && gz % 2 == 0) { gy *= 2; gz /= 2; }
+  // (z also carries the chunks)
+  int64_t gy, gz;
+  batch_grid(d, &gy, &gz);
   const bool thin = d.M <= 64 && d.K >= 1024;
   const int64_t ws_fit =
       d.ws ? std::min<int64_t>(d.ws_elems / std::max<int64_t>(1, nb * d.M * d.N), 65535 / gz) : 0;
@@ -971,14 +979,14 @@ F64Plan f64_plan(int64_t tiles, int bm, int bn, int K, int64_t sum_elems, int64_
 }
 
 template <int BN, bool A_KC, bool B_KC, bool LONG = false, bool ASC = !A_KC && !B_KC>
-void launch_f64_layout(const f64pipe::Args& p, bool vec, unsigned grid, hipStream_t s) {
+void launch_f64_layout(const f64pipe::Args& p, bool vec, dim3 grid, hipStream_t s) {
   if (vec) f64pipe::gemm_f64_pipe<64, BN, A_KC, B_KC, true, LONG, ASC><<<grid, 256, 0, s>>>(p);
   else f64pipe::gemm_f64_pipe<64, BN, A_KC, B_KC, false, LONG, ASC><<<grid, 256, 0, s>>>(p);
 }
 
 // LONG: the tile kept to 64 x 64
 template <int BN, bool LONG>
-void launch_f64_kernel(const f64pipe::Args& p, bool akc, bool bkc, bool vec, bool asc, unsigned grid, hipStream_t s) {
+void launch_f64_kernel(const f64pipe::Args& p, bool akc, bool bkc, bool vec, bool asc, dim3 grid, hipStream_t s) {
   if (akc && bkc) launch_f64_layout<BN, true, true, LONG>(p, vec, grid, s);
   else if (akc && BN == 64 && asc) launch_f64_layout<64, true, false, LONG, true>(p, vec, grid, s);
   else if (akc) launch_f64_layout<BN, true, false, LONG>(p, vec, grid, s);
@@ -1023,7 +1031,8 @@ void launch_f64_tiles(f64pipe::Args p, const F64Layout& la, const F64Layout& lb,
   p.ts = (int)ceil_div(p.K, p.kchunk);  // no empty chunk
   p.nfull = (int)(p.ts > 1 ? plan.nfull : tiles);
   p.ntail = (int)(tiles - p.nfull);
-  const unsigned grid = (unsigned)(p.nfull + (int64_t)p.ntail * p.ts);
+  const int64_t items = p.nfull + (int64_t)p.ntail * p.ts;
+  const dim3 grid((unsigned)std::min(items, f64pipe::kMaxGridX), (unsigned)ceil_div(items, f64pipe::kMaxGridX));
   if (p.bm == 72) f64pipe::gemm_f64_pipe<72, 64, true, false, true><<<grid, 256, 0, s>>>(p);
   else if (p.bm == 80) f64pipe::gemm_f64_pipe<80, 64, true, false, true><<<grid, 256, 0, s>>>(p);
   else if (p.bm == 48) f64pipe::gemm_f64_pipe<48, 64, true, false, true><<<grid, 256, 0, s>>>(p);
@@ -1046,6 +1055,8 @@ bool launch_f64(const GemmDesc& d, const double* A, const double* B, const doubl
   const F64Layout la = f64_layout(A, A2, d.M, d.K, d.a_m, d.a_k, d.a_b0, d.a_b1);
   const F64Layout lb = f64_layout(B, B2, d.N, d.K, d.b_n, d.b_k, d.b_b0, d.b_b1);
   if (!la.ok || !lb.ok) return false;
+  int64_t gy, gz;
+  batch_grid(d, &gy, &gz);
   f64pipe::Args p{};
   p.M = d.M; p.N = d.N; p.K = d.K; p.nb0 = d.nb0;
   p.A = A; p.B = B; p.A2 = A2; p.B2 = A2 ? B2 : nullptr;

@@ -65,6 +65,11 @@ __device__ inline void to_lds(const void* src, uint32_t* dst) {
   else __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
 }
 
+// A launch holds fewer than 2^32 threads along x: products of more tiles and
+// chunks than this take gridDim.y rows of them (a multiple of 8, as
+// xcd_range needs).
+constexpr int64_t kMaxGridX = int64_t(1) << 23;
+
 // 16 zero bytes that a remainder panel reads in place of k past the end
 static __device__ __align__(16) double zero_src[2];
 
@@ -116,12 +121,14 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
+  const uint32_t item = blockIdx.y * gridDim.x + blockIdx.x;  // (the last row of the grid may pass the end)
+  if (item >= (uint32_t)(p.nfull + p.ntail * p.ts)) return;
   int tile, split = 0, nsplit = 1;
-  if ((int)blockIdx.x < p.nfull) {
-    tile = xcd_range(blockIdx.x, p.nfull);
+  if ((int)item < p.nfull) {
+    tile = xcd_range(item, p.nfull);
   } else {
     nsplit = p.ts;
-    const int e = xcd_range(blockIdx.x - p.nfull, p.ntail * p.ts);
+    const int e = xcd_range(item - p.nfull, p.ntail * p.ts);
     split = e / p.ntail;
     tile = p.nfull + e - split * p.ntail;
   }
