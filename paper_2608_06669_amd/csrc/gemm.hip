@@ -932,11 +932,13 @@ F64Layout f64_layout(const void* x, const void* x2, int rows, int K, int64_t s_r
 // 128 tile 0.456), w units of work per CU take w / e with e the share of the
 // matrix rate that the c workgroups resident on a CU reach (measured; a
 // little less where every one ends at once). Chunk sums cost a launch (5 us)
-// and their bytes twice at 4 TB/s. Checked on MI355X against every (nfull,
-// ts) of a sweep over 45 products, 64^3 to 3600^3 and 20 x 20 x 648000 among
-// them: the choice is within 5 % of the best for most and 12 % for the
-// worst. 3600^3 takes 1691 us in whole tiles and 1508 with its last 177 tiles
-// in four chunks; 90 x 90 x 9000 562 us in one piece, 20 us in 63.
+// and their bytes twice at 4 TB/s. Checked on MI355X against every (nfull, ts)
+// that it considers, for 85 products from 64^3 to 3600^3, the ladders of o/v =
+// 10/90 to 20/180 and 20 x 20 x 648000 among them: the choice is within 5 % of
+// the best for 58 and within 14 % for all but three (128^3 13 us for 10, 91 x
+// 5464 x 4192 107 for 90, 1700 x 2200 x 9000 1299 for 1104). 3600^3 takes 1508
+// us with its last 177 64 x 64 tiles in four chunks and 1691 in whole tiles; 90
+// x 90 x 9000 20 us in 63 chunks and 562 in one piece.
 struct F64Plan {
   int64_t nfull;
   int ts;
@@ -946,12 +948,20 @@ F64Plan f64_plan(int64_t tiles, int bm, int bn, int K, int64_t sum_elems, int64_
   auto rate = [&](int64_t c, bool together) {
     static const double e[2][2][4] = {{{0.50, 0.72, 0.85, 0.90}, {0.50, 0.65, 0.78, 0.82}},
                                       {{0.76, 0.85, 0.90, 0.92}, {0.76, 0.74, 0.85, 0.85}}};
-    // (four whole tiles to a CU with a long contraction: 933 tiles of 190 x
-    // 19904 x 16112 took 2830 us in one piece, 2560 with the last 421 cut)
+    // (four whole tiles to a CU with a long contraction are slower than that:
+    // 190 x 19904 x 16112, 933 tiles, takes 2423 us in one piece and 2126 with
+    // the last 165 cut, 250 x 13000 x 9000 1241 and 1055, 960 x 3900 x 16000
+    // 2268 and 2015; of seven such products one, 1700 x 2200 x 9000, loses: 1193
+    // and 1299)
     if (together && bn == 64 && c >= 4 && K >= 8192) return 0.82;
     return e[bn == 128][together][std::min<int64_t>(c, 4) - 1];
   };
-  const int64_t resident = bm > 64 ? 3 : 4;  // tiles that fit a CU
+  // tiles to a CU up to which they are taken to end together. Four 64 x 64 or
+  // three 72 x 64 tiles fit one. Of 64 x 128 tiles and, by registers, 80 x 64
+  // ones three and two fit, but with those counts here, in the rates and below
+  // the choice was no better for any of 80 products and worse for 2304^3 (433 us
+  // in place of 382): the rates above were fitted with these.
+  const int64_t resident = bm > 64 ? 3 : 4;
   F64Plan best{tiles, 1};
   const int64_t c0 = ceil_div(tiles, 256);
   double t_best = c0 <= resident ? c0 / rate(c0, true) * unit : ((tiles / 256) / 0.9 + (tiles % 256 ? 1.0 / 0.6 : 0.0)) * unit;
@@ -1067,15 +1077,16 @@ bool launch_f64(const GemmDesc& d, const double* A, const double* B, const doubl
   p.alpha = d.alpha; p.beta = d.beta;
   p.ws = d.ws;
   const int64_t nb = (int64_t)d.nb0 * d.nb1, ws = d.ws ? d.ws_elems : 0;
-  // The largest products hold the chip at its power limit (the instruction
-  // alone then reaches 72 TFLOP/s), where 64 x 128 tiles, which read LDS and
-  // L2 less for each flop, are 1 to 5 % faster: 3600^3 1441 against 1508 us,
-  // 400 x 3600 x 32400 1692 against 1767. Below about 1e10 multiplications
-  // their coarser rounds cost more than that (600 x 3600 x 3600 306 against
-  // 292 us).
   const bool asc = d.ascending && !lb.kc;
-  // (and with fewer than two tiles to a CU: 190 x 19904 x 16112 2680 against
-  // 2560)
+  // 64 x 128 tiles read LDS and L2 less for each flop: where the largest
+  // products run at the rate that the instruction alone sustains (72 TFLOP/s),
+  // 1 to 6 % faster (3600^3 1430 against 1505 us, 2304^3 393 against 420, 1280 x
+  // 4096 x 4096 676 against 718). Their coarser rounds cost more than that below
+  // about 1e10 multiplications (600 x 3600 x 3600 321 against 310, 2000 x 2000
+  // x 2100 321 against 291), and mostly below 512 of them, two to a CU (190 x
+  // 19904 x 16112, 468, 2290 against 2140; 1800 x 1800 x 8192, 435, 1084 against
+  // 940; but 400 x 3600 x 32400, 203, 1675 against 1890). At 512 to 620 they gain
+  // in some products and lose in others, 8 % at most.
   const int64_t tiles128 = ceil_div(d.M, 64) * ceil_div(d.N, 128) * nb;
   const bool wide = !asc && !la.far && !lb.far && f64_rows(d.M, la, lb) == 64 && d.K >= 2048 && tiles128 >= 512 &&
                     (double)d.M * d.N * d.K * nb >= 1e10;
