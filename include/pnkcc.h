@@ -446,6 +446,17 @@ cc_status cc_diag_gemm_batched(int M, int N, int K, int nbatch, const double* A,
                                int64_t c_m, int64_t c_n, int64_t c_b, double alpha, double beta, cc_precision prec,
                                int flags, void* stream);
 
+/* The FP64 product in the other forms that the residual and J v use:
+ * C[b] = alpha (A[b] B[b] + A2[b] B2[b]) + beta Cin[b] for b < nbatch, A2 and
+ * B2 (both or neither) at A's and B's strides, Cin at C's (NULL: C itself).
+ * flags bit 0: sums in one piece and ascending k, whatever the tiles (where B
+ * is contiguous along n); bit 1: allow split-K. Scratch and synchronisation
+ * as in cc_diag_gemm_batched. */
+cc_status cc_diag_gemm_forms(int M, int N, int K, int nbatch, const double* A, const double* A2, int64_t a_m,
+                             int64_t a_k, int64_t a_b, const double* B, const double* B2, int64_t b_k, int64_t b_n,
+                             int64_t b_b, const double* Cin, double* C, int64_t c_m, int64_t c_n, int64_t c_b,
+                             double alpha, double beta, int flags, void* stream);
+
 /* ---------------------------------------------------------------------
  * Allocation-free product (for callers that cannot allocate device memory:
  * code under HIP graph capture, tight serving loops, harnesses that forbid

@@ -305,6 +305,19 @@ def diag_gemm_batched(A, B, C, a_strides, b_strides, c_strides, M, N, K, nbatch,
     return C
 
 
+def diag_gemm_forms(A, B, C, a_strides, b_strides, c_strides, M, N, K, nbatch, A2=None, B2=None, Cin=None, alpha=1.0,
+                    beta=0.0, ascending=False, splitk=False, stream=None):
+    """C[b] = alpha (A[b] B[b] + A2[b] B2[b]) + beta Cin[b] in FP64
+    (cc_diag_gemm_forms)."""
+    A2, B2, Cin = (None if t is None else _ptr(t) for t in (A2, B2, Cin))
+    st = _lib().cc_diag_gemm_forms(M, N, K, nbatch, _ptr(A), A2, *a_strides, _ptr(B), B2, *b_strides, Cin, _ptr(C),
+                                   *c_strides, alpha, beta,
+                                   (1 if ascending else 0) | (2 if splitk else 0), _stream(stream))
+    if st != L.CC_OK:
+        raise CCError(st, "cc_diag_gemm_forms failed")
+    return C
+
+
 def gemm_noalloc(A, B, C, a_strides, b_strides, c_strides, M, N, K, nbatch, alpha=1.0, beta=0.0, prec="fp64",
                  precast=False, splitk=False, stream=None):
     """cc_gemm_noalloc: diag_gemm_batched's product with its scratch in the

@@ -772,4 +772,42 @@ cc_status cc_diag_gemm_batched(int M, int N, int K, int nbatch, const double* A,
   return st;
 }
 
+cc_status cc_diag_gemm_forms(int M, int N, int K, int nbatch, const double* A, const double* A2, int64_t a_m,
+                             int64_t a_k, int64_t a_b, const double* B, const double* B2, int64_t b_k, int64_t b_n,
+                             int64_t b_b, const double* Cin, double* C, int64_t c_m, int64_t c_n, int64_t c_b,
+                             double alpha, double beta, int flags, void* stream) {
+  if (M < 1 || N < 1 || K < 1 || nbatch < 1 || !A || !B || !C || !A2 != !B2 || (flags & ~3)) return CC_ERR_ARG;
+  hipStream_t s = (hipStream_t)stream;
+  double* ws = nullptr;
+  cc_status st = CC_OK;
+  try {
+    GemmDesc d;
+    d.M = M; d.N = N; d.K = K;
+    d.nb0 = nbatch;
+    d.a_m = a_m; d.a_k = a_k; d.a_b0 = a_b;
+    d.b_k = b_k; d.b_n = b_n; d.b_b0 = b_b;
+    d.c_m = c_m; d.c_n = c_n; d.c_b0 = c_b;
+    d.alpha = alpha; d.beta = beta;
+    d.Cin = Cin;
+    d.ascending = flags & 1;
+    if (flags & 2) {
+      d.ws_elems = diag_splitk_elems(nbatch, M, N);
+      if (hipMalloc((void**)&ws, d.ws_elems * sizeof(double)) != hipSuccess) throw OomError("diag_gemm: split-K scratch");
+      d.ws = ws;
+    }
+    if (A2) gemm_sum(d, A, B, A2, B2, Prec::F64, Prec::F64, C, Prec::F64, Prec::F64, s);
+    else gemm64(d, A, B, C, s);
+    PNK_HIP(hipStreamSynchronize(s));
+  } catch (const ArgError&) {
+    st = CC_ERR_ARG;
+  } catch (const OomError&) {
+    (void)hipGetLastError();
+    st = CC_ERR_OOM;
+  } catch (const std::exception&) {
+    st = CC_ERR_HIP;
+  }
+  if (ws) (void)hipFree(ws);
+  return st;
+}
+
 }  // extern "C"
