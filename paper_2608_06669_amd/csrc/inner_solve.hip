@@ -531,7 +531,6 @@ __global__ __launch_bounds__(256) void inner_begin_kernel(const double* __restri
   fin[kInnerFinBNorm] = bn;
   fin[kInnerFinTol] = rtol * bn;
   fin[kInnerFinLimit] = limit;
-  fin[kInnerFinBHat] = bhat;
 }
 
 // A whole segment of the solve in one workgroup, for vectors of at most

@@ -40,7 +40,7 @@ constexpr int kInnerState = 16;    // doubles per state slot: two slots, then `f
 constexpr int kInnerMaxParts = 4096;
 // what the host reads after a batch of steps
 enum { kInnerFinSteps = 0, kInnerFinRes, kInnerFinBeta, kInnerFinBNorm, kInnerFinRead, kInnerFinTol = kInnerFinRead,
-       kInnerFinLimit, kInnerFinBHat };
+       kInnerFinLimit };
 
 struct InnerSolve {
   FockEigen eig;
@@ -54,7 +54,6 @@ struct InnerSolve {
   double *coef = nullptr;   // kInnerSegment x kInnerCoef
   double *state = nullptr;  // 3 x kInnerState
   double *norm_parts = nullptr;  // 2 x 16 kInnerMaxRows
-  int nparts() const { return blocks * segs; }
 };
 constexpr int kInnerMaxRows = 1024;  // workgroup rows of a launch over pairs
 constexpr int64_t kInnerPartsElems =
