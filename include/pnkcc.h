@@ -128,18 +128,22 @@ cc_status cc_fock_apply(cc_handle* h, const cc_problem* p, const double* x1, con
  * form, run on D^1/2 A_F D^1/2 with D = 2 on the singles and 1 on the
  * doubles (same solution; the scaled residual bounds the true one), in the
  * eigenvectors of f_oo and f_vv (an orthogonal change of basis, under which
- * its steps are the same). The cap is counted in whole blocks of steps.
- * Otherwise restarted GMRES (restart 30). Returns CC_NOT_CONVERGED when
- * maxit is reached first. Synchronises. */
+ * its steps are the same). The cap is maxit rounded up to a multiple of six;
+ * for the pair-symmetric form below, at the sizes where the A_F product works
+ * in 32-wide tiles (nvir up to 32, and others by nocc and nvir), up to a
+ * multiple of four less one, which is maxit - 1 where four divides maxit.
+ * Otherwise restarted GMRES (restart 30). Returns CC_NOT_CONVERGED when the
+ * cap is reached first. Synchronises. */
 cc_status cc_precond_solve(cc_handle* h, const cc_problem* p, const double* b1, const double* b2, double* x1,
                            double* x2, double rtol, int maxit, int* iters_out, void* stream);
 
 /* cc_precond_solve for a pair-symmetric right-hand side, b2[j][i][b][a] =
  * b2[i][j][a][b], as every closed-shell amplitude vector is (the residual,
- * J v and their preconditioned images). When f_ov = 0 the recurrence then
- * runs on the pairs i <= j only, which halves its memory traffic. What is solved is the pair-symmetric part of b
- * ((b2[i][j] + b2[j][i]^T) / 2); x is pair-symmetric. Same arguments and
- * errors as cc_precond_solve. */
+ * J v and their preconditioned images). When f_ov = 0 and nocc <= 31 the
+ * recurrence then runs on the pairs i <= j only, which halves its memory
+ * traffic: what is solved is the pair-symmetric part of b ((b2[i][j] +
+ * b2[j][i]^T) / 2), and x is pair-symmetric. Same arguments and errors as
+ * cc_precond_solve. */
 cc_status cc_precond_solve_pairsym(cc_handle* h, const cc_problem* p, const double* b1, const double* b2, double* x1,
                                    double* x2, double rtol, int maxit, int* iters_out, void* stream);
 
@@ -390,8 +394,9 @@ void cc_server_destroy(cc_server* s);
 /* Device timing of tagged work on the handle, with HIP events recorded on
  * the stream each launch runs on. Slots: 0 the particle-particle ladder
  * contraction (one launch per residual or J v), 1 whole residual
- * evaluations, 2 whole J v products, 3 A_F products
- * (in a symmetric inner solve its step launches), 4 inner A_F solves.
+ * evaluations, 2 whole J v products, 3 A_F products (in a symmetric inner
+ * solve its step launches, sampled; for vectors of at most 8192 elements the
+ * launches that each run up to 64 steps), 4 inner A_F solves.
  * cc_diag_timing(h, 1) enables and resets; cc_diag_timing_read synchronises
  * the recorded events and returns the launch count and total milliseconds
  * of one slot. */

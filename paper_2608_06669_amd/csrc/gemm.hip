@@ -1,7 +1,10 @@
 // Matrix-core GEMM for gfx950 (CDNA4), FP64 / FP32 / BF16 compute.
 //
-// FP64 products run in gemm_f64_pipe (gemm_f64.hpp), BF16 ones of packed
-// operands in gemm_pipe; the others in gemm_kernel:
+// FP64 products run in gemm_f64_pipe (gemm_f64.hpp), those of a short side and
+// a short contraction in gemm_smallk. BF16 and FP32 products of operands stored
+// in that type along k run in gemm_pipe, those of at most 32 rows or columns in
+// gemm_thin. The others (FP64: an operand contiguous along neither index) run
+// in gemm_kernel:
 //
 // One workgroup = 4 wavefronts of 64 lanes computes a BM x BN tile of C.
 // The waves form a WGM x WGN grid; each wave owns (BM/WGM) x (BN/WGN)
@@ -237,11 +240,14 @@ __global__ __launch_bounds__(256) void gemm_kernel(KArgs p) {
 // FP32 / BF16 products with at most 32 rows (M; a product with few columns
 // comes transposed): one wave per 16 columns and MT 16-row tiles, operands
 // straight from memory to registers, rounded there, U steps of 32 (BF16) or 16
-// (FP32) k ahead; no LDS, no barrier. The wide operand is read once and
-// used by MT instructions, so these products are HBM-bound: those of one BF16
-// J v at o = 20, v = 180 (1.2 GB, 1 to 20 rows) take 1.05 ms, where 64 x 64
-// tiles through LDS, mostly padding and one panel in flight, took 1.31; 20 x
-// 32400 x 20 in 20 batches 171 us with one step ahead, 212 with two.
+// (FP32) k ahead; no LDS, no barrier. The wide operand is read once and used
+// by MT instructions. Bound by the loads in flight: those of one BF16 J v at o =
+// 20, v = 180 read 2.1 GB in 0.79 ms, from 1.8 to 4.2 TB/s (a copy reaches 4.7),
+// the waves waiting for 40 to 70 % of their cycles and the matrix cores busy for
+// 4 %. Through LDS in 64 x 64 tiles, mostly padding and one panel in flight, J v
+// took 4.79 ms in place of 4.58, at o = 10, v = 90 1059 us in place of 970 (FP32
+// 1270 and 1186). 20 x 32400 x 20 in 20 batches takes 171 us with one step
+// ahead, 212 with two.
 // k order, chunks and roundings are those of gemm_kernel: same results.
 template <class Mma, typename TA, typename TB, int MT, int U>
 __global__ __launch_bounds__(256, U == 1 ? 4 : 2) void gemm_thin(KArgs p) {

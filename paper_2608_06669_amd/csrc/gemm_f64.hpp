@@ -88,8 +88,11 @@ static __device__ __align__(16) double zero_src[2];
 // while the panel before it is multiplied, so neither the LDS latency nor the
 // barrier is on the matrix cores' path.
 // Limits (MI355X, operands with full mantissas): the 4x4x4 instruction alone,
-// operands in registers, holds 72 TFLOP/s at the power limit; 3600^3 runs at
-// 62-65 (the former kernel, 16-deep panels in three stages with the fragments
+// operands in registers, sustains 72 TFLOP/s. In a residual at o = 20, v = 180
+// the matrix pipes are busy for 88 to 92 % of the cycles with 64 x 128 tiles, 80
+// with 64 x 64, 75 with 72 x 64 and 71 where both operands are contiguous along
+// their rows (LDS bank conflicts in 44 % of its cycles), at a clock of 2.1 to 2.3
+// GHz where lighter kernels get 2.4. 3600^3 runs at 62-65 (the former kernel, 16-deep panels in three stages with the fragments
 // read after the barrier, 1640-1710 us in place of 1441-1492), 1183^3 with
 // rows of odd length, which it could not take, at 37-41 (4-byte loads).
 // Tiles of 48, 72 or 80 rows serve row counts that multiples of 64 fit badly

@@ -325,8 +325,9 @@ int Solver::precond_solve_sym(const FockEigen& eig, VecIn b, VecOut x, double rt
   const int nshares = inner_load(q, b, Qi_ + 2 * n, Qi_ + 3 * n, kInnerSinglesScale, s);
   const int64_t rows = (q.n - (int64_t)eig.o * eig.v) / ((int64_t)eig.v * eig.v);
   if (eig.ut_v) inner_rotate_vir(eig, true, rows, q.v0, q.v1, s);
-  // the cap, in whole blocks of steps: six, or four less the first one's
-  // normalising launch where the packed step is of the short form
+  // The cap stays where callers have it, maxit in whole blocks of six steps, or
+  // of four launches with one step fewer, by the tiles of the A_F product
+  // (the device itself would stop after any step).
   const FockOp* op = eng_.fock_op();
   const int64_t cap = packed && op && op->bm == 32 ? 4 * ceil_div(maxit, 4) - 1 : 6 * ceil_div(maxit, 6);
   const int limit = (int)std::min<int64_t>(cap, 0x7fffffff);
