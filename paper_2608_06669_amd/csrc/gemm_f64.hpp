@@ -82,8 +82,8 @@ static __device__ __align__(16) double zero_src[2];
 // rows of any alignment and length take the same path.
 // Operands are read from LDS 16 bytes at a time: two consecutive k of a row
 // (k-contiguous panels, stored [row][8] with the four 16-byte chunks of a row
-// at slot chunk ^ ((row / 4) % 4), rows counted within the wave's half) or two consecutive rows at one k (stored
-// [k][rows]). Lanes 16 g .. 16 g + 15 take k = 2 g and 2 g + 1 of a panel, one
+// at slot chunk ^ ((row / 4) % 4), rows counted within the wave's half) or two
+// consecutive rows at one k (stored [k][rows]). Lanes 16 g .. 16 g + 15 take k = 2 g and 2 g + 1 of a panel, one
 // for each of its two instruction steps. The fragments of a panel are read
 // while the panel before it is multiplied, so neither the LDS latency nor the
 // barrier is on the matrix cores' path.
@@ -92,9 +92,10 @@ static __device__ __align__(16) double zero_src[2];
 // the matrix pipes are busy for 88 to 92 % of the cycles with 64 x 128 tiles, 80
 // with 64 x 64, 75 with 72 x 64 and 71 where both operands are contiguous along
 // their rows (LDS bank conflicts in 44 % of its cycles), at a clock of 2.1 to 2.3
-// GHz where lighter kernels get 2.4. 3600^3 runs at 62-65 (the former kernel, 16-deep panels in three stages with the fragments
-// read after the barrier, 1640-1710 us in place of 1441-1492), 1183^3 with
-// rows of odd length, which it could not take, at 37-41 (4-byte loads).
+// GHz where lighter kernels get 2.4. 3600^3 runs at 62-65 TFLOP/s (the former
+// kernel, 16-deep panels in three stages with the fragments read after the
+// barrier, 1640-1710 us in place of 1441-1492), 1183^3 with rows of odd length,
+// which it could not take, at 37-41 (4-byte loads).
 // Tiles of 48, 72 or 80 rows serve row counts that multiples of 64 fit badly
 // (the pair rows of the ladders): 136 x 12880 x 10440 takes 990 us with 72 rows
 // where 64 took 1430, 78 x 5360 x 4096 118 with 80 (142), 20 x 180 x 108000 126
@@ -124,7 +125,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_pipe(Args p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  const uint32_t item = blockIdx.y * gridDim.x + blockIdx.x;  // (the last row of the grid may pass the end)
+  // (a grid of several rows has this width; its last one may pass the end)
+  const uint32_t item = blockIdx.y * (uint32_t)kMaxGridX + blockIdx.x;
   if (item >= (uint32_t)(p.nfull + p.ntail * p.ts)) return;
   int tile, split = 0, nsplit = 1;
   if ((int)item < p.nfull) {
