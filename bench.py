@@ -40,12 +40,16 @@ HEADLINE = "c4_mixed"     # the default line
 # host baseline); the untimed FP64 reference
 # solve is skipped when it would not fit.
 RUN_BUDGET_S = 540.0
-# HBM bytes of one residual evaluation and of one step launch of the inner
-# solve from rocprofv3 FETCH_SIZE / WRITE_SIZE passes (each scaled by the same
-# counter for a copy of known size); None when a kernel has changed since the
-# counters were taken.
-RESIDUAL_TRAFFIC_BYTES = None
-INNER_STEP_TRAFFIC_BYTES = None
+# HBM bytes (read plus written) of one residual evaluation, of one BF16 J v and
+# of one step launch of the inner solve at o=20, v=180, naux=600, and of a step
+# launch at o=10, v=90, from the rocprofv3 FETCH_SIZE / WRITE_SIZE passes (each
+# scaled by the same counter for a copy of known size) in
+# profiles/residual_jvp_inner_counters.md; None when a kernel has changed since
+# the counters were taken.
+RESIDUAL_TRAFFIC_BYTES = 21811265472
+BF16_JVP_TRAFFIC_BYTES = 17395705376
+INNER_STEP_TRAFFIC_BYTES = 55471449
+C2_INNER_STEP_TRAFFIC_BYTES = 3955851
 
 
 def folded_residual_flops(o, v):
@@ -170,7 +174,7 @@ def bench_c2(args):
     if af_ms:
         gbs = af_bytes / (af_ms * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": gbs / HBM_PEAK_GBS, "traffic": None, "kernel": INNER_STEP_KERNEL,
+                "frac": gbs / HBM_PEAK_GBS, "traffic": C2_INNER_STEP_TRAFFIC_BYTES, "kernel": INNER_STEP_KERNEL,
                 "launches_timed": n_afm, "avg_us": af_ms * 1e3, "bytes_per_launch": af_bytes}
     out = {
         "metric": "PNK CCSD solves/s + p50/p99 latency at |dE|<1e-6 Eh; residual TFLOP/s vs FP64",
@@ -343,7 +347,7 @@ def bench_headline(args):
         jv_ms = ms_jvp / n_jvp
         tj = F_jv / (jv_ms * 1e-3) / 1e12
         roof_jvp = {"bound": "mfma", "achieved": tj, "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
-                    "frac": tj / BF16_PEAK_TFLOPS, "traffic": None,
+                    "frac": tj / BF16_PEAK_TFLOPS, "traffic": BF16_JVP_TRAFFIC_BYTES,
                     "kernel": "BF16 J v product (recorded graph: the tangent contractions in BF16 with float "
                               "accumulation, their FP64 operands rounded once per product)",
                     "launches_timed": n_jvp, "avg_ms": jv_ms, "flops_per_launch": F_jv}

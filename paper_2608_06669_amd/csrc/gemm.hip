@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(KArgs p) {
 // by MT instructions. Bound by the loads in flight: those of one BF16 J v at o =
 // 20, v = 180 read 2.1 GB in 0.79 ms, from 1.8 to 4.2 TB/s (a copy reaches 4.7),
 // the waves waiting for 40 to 70 % of their cycles and the matrix cores busy for
-// 4 %. Through LDS in 64 x 64 tiles, mostly padding and one panel in flight, J v
+// 1 %. Through LDS in 64 x 64 tiles, mostly padding and one panel in flight, J v
 // took 4.79 ms in place of 4.58, at o = 10, v = 90 1059 us in place of 970 (FP32
 // 1270 and 1186). 20 x 32400 x 20 in 20 batches takes 171 us with one step
 // ahead, 212 with two.

@@ -91,8 +91,8 @@ static __device__ __align__(16) double zero_src[2];
 // operands in registers, sustains 72 TFLOP/s. In a residual at o = 20, v = 180
 // the matrix pipes are busy for 88 to 92 % of the cycles with 64 x 128 tiles, 80
 // with 64 x 64, 75 with 72 x 64 and 71 where both operands are contiguous along
-// their rows (LDS bank conflicts in 44 % of its cycles), at a clock of 2.1 to 2.3
-// GHz where lighter kernels get 2.4. 3600^3 runs at 62-65 TFLOP/s (the former
+// their rows (LDS bank conflicts in 44 % of its cycles), at a clock of 2.0 to 2.3
+// GHz where the streaming kernels beside them get 2.5. 3600^3 runs at 62-65 TFLOP/s (the former
 // kernel, 16-deep panels in three stages with the fragments read after the
 // barrier, 1640-1710 us in place of 1441-1492), 1183^3 with rows of odd length,
 // which it could not take, at 37-41 (4-byte loads).
